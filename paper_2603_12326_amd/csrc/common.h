@@ -227,8 +227,11 @@ struct AsmArgs {
 };
 void launch_eps_assemble(const AsmArgs& a, const Chi0Geom& g, cplx* eps, hipStream_t st);
 // Gauss-Jordan diag(eps^-1) of n_w matrices; a zero or non-finite pivot in
-// matrix j sets *sing to at most w_base + j (atomic minimum)
-void launch_gj_diag(cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,
+// matrix j sets *sing to at most w_base + j (atomic minimum).  The matrices are
+// read from src; eps (src itself, or apart from it; not read or written up to
+// n_g = kGjRegMax) holds the sweep.  diag lies outside src.
+constexpr int kGjRegMax = 128;
+void launch_gj_diag(const cplx* src, cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,
                     int w_base = 0);
 // noLFE loss from diagonal-only partials of n_g G (chunk columns 0..n_g-1)
 // into loss[j * ldl + g0 + b]

@@ -207,12 +207,14 @@ inline int reject_capture(qcx_ctx* c) {
 }
 
 
-// Upload an index table unless the buffer already holds exactly these values
-// (the pair tables repeat from call to call); `last` mirrors what `b` last
+// do a[0 .. na) and b[0 .. nb) share memory?
+inline bool overlaps(const cplx* a, size_t na, const cplx* b, size_t nb) { return a < b + nb && b < a + na; }
+
+// Upload a table unless the buffer already holds exactly these values (pair
+// tables, G and frequency lists repeat from call to call); `last` mirrors what `b` last
 // received and must be the only record of writes to it.
-template <class B>
-inline hipError_t upload_cached(B* c, DevBuf& b, std::vector<int>& last,
-                                const std::vector<int>& v);
+template <class B, class T>
+inline hipError_t upload_cached(B* c, DevBuf& b, std::vector<T>& last, const std::vector<T>& v);
 
 // Begin a call that stages host data: take the next buffer of the ring and
 // wait until the copies staged in it kStageSlots calls ago have left it.  All
@@ -269,9 +271,8 @@ inline hipError_t upload(qcx_ctx* c, DevBuf& b, const T* src, size_t n, bool dev
   return hipStreamSynchronize(c->stream);
 }
 
-template <class B>
-inline hipError_t upload_cached(B* c, DevBuf& b, std::vector<int>& last,
-                                const std::vector<int>& v) {
+template <class B, class T>
+inline hipError_t upload_cached(B* c, DevBuf& b, std::vector<T>& last, const std::vector<T>& v) {
   if (b.p && !v.empty() && last == v) return hipSuccess;
   last.clear();  // unknown contents until the copy below is queued
   hipError_t e = upload(c, b, v.data(), v.size());

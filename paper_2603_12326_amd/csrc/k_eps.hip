@@ -108,31 +108,12 @@ __device__ inline bool bad_pivot(cplx v) {
   return !(m > 0.0 && m < INFINITY);
 }
 
-// 64-bit pivot key for a wave maximum: the modulus |re| + |im| in the high
-// bits (non-negative doubles order like their bit patterns), the complement
-// of the row index in the low 12 bits, so that moduli equal to 40 mantissa
-// bits go to the smaller row.  A NaN entry counts as infinite so that it still selects a
-// row (and poisons the result instead of hiding).  Every key is > 0.
-__device__ inline unsigned long long pivot_key(cplx v, int row) {
-  double mag = fabs(v.re) + fabs(v.im);
-  if (mag != mag) mag = INFINITY;
-  const unsigned long long b = (unsigned long long)__double_as_longlong(mag);
-  return (b & ~0xFFFull) | (unsigned long long)(0xFFF - row);
-}
-
 // An empty asm statement makes x opaque, so that choosing one element of a
 // register array by a run-time index (a == pa, b == jt / 16) stays a choice
 // between values instead of becoming an indexed load that would move the
 // whole array to scratch memory.
 __device__ inline cplx opaque(cplx x) {
   asm volatile("" : "+v"(x.re), "+v"(x.im));
-  return x;
-}
-
-// The same for an integer: row indices derived from it inside a loop are then
-// recomputed there instead of being hoisted (and spilled) as RP constants.
-__device__ inline int opaque_i(int x) {
-  asm volatile("" : "+v"(x));
   return x;
 }
 
@@ -153,46 +134,6 @@ __device__ inline cplx readlane_slot(const cplx (&c)[RP], int pa, int pl) {
   for (int a = 0; a < RP; ++a)
     if (a == pa) r = {readlane_d(c[a].re, pl), readlane_d(c[a].im, pl)};
   return r;
-}
-
-// Maximum of a 64-bit value over the wave: butterflies inside each row of 16
-// lanes by DPP (lane xor 1, xor 2, half-row mirror, row mirror), then the four
-// row results by readlane.  Needs every lane active.
-__device__ inline unsigned long long wave_max_u64(unsigned long long x) {
-  auto step = [&](auto ctrl) {
-    constexpr int c = decltype(ctrl)::value;
-    const int lo = __builtin_amdgcn_update_dpp((int)x, (int)x, c, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp((int)(x >> 32), (int)(x >> 32), c, 0xF, 0xF, false);
-    const unsigned long long o = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
-    x = o > x ? o : x;
-  };
-  step(std::integral_constant<int, 0xB1>{});   // quad_perm [1,0,3,2]
-  step(std::integral_constant<int, 0x4E>{});   // quad_perm [2,3,0,1]
-  step(std::integral_constant<int, 0x141>{});  // row_half_mirror
-  step(std::integral_constant<int, 0x140>{});  // row_mirror
-  unsigned long long r = 0ull;
-#pragma unroll
-  for (int row = 0; row < 4; ++row) {
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)x, 16 * row);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(x >> 32), 16 * row);
-    const unsigned long long o = ((unsigned long long)hi << 32) | lo;
-    r = o > r ? o : r;
-  }
-  return r;
-}
-
-// 32-bit pivot key: the high word of the modulus |re| + |im| as a double (its
-// exponent and 8 mantissa bits; non-negative doubles order like their bit
-// patterns, over the whole double range) with the low 12 bits replaced by the
-// complement of the row index, so that moduli equal to that precision go to
-// the smaller row.  Partial pivoting then takes a pivot within a factor
-// 1 - 2^-8 of the largest modulus.  A NaN entry counts as infinite.  Every key
-// of a live row is > 0 except for modulus 0.
-__device__ inline unsigned pivot_key32(cplx v, int row) {
-  double mag = fabs(v.re) + fabs(v.im);
-  if (mag != mag) mag = INFINITY;
-  const unsigned hi = (unsigned)((unsigned long long)__double_as_longlong(mag) >> 32);
-  return (hi & ~0xFFFu) | (unsigned)(0xFFF - row);
 }
 
 // Maximum of a 32-bit value over the wave: DPP butterflies inside each row of
@@ -236,6 +177,54 @@ __device__ inline cplx cinv_nr(cplx a) {
   return {ldexp(x * r, -e), ldexp(-y * r, -e)};
 }
 
+// 1/a by |a|^2 and the hardware reciprocal refined by two Newton steps where
+// |a|^2 is far from the ends of the range, cinv_nr elsewhere.
+__device__ inline cplx cinv_pivot(cplx a) {
+  const double d = fma(a.re, a.re, a.im * a.im);
+  if (!(d > 0x1p-900 && d < 0x1p900)) return cinv_nr(a);
+  double r = __builtin_amdgcn_rcp(d);
+  r = fma(r, fma(-d, r, 1.0), r);
+  r = fma(r, fma(-d, r, 1.0), r);
+  return {a.re * r, -a.im * r};
+}
+
+// The pivot of a column c (row l + 64 a in slot a of lane l): the live row
+// (bit a of live) of largest modulus |re| + |im| to 8 mantissa bits, then the
+// smaller row; a NaN counts above infinity.  Each lane keeps its best element,
+// so the pivot is read from lane p % 64 without a look at its slot.  Writes
+// u_i = (c_i - [i == p]) / piv to uc[64 RP] and returns p; wk = piv + 1.
+template <int RP>
+__device__ __forceinline__ int gj_choose(const cplx (&c)[RP], unsigned live, int l, cplx* uc, cplx& wk,
+                                         bool& singular) {
+  unsigned best = 0u;
+  cplx bv = {0.0, 0.0};
+#pragma unroll
+  for (int a = 0; a < RP; ++a) {
+    const double mag = fabs(c[a].re) + fabs(c[a].im);
+    const unsigned hi = (unsigned)((unsigned long long)__double_as_longlong(mag) >> 32);
+    const unsigned on = (unsigned)__builtin_amdgcn_sbfe((int)live, a, 1);
+    const unsigned key = ((hi & 0x7FFFF000u) | (unsigned)(0xFFF - (l + 64 * a))) & on;
+    const bool g = key > best;
+    best = g ? key : best;
+    bv.re = g ? c[a].re : bv.re;
+    bv.im = g ? c[a].im : bv.im;
+  }
+  best = wave_max_u32(best);
+  const int p = __builtin_amdgcn_readfirstlane(0xFFF - (int)(best & 0xFFFu));
+  const cplx pv = {readlane_d(bv.re, p & 63), readlane_d(bv.im, p & 63)};
+  const cplx inv = cinv_pivot(pv);
+#pragma unroll
+  for (int a = 0; a < RP; ++a) {
+    const int i = l + 64 * a;
+    cplx x = c[a];
+    x.re -= i == p ? 1.0 : 0.0;
+    uc[i] = cmul(x, inv);
+  }
+  if (bad_pivot(pv)) singular = true;
+  wk = {pv.re + 1.0, pv.im};
+  return p;
+}
+
 // Register-resident Gauss-Jordan for n <= 64 RP and n <= 16 CP with 16 waves:
 // lane l of wave v owns rows l + 64 a and columns v + 16 b, so column k lives
 // in wave k % 16 alone.  Step k applies m <- m - u w^T with the pivot folded
@@ -246,17 +235,18 @@ __device__ inline cplx cinv_nr(cplx a) {
 //
 // One barrier per step.  Between two barriers the wave that owns column k + 1
 // runs the chain that bounds the step: read p and u, update column k + 1,
-// choose its pivot (largest unused modulus by pivot_key32 and DPP maxima),
-// publish u and p through LDS.  It runs that chain before any of its other
-// columns, while the other waves do their FMAs.  Every wave then reads row p
-// of its columns from lane p % 64 with readlane (scalar registers, no LDS
+// choose its pivot and publish u and p through LDS (gj_choose).  It runs that
+// chain before any of its other columns, while the other waves do their FMAs.
+// Every wave then reads row p of its columns from lane p % 64 with readlane (scalar registers, no LDS
 // traffic: the LDS pipe is shared by all 16 waves); the row slot p / 64 is
 // dispatched once per step by a scalar branch, so the readlanes take the
 // registers in place instead of a VALU copy of the chosen slot.  u and p are
 // double-buffered by the parity of k; u is zero past row n; used-row marks
 // live in registers.
-// Body of one 1024-thread block: matrix A (n x n), diagonal of the inverse
-// into drow[n]; a zero pivot sets *sing to at most widx.
+// What bounds it is the issue of the FMAs and readlanes (1.5 us per step at
+// n = 113, 0.66 us with the chain alone).
+// Body of one 1024-thread block: matrix A (n x n, only read), diagonal of the
+// inverse into drow[n]; a zero pivot sets *sing to at most widx.
 template <int RP, int CP>
 __device__ __forceinline__ void gj_reg_body(const cplx* __restrict__ A, int n,
                                             cplx* __restrict__ drow, int* sing, int widx) {
@@ -275,37 +265,20 @@ __device__ __forceinline__ void gj_reg_body(const cplx* __restrict__ A, int n,
     }
   for (int e = tid; e < 2 * 64 * RP; e += 1024) (&ucol[0][0])[e] = {0.0, 0.0};
   __syncthreads();
-  unsigned used = 0;       // bit a: row l + 64 a already served as pivot
+  unsigned live = 0;       // bit a: row l + 64 a has not served as a pivot yet
+#pragma unroll
+  for (int a = 0; a < RP; ++a) live |= l + 64 * a < n ? 1u << a : 0u;
   bool singular = false;
   cplx wk = {0.0, 0.0};    // piv + 1 of the column this wave owns next
 
   // Owner wave of column kc (current values c): choose the pivot, publish u
   // into buffer pb, p and sor[p].
-  auto choose = [&](const cplx (&c)[RP], int kc, int pb) {
-    unsigned best = 0u;
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = l + 64 * a;
-      if (i < n && !((used >> a) & 1u)) best = max(best, pivot_key32(c[a], i));
-    }
-    best = wave_max_u32(best);
-    const int p = __builtin_amdgcn_readfirstlane(0xFFF - (int)(best & 0xFFFu));
-    const int pl = p & 63, pa = p >> 6;
-    const cplx pv = readlane_slot<RP>(c, pa, pl);
-    if (bad_pivot(pv)) singular = true;
-    const cplx inv = cinv_nr(pv);
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = l + 64 * a;
-      cplx x = c[a];
-      if (i == p) x.re -= 1.0;
-      if (i < n) ucol[pb][i] = cmul(x, inv);
-    }
+  auto choose = [&](const cplx (&c)[RP], int kc, int pb) __attribute__((always_inline)) {
+    const int p = gj_choose<RP>(c, live, l, ucol[pb], wk, singular);
     if (l == 0) {
       prow[pb] = p;
       sor[p] = kc;
     }
-    wk = {pv.re + 1.0, pv.im};
   };
 
   if (v == 0) {
@@ -332,7 +305,7 @@ __device__ __forceinline__ void gj_reg_body(const cplx* __restrict__ A, int n,
       cplx u[RP];
 #pragma unroll
       for (int a = 0; a < RP; ++a) u[a] = ucol[par][l + 64 * a];
-      if (l == pl) used |= 1u << pa;
+      if (l == pl) live &= ~(1u << pa);
       const int k1 = k + 1;
       const bool owner1 = k1 < n && v == k1 % NW;  // owns column k + 1
       const bool next = kk == NW - 1;               // column k + 1 in slot kb + 1
@@ -395,382 +368,243 @@ __device__ __forceinline__ void gj_reg_body(const cplx* __restrict__ A, int n,
   if (singular) atomicMin(sing, widx);
 }
 
-// Blocked Gauss-Jordan for 128 < n <= 64 RP (RP <= 16) with 1024 threads per
-// matrix; the matrix stays in global memory and is swept in panels of MB
-// columns, made of one or two sub-panels of 16.  For each panel:
-//  1. lane l of wave v holds rows l + 64 a of sub-panel column s0 + v in
-//     registers, and the sub-panel's 16 pivot steps run as in k_gj_reg (one
-//     barrier per step, the next column's owner chooses its pivot while the
-//     others update), restricted to the sub-panel's columns;
-//  2. with two sub-panels, the second one's columns first receive the first
-//     one's rank-16 update, and after their own sweep the first one's columns
-//     receive theirs (the same deferred update as below, on 16 columns), so
-//     that the panel holds what 32 single steps would leave there;
-//  3. every other column j receives the deferred rank-MB update
-//     T[:, j] += Z Y[:, j]  with Y = T[P][j] (the MB pivot rows before this
-//     update) and Z = swept panel with 1 subtracted at (p_a, a), one chunk of
-//     ZR rows of Z at a time.  With several chunks the pivot rows are left
-//     out of the chunk passes and updated in a last pass of their own, so
-//     that every chunk pass reads their old values; with one chunk they are
-//     updated with the other rows.
-// The update runs on FP64 MFMA (v_mfma_f64_16x16x4f64) as two real products
-// with K = 2 MB:  Re T += [Re Z | Im Z] [Re Y ; -Im Y],
-//                 Im T += [Re Z | Im Z] [Im Y ;  Re Y].
-// Z (chunks of ZR rows) and a JT-column tile of Y are staged in LDS k-major
-// (lane-consecutive rows / columns); each wave owns a 32 x 16 output block
-// (2 MFMA tiles, re and im) per tile and updates it in place.  Each Y tile is
-// loaded into registers while the previous tile's MFMAs run and stored into
-// the other of two LDS buffers: one barrier per column tile.
+// Blocked Gauss-Jordan over several workgroups per matrix for n > 128; the
+// matrix stays in global memory and is swept in panels of MB columns.  One
+// workgroup per matrix left most of the chip idle below 256 matrices, and its
+// updates waited on one L2 round trip after the other (n = 259, 175 matrices:
+// 0.5 ms of pivot steps, 1.3 ms of updates).  With a block per column tile the
+// updates fill the chip and the pivot steps, 1.9 us each (instruction issue of
+// the 16 waves of a sweep), bound it: 175 matrices of 259 1.09 ms (1.89 before),
+// 44 0.63 (1.72), 875 6.7 (9.7); 500 x 128 5.4 (11.6); 749 x 512 75 (87);
+// 953 x 16 10.0 (63), 953 x 256 79 (93).
+//
+// T[:, j] += Z Y[:, j] on the tile of MB columns j = jt .., by one block of NT
+// threads: Z = swept panel k0 .. with 1 subtracted at (p_a, a), Y the panel's
+// pivot rows before the update (staged in y).  FP64 MFMA on 16 x 16 blocks,
+// Re T += Re Z Re Y - Im Z Im Y, Im T += Re Z Im Y + Im Z Re Y; each wave takes
+// its Z fragments and its T block straight from L2 into registers.
 // MFMA layouts: A 16x4, lane l holds A[l%16][l/16]; B 4x16, lane l holds
 // B[l/16][l%16]; D 16x16, lane l holds D[4r + l/16][l%16], r = 0..3.
-// Panel shape by row class: up to 320 rows (RP <= 5) a panel is one sub-panel
-// of 16 columns and Z is staged in one chunk of every row (one pass per
-// panel); larger matrices take two sub-panels per panel (rank-32 updates,
-// half the passes over the matrix, which bound them) and Z in chunks of 128
-// rows, which is what fits the LDS with the wider panel.
-__host__ __device__ constexpr int gjp_nsub(int rp) { return rp <= 5 ? 1 : 2; }
-__host__ __device__ constexpr int gjp_zr(int rp) { return rp <= 5 ? 64 * rp : 128; }
-constexpr int GJP_MS = 16, GJP_JT = 64;
-
-template <int RP>
-__device__ __forceinline__ void gj_panel_body(cplx* __restrict__ A, int n,
-                                              cplx* __restrict__ drow, int* sing, int widx) {
-  constexpr int NW = 16, MS = GJP_MS, MB = gjp_nsub(RP) * MS, JT = GJP_JT, KR = 2 * MB,
-                ZR = gjp_zr(RP);
-  extern __shared__ __align__(16) char smem[];
-  double* Zt = reinterpret_cast<double*>(smem);    // [KR][ZR]: k' < MB Re Z, else Im Z
-  cplx* ucol = reinterpret_cast<cplx*>(smem);      // [2][64 RP] during the pivot steps
-  cplx* Ys = reinterpret_cast<cplx*>(Zt + (size_t)KR * ZR);  // [2][MB][JT]: Y tiles
-  int* piv = reinterpret_cast<int*>(Ys + 2 * MB * JT);  // [n] pivot row of step k
-  int* sor = piv + n;                               // [n] step of pivot row i
-  __shared__ int prow[2];
-  const int tid = threadIdx.x, l = tid & 63;
+// The pivot record of a matrix is S[4 k] = pivot row of step k, S[4 i + 1] =
+// step of pivot row i (-1: none yet), kept where its diagonal will go.
+template <int MB, int NT>
+__device__ __forceinline__ void gj_update(cplx* y, int* piv, const cplx* src, cplx* A, int n, const int* S,
+                                          int k0, int jt) {
+  constexpr int CT = MB / 16;
+  const int tid = threadIdx.x, l = tid & 63, li = l & 15, lk = l >> 4;
   const int v = __builtin_amdgcn_readfirstlane(tid >> 6);
-  unsigned used = 0;  // bit a: row l + 64 a already served as pivot
-  bool singular = false;
-  cplx wk = {0.0, 0.0};
-
-  auto choose = [&](const cplx (&c)[RP], int kc, int pb) {
-    const int lo = opaque_i(l);
-    unsigned long long best = 0ull;
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = lo + 64 * a;
-      if (i < n && !((used >> a) & 1u)) best = max(best, pivot_key(c[a], i));
-    }
-    best = wave_max_u64(best);
-    const int p = __builtin_amdgcn_readfirstlane(0xFFF - (int)(best & 0xFFFull));
-    const int pl = p & 63, pa = p >> 6;
-    cplx x = c[0];
-#pragma unroll
-    for (int a = 1; a < RP; ++a)
-      if (a == pa) x = opaque(c[a]);
-    const cplx pv = {readlane_d(x.re, pl), readlane_d(x.im, pl)};
-    if (bad_pivot(pv)) singular = true;
-    const cplx inv = cinv(pv);
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = lo + 64 * a;
-      cplx y = c[a];
-      if (i == p) y.re -= 1.0;
-      if (i < n) ucol[pb * 64 * RP + i] = cmul(y, inv);
-    }
-    if (l == 0) {
-      prow[pb] = p;
-      piv[kc] = p;
-      sor[p] = kc;
-    }
-    wk = {pv.re + 1.0, pv.im};
-  };
-  // Up to five row slots (N_G <= 320) the sweep takes the register kernel's
-  // short pivot chain (32-bit keys, the pivot read under a scalar branch on its
-  // slot, Newton-refined reciprocal, the owner at raised priority); the larger
-  // classes keep the form above, which spills fewer registers there.
-  constexpr bool SHORT = RP <= 5;
-  auto choose_short = [&](const cplx (&c)[RP], int kc, int pb) {
-    const int lo = opaque_i(l);
-    unsigned best = 0u;
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = lo + 64 * a;
-      if (i < n && !((used >> a) & 1u)) best = max(best, pivot_key32(c[a], i));
-    }
-    best = wave_max_u32(best);
-    const int p = __builtin_amdgcn_readfirstlane(0xFFF - (int)(best & 0xFFFu));
-    const int pl = p & 63, pa = p >> 6;
-    const cplx pv = readlane_slot<RP>(c, pa, pl);
-    if (bad_pivot(pv)) singular = true;
-    const cplx inv = cinv_nr(pv);
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = lo + 64 * a;
-      cplx y = c[a];
-      if (i == p) y.re -= 1.0;
-      if (i < n) ucol[pb * 64 * RP + i] = cmul(y, inv);
-    }
-    if (l == 0) {
-      prow[pb] = p;
-      piv[kc] = p;
-      sor[p] = kc;
-    }
-    wk = {pv.re + 1.0, pv.im};
-  };
-
-  auto load_col = [&](cplx (&pm)[RP], int jc) {
-    const int lo = opaque_i(l);
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = lo + 64 * a;
-      pm[a] = i < n ? A[(size_t)i * n + jc] : cplx{0.0, 0.0};
-    }
-  };
-  auto store_col = [&](const cplx (&pm)[RP], int jc) {
-    const int lo = opaque_i(l);
-#pragma unroll
-    for (int a = 0; a < RP; ++a) {
-      const int i = lo + 64 * a;
-      if (i < n) A[(size_t)i * n + jc] = pm[a];
-    }
-  };
-  // The deferred update of one column jc held in pm by the steps z0 .. z0 +
-  // zs - 1 (already swept, their columns in A):
-  //   pm[i] += sum_b (A[i][z0 + b] - [i == piv[z0 + b]]) A[piv[z0 + b]][jc],
-  // the second factor read from A, which still holds the column before it.
-  auto defer = [&](cplx (&pm)[RP], int jc, int z0, int zs) {
-    const int lo = opaque_i(l);
-    for (int b0 = 0; b0 < zs; b0 += 4) {
-      cplx y[4];
-      int pr[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int b = b0 + q;
-        pr[q] = b < zs ? piv[z0 + b] : -1;
-        y[q] = b < zs ? A[(size_t)pr[q] * n + jc] : cplx{0.0, 0.0};
-      }
-#pragma unroll
-      for (int a = 0; a < RP; ++a) {
-        const int i = lo + 64 * a;
-        if (i >= n) continue;
-        cplx acc = pm[a];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (b0 + q >= zs) continue;
-          cplx z = A[(size_t)i * n + z0 + b0 + q];
-          if (i == pr[q]) z.re -= 1.0;
-          acc.re = fma(z.re, y[q].re, acc.re);
-          acc.re = fma(-z.im, y[q].im, acc.re);
-          acc.im = fma(z.re, y[q].im, acc.im);
-          acc.im = fma(z.im, y[q].re, acc.im);
-        }
-        pm[a] = acc;
-      }
-    }
-  };
-  // The pivot steps s0 .. s0 + ms - 1 on their columns, held by waves v < ms
-  // in pm; each wave's column goes back to A afterwards.
-  auto sweep = [&](cplx (&pm)[RP], int s0, int ms) {
-    const bool hascol = v < ms;
-    if (v == 0) {
-      if constexpr (SHORT)
-        choose_short(pm, s0, s0 & 1);
-      else
-        choose(pm, s0, s0 & 1);
-    }
-    for (int kk = 0; kk < ms; ++kk) {
-      const int k = s0 + kk, par = k & 1;
-      // the owner of column k + 1 at raised priority until it has published
-      if (SHORT && v == kk + 1) __builtin_amdgcn_s_setprio(3);
-      __syncthreads();  // u, p of column k published
-      const int p = __builtin_amdgcn_readfirstlane(prow[par]);
-      const int pl = p & 63, pa = p >> 6;
-      if (l == pl) used |= 1u << pa;
-      if (hascol) {
-        const int lo = opaque_i(l);
-        cplx x = pm[0];
-#pragma unroll
-        for (int a = 1; a < RP; ++a)
-          if (!SHORT && a == pa) x = opaque(pm[a]);
-        cplx w = {readlane_d(x.re, pl), readlane_d(x.im, pl)};
-        if constexpr (SHORT) w = readlane_slot<RP>(pm, pa, pl);
-        if (v == kk) w = wk;  // owner of column k: w_k = piv + 1
-#pragma unroll
-        for (int a = 0; a < RP; ++a) {
-          const int i = lo + 64 * a;
-          const cplx u = i < n ? ucol[par * 64 * RP + i] : cplx{0.0, 0.0};
-          pm[a].re = fma(-u.re, w.re, pm[a].re);
-          pm[a].re = fma(u.im, w.im, pm[a].re);
-          pm[a].im = fma(-u.re, w.im, pm[a].im);
-          pm[a].im = fma(-u.im, w.re, pm[a].im);
-          // keep the scheduler from hoisting all RP loads of u at once
-          if ((a & 3) == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-        if (kk + 1 < ms && v == kk + 1) {
-          if constexpr (SHORT)
-            choose_short(pm, k + 1, par ^ 1);
-          else
-            choose(pm, k + 1, par ^ 1);
-        }
-      }
-      if (SHORT) __builtin_amdgcn_s_setprio(0);
-    }
-    if (hascol) store_col(pm, s0 + v);
-  };
-
-  for (int k0 = 0; k0 < n; k0 += MB) {
-    const int mb = min(MB, n - k0);
-    const int ms1 = min(MS, mb), ms2 = mb - ms1;
-    __syncthreads();  // the previous panel's update is complete
-    cplx pm[RP];
-    // first sub-panel
-    if (v < ms1) load_col(pm, k0 + v);
-    sweep(pm, k0, ms1);
-    if (ms2 > 0) {
-      __syncthreads();  // its swept columns in A; pivot buffers free
-      // second sub-panel: the first one's update, then its own steps
-      if (v < ms2) {
-        load_col(pm, k0 + ms1 + v);
-        defer(pm, k0 + ms1 + v, k0, ms1);
-      }
-      sweep(pm, k0 + ms1, ms2);
-      __syncthreads();  // its swept columns in A
-      // the first sub-panel's columns: the second one's update
-      if (v < ms1) {
-        load_col(pm, k0 + v);
-        defer(pm, k0 + v, k0 + ms1, ms2);
-        store_col(pm, k0 + v);
-      }
-    }
-    __syncthreads();  // swept panel in memory; pivot buffers free
-    // ---- deferred rank-mb update of every column outside the panel
-    const int nch = (n + ZR - 1) / ZR;
-    // With several chunks the panel's pivot rows are left out of the chunk
-    // passes (their Z rows are zero there) and updated in a pass of their own
-    // at the end, so every chunk pass reads Y = the pivot rows before this
-    // update straight from the matrix, and each Z chunk is staged once per
-    // panel.  With one chunk, a column tile's Y is staged before any of its
-    // columns changes, so the pivot rows take their update in the same pass
-    // (Z with 1 subtracted at (p_a, a)).
-    const bool one = nch == 1;
-    auto is_piv = [&](int i) {
-      bool f = false;
-      for (int a = 0; a < mb; ++a) f |= piv[k0 + a] == i;
-      return f;
-    };
-    auto load_z = [&](int r0) {
-      for (int e = tid; e < ZR * MB; e += 1024) {
-        const int r = e / MB, a = e % MB, i = r0 + r;
-        cplx z = {0.0, 0.0};
-        if (i < n && a < mb && (one || !is_piv(i))) {
-          z = A[(size_t)i * n + k0 + a];
-          if (i == piv[k0 + a]) z.re -= 1.0;
-        }
-        Zt[a * ZR + r] = z.re;
-        Zt[(MB + a) * ZR + r] = z.im;
-      }
-    };
-    // Z of the pivot rows: row r < mb is the pivot row of step k0 + r, with 1
-    // subtracted at (r, r)
-    auto load_zp = [&]() {
-      for (int e = tid; e < ZR * MB; e += 1024) {
-        const int r = e / MB, a = e % MB;
-        cplx z = {0.0, 0.0};
-        if (r < mb && a < mb) {
-          z = A[(size_t)piv[k0 + r] * n + k0 + a];
-          if (a == r) z.re -= 1.0;
-        }
-        Zt[a * ZR + r] = z.re;
-        Zt[(MB + a) * ZR + r] = z.im;
-      }
-    };
-    // Y tile of columns jt ..: two elements per thread, loaded into registers
-    // a tile ahead and stored into the other buffer after this tile's MFMAs
-    constexpr int YE = MB * JT / 1024;
-    cplx yreg[YE];
-    auto y_load = [&](int jt) {
-#pragma unroll
-      for (int q = 0; q < YE; ++q) {
-        const int e = tid + 1024 * q, a = e / JT, c = e % JT, j = jt + c;
-        yreg[q] = (a < mb && j < n) ? A[(size_t)piv[k0 + a] * n + j] : cplx{0.0, 0.0};
-      }
-    };
-    auto y_store = [&](int buf) {
-#pragma unroll
-      for (int q = 0; q < YE; ++q) Ys[buf * MB * JT + tid + 1024 * q] = yreg[q];
-    };
-    const int li = l & 15, lk = l >> 4;
-    // one 32 x 16 output block: rows r0 + 32 rb .. (the pivot rows of steps
-    // k0 + 32 rb .. in the pivot pass), columns jt + 16 cb ..  The B operands
-    // come from the stored Y: rows kr < MB give Re Y (for Re T) and Im Y (for
-    // Im T), rows kr >= MB give -Im Y and Re Y.
-    auto block = [&](int r0, int rb, int jt, int cb, int buf, bool pivot_pass) {
-      f64x4 acc[2][2];
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
-        acc[rt][0] = f64x4{0.0, 0.0, 0.0, 0.0};
-        acc[rt][1] = f64x4{0.0, 0.0, 0.0, 0.0};
-      }
-      const cplx* Yb = Ys + buf * MB * JT;
-#pragma unroll 2
-      for (int s = 0; s < KR / 4; ++s) {
-        const int kr = 4 * s + lk;
-        const cplx y = Yb[(kr % MB) * JT + 16 * cb + li];
-        const bool lower = 4 * s < MB;  // wave-uniform
-        const double br = lower ? y.re : -y.im, bi = lower ? y.im : y.re;
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-          const double za = Zt[kr * ZR + 32 * rb + 16 * rt + li];
-          acc[rt][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(za, br, acc[rt][0], 0, 0, 0);
-          acc[rt][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(za, bi, acc[rt][1], 0, 0, 0);
-        }
-      }
-      const int j = jt + 16 * cb + li;
-      if (j >= n || (j >= k0 && j < k0 + mb)) return;
-#pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int rr = 32 * rb + 16 * rt + 4 * r + lk;
-          if (pivot_pass ? rr >= mb : (rr >= ZR || r0 + rr >= n)) continue;
-          const int i = pivot_pass ? piv[k0 + rr] : r0 + rr;
-          cplx t = A[(size_t)i * n + j];
-          t.re += acc[rt][0][r];
-          t.im += acc[rt][1][r];
-          A[(size_t)i * n + j] = t;
-        }
-    };
-    // the column tiles of one pass (rows r0 .. of Z in Zt, or the pivot
-    // rows): Y of the first tile staged beforehand, one barrier per tile
-    auto pass = [&](int r0, bool pivot_pass) {
-      y_load(0);
-      y_store(0);
-      __syncthreads();  // Z and the first Y tile staged
-      int buf = 0;
-      for (int jt = 0; jt < n; jt += JT) {
-        const bool more = jt + JT < n;
-        if (more) y_load(jt + JT);
-        constexpr int NRB = ZR / 32, NU = NRB * (JT / 16);
-        if (pivot_pass) {
-          for (int u = v; u < JT / 16; u += NW) block(0, 0, jt, u, buf, true);
-        } else {
-          for (int u = v; u < NU; u += NW) block(r0, u % NRB, jt, u / NRB, buf, false);
-        }
-        if (more) y_store(buf ^ 1);
-        __syncthreads();  // this tile's Y reads and updates done; the next Y staged
-        buf ^= 1;
-      }
-    };
-    for (int c = 0; c < nch; ++c) {
-      load_z(c * ZR);
-      pass(c * ZR, false);
-    }
-    if (!one) {
-      load_zp();
-      pass(0, true);
-    }
+  const int mb = min(MB, n - k0);
+  const cplx* T = k0 ? A : src;
+  for (int e = tid; e < MB * MB; e += NT) {
+    const int a = e / MB, j = jt + e % MB;
+    const int pa = a < mb ? S[4 * (k0 + a)] : -1;
+    y[e] = (a < mb && j < n) ? T[(size_t)pa * n + j] : cplx{0.0, 0.0};
+    if (e % MB == 0) piv[a] = pa;
   }
   __syncthreads();
-  for (int k = tid; k < n; k += 1024) drow[k] = A[(size_t)piv[k] * n + sor[k]];
-  if (singular) atomicMin(sing, widx);
+  const int n_u = (n + 15) / 16 * CT;
+  for (int u = v; u < n_u; u += NT / 64) {
+    const int i0 = u / CT * 16, c0 = u % CT * 16, j = jt + c0 + li;
+    cplx z[MB / 4];
+#pragma unroll
+    for (int s = 0; s < MB / 4; ++s) {
+      const int a = 4 * s + lk, i = i0 + li;
+      z[s] = (i < n && a < mb) ? A[(size_t)i * n + k0 + a] : cplx{0.0, 0.0};
+    }
+    cplx t[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * r + lk;
+      t[r] = (i < n && j < n) ? T[(size_t)i * n + j] : cplx{0.0, 0.0};
+    }
+    f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = re;  // T is added once, at the end
+#pragma unroll
+    for (int s = 0; s < MB / 4; ++s) {
+      const int a = 4 * s + lk;
+      const cplx b = y[a * MB + c0 + li];
+      if (piv[a] == i0 + li) z[s].re -= 1.0;
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(z[s].re, b.re, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(z[s].re, b.im, im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(-z[s].im, b.im, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(z[s].im, b.re, im, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + 4 * r + lk;
+      if (i < n && j < n) A[(size_t)i * n + j] = cplx{t[r].re + re[r], t[r].im + im[r]};
+    }
+  }
+}
+
+template <int RP, int CP, int NW>
+struct GjTile {
+  static constexpr int MB = NW * CP, NT = 64 * NW;
+  struct Lds {
+    cplx y[MB * MB];
+    cplx ucol[2][64 * RP];
+    int piv[MB];
+    int prow[2];
+  };
+
+  // The pivot steps of panel s0 .. on its own columns (column s0 + NW b + v in
+  // slot b of wave v, row l + 64 a in lane l), steps as in gj_reg_body.
+  static __device__ __forceinline__ void sweep(Lds& L, const cplx* src, cplx* A, int n,
+                                               int* S, int s0, int* sing, int widx) {
+    const int tid = threadIdx.x, l = tid & 63;
+    const int v = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ms = min(MB, n - s0);
+    const cplx* T = s0 ? A : src;
+    unsigned live = 0;
+    bool singular = false;
+    cplx wk = {0.0, 0.0};
+    if (s0 == 0)
+      for (int i = tid; i < n; i += NT) S[4 * i + 1] = -1;
+#pragma unroll
+    for (int a = 0; a < RP; ++a) {
+      const int i = l + 64 * a;
+      if (i < n && (s0 == 0 || S[4 * i + 1] < 0)) live |= 1u << a;
+    }
+    cplx m[RP][CP];
+#pragma unroll
+    for (int b = 0; b < CP; ++b)
+#pragma unroll
+      for (int a = 0; a < RP; ++a) {
+        const int i = l + 64 * a, c = v + NW * b;
+        m[a][b] = (i < n && c < ms) ? T[(size_t)i * n + s0 + c] : cplx{0.0, 0.0};
+      }
+    for (int e = tid; e < 2 * 64 * RP; e += NT) (&L.ucol[0][0])[e] = {0.0, 0.0};
+    __syncthreads();
+    auto choose = [&](const cplx (&c)[RP], int kc, int pb) __attribute__((always_inline)) {
+      const int p = gj_choose<RP>(c, live, l, L.ucol[pb], wk, singular);
+      if (l == 0) {
+        L.prow[pb] = p;
+        L.piv[kc] = p;  // the record in S after the sweep: no global store waits at a barrier
+      }
+    };
+    if (v == 0) {
+      cplx c[RP];
+#pragma unroll
+      for (int a = 0; a < RP; ++a) c[a] = m[a][0];
+      choose(c, 0, 0);
+    }
+#pragma unroll
+    for (int kb = 0; kb < CP; ++kb) {
+      for (int kk = 0; kk < NW; ++kk) {
+        const int k = NW * kb + kk;
+        if (k >= ms) break;
+        const int par = k & 1;
+        if (v == (k + 1) % NW) __builtin_amdgcn_s_setprio(3);
+        __syncthreads();  // u, p of step k published
+        const int p = __builtin_amdgcn_readfirstlane(L.prow[par]);
+        const int pl = p & 63, pa = p >> 6;
+        if (l == pl) live &= ~(1u << pa);
+        auto update1 = [&](int b, cplx w) __attribute__((always_inline)) {
+#pragma unroll
+          for (int a = 0; a < RP; ++a) {
+            const cplx u = L.ucol[par][l + 64 * a];
+            m[a][b].re = fma(-u.re, w.re, m[a][b].re);
+            m[a][b].re = fma(u.im, w.im, m[a][b].re);
+            m[a][b].im = fma(-u.re, w.im, m[a][b].im);
+            m[a][b].im = fma(-u.im, w.re, m[a][b].im);
+          }
+        };
+        auto row = [&](int b) __attribute__((always_inline)) {
+          cplx c[RP];
+#pragma unroll
+          for (int a = 0; a < RP; ++a) c[a] = m[a][b];
+          return readlane_slot<RP>(c, pa, pl);
+        };
+        const bool next = kk == NW - 1;
+        const bool owner1 = k + 1 < ms && v == (k + 1) % NW;
+        auto step1 = [&](int b) __attribute__((always_inline)) {
+          update1(b, row(b));
+          cplx c[RP];
+#pragma unroll
+          for (int a = 0; a < RP; ++a) c[a] = m[a][b];
+          choose(c, k + 1, par ^ 1);
+        };
+        cplx w0 = wk;  // owner of column k: w_k = piv + 1
+        if (owner1) {
+          if (!next)
+            step1(kb);
+          else
+            step1(kb + 1 < CP ? kb + 1 : CP - 1);  // k + 1 < ms keeps kb + 1 < CP
+        }
+        __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+        for (int b = 0; b < CP; ++b) {
+          const bool done = owner1 && b == (next ? kb + 1 : kb);
+          if (done) continue;
+          update1(b, v == kk && b == kb ? w0 : row(b));
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < CP; ++b)
+#pragma unroll
+      for (int a = 0; a < RP; ++a) {
+        const int i = l + 64 * a, c = v + NW * b;
+        if (i < n && c < ms) A[(size_t)i * n + s0 + c] = m[a][b];
+      }
+    if (tid < ms) {
+      S[4 * (s0 + tid)] = L.piv[tid];
+      S[4 * L.piv[tid] + 1] = s0 + tid;
+    }
+    if (singular) atomicMin(sing, widx);
+  }
+
+  // Block y of a matrix in launch p (-1: the first sweep only).  Launch p gives
+  // every other column tile its update by panel p, one block per tile, and the
+  // block of tile p + 1 then sweeps its columns, the next panel: one launch per
+  // panel in a matrix's chain.
+  static __device__ __forceinline__ void run(const cplx* src, cplx* A, int n, cplx* drow,
+                                             int* sing, int widx, int p, int y) {
+    __shared__ Lds L;
+    const int n_t = (n + MB - 1) / MB;
+    int* S = reinterpret_cast<int*>(drow);
+    if (p >= n_t) return;
+    if (y > (p < 0 ? 0 : n_t - 2)) return;
+    const int t = p + 1 + y < n_t ? p + 1 + y : p + 1 + y - n_t;  // the next panel's tile first
+    if (p >= 0) {
+      gj_update<MB, NT>(L.y, L.piv, src, A, n, S, MB * p, MB * t);
+      if (t != p + 1) return;
+      __syncthreads();  // the tile's columns in memory
+    }
+    sweep(L, src, A, n, S, MB * (p + 1), sing, widx);
+  }
+};
+
+// The panel of 2 MB columns k0 .. by one block: its two halves swept in turn,
+// each half's update given to the other, so that it holds what 2 MB single
+// steps leave there.
+template <int RP, int CP, int NW>
+__device__ __forceinline__ void gj_panel2(const cplx* src, cplx* A, int n, cplx* drow, int* sing, int widx,
+                                          int k0) {
+  using G = GjTile<RP, CP, NW>;
+  __shared__ typename G::Lds L;
+  int* S = reinterpret_cast<int*>(drow);
+  if (k0 >= n) return;
+  G::sweep(L, src, A, n, S, k0, sing, widx);
+  if (k0 + G::MB >= n) return;
+  __syncthreads();  // the first half and its pivots in memory
+  gj_update<G::MB, G::NT>(L.y, L.piv, src, A, n, S, k0, k0 + G::MB);
+  __syncthreads();
+  G::sweep(L, src, A, n, S, k0 + G::MB, sing, widx);
+  __syncthreads();
+  gj_update<G::MB, G::NT>(L.y, L.piv, A, A, n, S, k0 + G::MB, k0);
+}
+
+// diag of the inverse from the swept matrix: [eps^-1]_kk sits at row piv[k],
+// column sor[k]; the pivot record in the diagonal's own storage is replaced
+__device__ __forceinline__ void gj_gather(const cplx* A, int n, cplx* drow) {
+  __shared__ int ps[2 * 1024];
+  const int* S = reinterpret_cast<const int*>(drow);
+  for (int k = threadIdx.x; k < n; k += blockDim.x) {
+    ps[2 * k] = S[4 * k];
+    ps[2 * k + 1] = S[4 * k + 1];
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < n; k += blockDim.x) drow[k] = A[(size_t)ps[2 * k] * n + ps[2 * k + 1]];
 }
 
 template <int RP, int CP>
@@ -780,40 +614,99 @@ __global__ void __launch_bounds__(1024) k_gj_reg(const cplx* __restrict__ eps, i
                       w_base + (int)blockIdx.x);
 }
 
-template <int RP>
-__global__ void __launch_bounds__(1024) k_gj_panel(cplx* __restrict__ eps, int n,
-                                                   cplx* __restrict__ diag, int* sing, int w_base) {
-  gj_panel_body<RP>(eps + (size_t)blockIdx.x * n * n, n, diag + (size_t)blockIdx.x * n, sing,
-                    w_base + (int)blockIdx.x);
-}
-
-// The job of this block in a multi-item launch: blocks [block0, block0 +
+// The job of a block in a multi-item launch: blocks [block0, block0 +
 // n_w) of a launch belong to job j (jobs sorted by block0).
-__device__ inline GjJob find_job(const GjJob* __restrict__ jobs, int n_jobs, int& w) {
+__device__ inline GjJob find_job(const GjJob* __restrict__ jobs, int n_jobs, int block, int& w) {
   int j = 0;
-  while (j + 1 < n_jobs && (int)blockIdx.x >= jobs[j + 1].block0) ++j;
-  w = (int)blockIdx.x - jobs[j].block0;
+  while (j + 1 < n_jobs && block >= jobs[j + 1].block0) ++j;
+  w = block - jobs[j].block0;
   return jobs[j];
 }
 
 template <int RP, int CP>
 __global__ void __launch_bounds__(1024) k_gj_reg_jobs(const GjJob* __restrict__ jobs, int n_jobs) {
   int w;
-  const GjJob J = find_job(jobs, n_jobs, w);
+  const GjJob J = find_job(jobs, n_jobs, blockIdx.x, w);
   gj_reg_body<RP, CP>(J.eps + (size_t)w * J.n * J.n, J.n, J.diag + (size_t)w * J.n, J.sing, w);
 }
 
-template <int RP>
-__global__ void __launch_bounds__(1024) k_gj_panel_jobs(const GjJob* __restrict__ jobs, int n_jobs) {
-  int w;
-  const GjJob J = find_job(jobs, n_jobs, w);
-  gj_panel_body<RP>(J.eps + (size_t)w * J.n * J.n, J.n, J.diag + (size_t)w * J.n, J.sing, w);
+// launch of panel p over n_w matrices (grid x, rounded up to 8 so that the
+// blocks of a matrix share an XCD) and their tiles (grid y)
+template <int RP, int CP, int NW>
+__global__ void __launch_bounds__(64 * NW) k_gj_tile(const cplx* src, cplx* A, int n, int n_w,
+                                                     cplx* diag, int* sing, int w_base, int p) {
+  const int w = blockIdx.x;
+  if (w >= n_w) return;
+  GjTile<RP, CP, NW>::run(src + (size_t)w * n * n, A + (size_t)w * n * n, n, diag + (size_t)w * n,
+                          sing, w_base + w, p, blockIdx.y);
 }
 
-size_t gj_panel_lds(int n, int rp) {
-  const int mb = gjp_nsub(rp) * GJP_MS;
-  return sizeof(double) * (size_t)(2 * mb) * gjp_zr(rp) + sizeof(cplx) * 2 * mb * GJP_JT +
-         sizeof(int) * 2 * (size_t)n;
+template <int RP, int CP, int NW>
+__global__ void __launch_bounds__(64 * NW) k_gj_tile_jobs(const GjJob* __restrict__ jobs, int n_jobs,
+                                                          int n_blocks, int p) {
+  if ((int)blockIdx.x >= n_blocks) return;
+  int w;
+  const GjJob J = find_job(jobs, n_jobs, blockIdx.x, w);
+  cplx* A = J.eps + (size_t)w * J.n * J.n;
+  GjTile<RP, CP, NW>::run(A, A, J.n, J.diag + (size_t)w * J.n, J.sing, w, p, blockIdx.y);
+}
+
+// The two launches per panel where the chip is full of matrices: their panels,
+// then the updates of every other tile by small blocks, those of a matrix
+// neighbours on one XCD (its Z stays in that L2).
+template <int RP>
+__global__ void __launch_bounds__(1024) k_gj_panel2(const cplx* src, cplx* A, int n, cplx* diag, int* sing,
+                                                    int w_base, int k0) {
+  const size_t w = blockIdx.x;
+  gj_panel2<RP, 1, 16>(src + w * n * n, A + w * n * n, n, diag + w * n, sing, w_base + (int)w, k0);
+}
+
+template <int RP>
+__global__ void __launch_bounds__(1024) k_gj_panel2_jobs(const GjJob* __restrict__ jobs, int n_jobs, int k0) {
+  int w;
+  const GjJob J = find_job(jobs, n_jobs, blockIdx.x, w);
+  cplx* A = J.eps + (size_t)w * J.n * J.n;
+  gj_panel2<RP, 1, 16>(A, A, J.n, J.diag + (size_t)w * J.n, J.sing, w, k0);
+}
+
+__device__ __forceinline__ bool gj_tile_of(int n_t, int n_w, int p, int& w, int& t) {
+  const int r = blockIdx.x / 8;
+  w = r / (n_t - 1) * 8 + blockIdx.x % 8;
+  t = r % (n_t - 1);
+  t += t >= p;
+  return w < n_w;
+}
+
+__global__ void __launch_bounds__(256) k_gj_update(const cplx* src, cplx* A, int n, int n_w, const cplx* diag,
+                                                   int p) {
+  __shared__ cplx y[32 * 32];
+  __shared__ int piv[32];
+  int w, t;
+  if (!gj_tile_of((n + 31) / 32, n_w, p, w, t)) return;
+  gj_update<32, 256>(y, piv, src + (size_t)w * n * n, A + (size_t)w * n * n, n,
+                     reinterpret_cast<const int*>(diag + (size_t)w * n), 32 * p, 32 * t);
+}
+
+__global__ void __launch_bounds__(256) k_gj_update_jobs(const GjJob* __restrict__ jobs, int n_jobs, int max_n,
+                                                        int n_w, int p) {
+  __shared__ cplx y[32 * 32];
+  __shared__ int piv[32];
+  int b, w, t;
+  if (!gj_tile_of((max_n + 31) / 32, n_w, p, b, t)) return;
+  const GjJob J = find_job(jobs, n_jobs, b, w);
+  if (32 * max(p, t) >= J.n) return;
+  cplx* A = J.eps + (size_t)w * J.n * J.n;
+  gj_update<32, 256>(y, piv, A, A, J.n, reinterpret_cast<const int*>(J.diag + (size_t)w * J.n), 32 * p, 32 * t);
+}
+
+__global__ void __launch_bounds__(256) k_gj_gather(const cplx* A, int n, cplx* diag) {
+  gj_gather(A + (size_t)blockIdx.x * n * n, n, diag + (size_t)blockIdx.x * n);
+}
+
+__global__ void __launch_bounds__(256) k_gj_gather_jobs(const GjJob* __restrict__ jobs, int n_jobs) {
+  int w;
+  const GjJob J = find_job(jobs, n_jobs, blockIdx.x, w);
+  gj_gather(J.eps + (size_t)w * J.n * J.n, J.n, J.diag + (size_t)w * J.n);
 }
 
 __global__ void k_nolfe(const cplx* eps, int n, int n_w, cplx* diag, int* sing, int w_base) {
@@ -898,36 +791,101 @@ int gj_class(int n_g) {
   return 8;  // beyond the inversion kernels: callers reject n_g > 1024
 }
 
-void launch_gj_diag(cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,
+namespace {
+
+// the launches of one class of tiled inversions: single (jobs null) or multi-item
+struct GjRun {
+  const cplx* src;
+  cplx* eps;
+  int n, n_w;  // the largest size, matrices
+  cplx* diag;
+  int *sing, w_base;
+  const GjJob* jobs;
+  int n_jobs;
+};
+
+void gj_gather(const GjRun& r, hipStream_t st) {
+  if (r.jobs)
+    hipLaunchKernelGGL(k_gj_gather_jobs, dim3(r.n_w), dim3(256), 0, st, r.jobs, r.n_jobs);
+  else
+    hipLaunchKernelGGL(k_gj_gather, dim3(r.n_w), dim3(256), 0, st, r.eps, r.n, r.diag);
+}
+
+template <int RP, int CP, int NW>
+void gj_tiles(const GjRun& r, hipStream_t st) {
+  constexpr int MB = NW * CP;
+  const int n_t = (r.n + MB - 1) / MB, bx = (r.n_w + 7) / 8 * 8;
+  for (int p = -1; p < n_t; ++p) {
+    const dim3 g(bx, p < 0 ? 1 : n_t - 1), b(64 * NW);
+    if (r.jobs)
+      hipLaunchKernelGGL((k_gj_tile_jobs<RP, CP, NW>), g, b, 0, st, r.jobs, r.n_jobs, r.n_w, p);
+    else
+      hipLaunchKernelGGL((k_gj_tile<RP, CP, NW>), g, b, 0, st, r.src, r.eps, r.n, r.n_w, r.diag, r.sing,
+                         r.w_base, p);
+  }
+  gj_gather(r, st);
+}
+
+template <int RP>
+void gj_panels(const GjRun& r, hipStream_t st) {
+  const int n_t = (r.n + 31) / 32, ub = (r.n_w + 7) / 8 * 8 * (n_t - 1);
+  for (int p = 0; p < n_t; ++p) {
+    if (r.jobs) {
+      hipLaunchKernelGGL(k_gj_panel2_jobs<RP>, dim3(r.n_w), dim3(1024), 0, st, r.jobs, r.n_jobs, 32 * p);
+      hipLaunchKernelGGL(k_gj_update_jobs, dim3(ub), dim3(256), 0, st, r.jobs, r.n_jobs, r.n, r.n_w, p);
+    } else {
+      hipLaunchKernelGGL(k_gj_panel2<RP>, dim3(r.n_w), dim3(1024), 0, st, r.src, r.eps, r.n, r.diag, r.sing,
+                         r.w_base, 32 * p);
+      hipLaunchKernelGGL(k_gj_update, dim3(ub), dim3(256), 0, st, r.src, r.eps, r.n, r.n_w, r.diag, p);
+    }
+  }
+  gj_gather(r, st);
+}
+
+// Which form.  One launch per panel (gj_tiles) keeps a matrix's chain short:
+// the next panel is swept beside the other tiles' updates.  It wins while the
+// sweeps leave compute units free for those; past that its 1024-thread update
+// blocks, one per compute unit, are the bound, and smaller ones win: 8 waves
+// holding four columns each up to n = 320, above it panels and updates in two
+// launches (gj_panels).  Measured, us (gj_tiles | the other): n = 259, 97
+// matrices 849 | 891, 160 1225 | 1095; n = 500, 128 5557 | 6276, 256 10963 |
+// 10522; n = 749, 64 11953 | 12945, 128 23417 | 21449; n = 953, 32 16881 |
+// 17715, 64 33785 | 26906.
+void gj_tiles(int cls, const GjRun& r, hipStream_t st) {
+  const bool few = r.n_w <= (cls == 7 ? 32 : cls == 6 ? 64 : 128);
+  switch (cls) {
+    case 2: return few ? gj_tiles<3, 2, 16>(r, st) : gj_tiles<3, 4, 8>(r, st);
+    case 3: return few ? gj_tiles<4, 2, 16>(r, st) : gj_tiles<4, 4, 8>(r, st);
+    case 4: return few ? gj_tiles<5, 2, 16>(r, st) : gj_tiles<5, 4, 8>(r, st);
+    case 5: return few ? gj_tiles<8, 2, 16>(r, st) : gj_panels<8>(r, st);
+    case 6: return few ? gj_tiles<12, 2, 16>(r, st) : gj_panels<12>(r, st);
+    case 7: return few ? gj_tiles<16, 1, 16>(r, st) : gj_panels<16>(r, st);
+    default: return;  // callers keep n_g <= 1024 (class 7); nothing is launched beyond
+  }
+}
+
+}  // namespace
+
+void launch_gj_diag(const cplx* src, cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,
                     int w_base) {
   const dim3 g(n_w), b(1024);
-  switch (gj_class(n_g)) {
-    case 0: hipLaunchKernelGGL((k_gj_reg<1, 4>), g, b, 0, st, eps, n_g, diag, sing, w_base); return;
-    case 1: hipLaunchKernelGGL((k_gj_reg<2, 8>), g, b, 0, st, eps, n_g, diag, sing, w_base); return;
-    case 2: hipLaunchKernelGGL(k_gj_panel<3>, g, b, gj_panel_lds(n_g, 3), st, eps, n_g, diag, sing, w_base); return;
-    case 3: hipLaunchKernelGGL(k_gj_panel<4>, g, b, gj_panel_lds(n_g, 4), st, eps, n_g, diag, sing, w_base); return;
-    case 4: hipLaunchKernelGGL(k_gj_panel<5>, g, b, gj_panel_lds(n_g, 5), st, eps, n_g, diag, sing, w_base); return;
-    case 5: hipLaunchKernelGGL(k_gj_panel<8>, g, b, gj_panel_lds(n_g, 8), st, eps, n_g, diag, sing, w_base); return;
-    case 6: hipLaunchKernelGGL(k_gj_panel<12>, g, b, gj_panel_lds(n_g, 12), st, eps, n_g, diag, sing, w_base); return;
-    case 7: hipLaunchKernelGGL(k_gj_panel<16>, g, b, gj_panel_lds(n_g, 16), st, eps, n_g, diag, sing, w_base); return;
-    default: break;
-  }
-  // callers keep n_g <= 1024 (class 7); nothing is launched beyond
+  const int cls = gj_class(n_g);
+  if (cls == 0)
+    hipLaunchKernelGGL((k_gj_reg<1, 4>), g, b, 0, st, src, n_g, diag, sing, w_base);
+  else if (cls == 1)
+    hipLaunchKernelGGL((k_gj_reg<2, 8>), g, b, 0, st, src, n_g, diag, sing, w_base);
+  else
+    gj_tiles(cls, GjRun{src, eps, n_g, n_w, diag, sing, w_base, nullptr, 0}, st);
 }
 
 void launch_gj_jobs(int cls, const GjJob* jobs, int n_jobs, int n_blocks, int max_n, hipStream_t st) {
   const dim3 g(n_blocks), b(1024);
-  switch (cls) {
-    case 0: hipLaunchKernelGGL((k_gj_reg_jobs<1, 4>), g, b, 0, st, jobs, n_jobs); return;
-    case 1: hipLaunchKernelGGL((k_gj_reg_jobs<2, 8>), g, b, 0, st, jobs, n_jobs); return;
-    case 2: hipLaunchKernelGGL(k_gj_panel_jobs<3>, g, b, gj_panel_lds(max_n, 3), st, jobs, n_jobs); return;
-    case 3: hipLaunchKernelGGL(k_gj_panel_jobs<4>, g, b, gj_panel_lds(max_n, 4), st, jobs, n_jobs); return;
-    case 4: hipLaunchKernelGGL(k_gj_panel_jobs<5>, g, b, gj_panel_lds(max_n, 5), st, jobs, n_jobs); return;
-    case 5: hipLaunchKernelGGL(k_gj_panel_jobs<8>, g, b, gj_panel_lds(max_n, 8), st, jobs, n_jobs); return;
-    case 6: hipLaunchKernelGGL(k_gj_panel_jobs<12>, g, b, gj_panel_lds(max_n, 12), st, jobs, n_jobs); return;
-    case 7: hipLaunchKernelGGL(k_gj_panel_jobs<16>, g, b, gj_panel_lds(max_n, 16), st, jobs, n_jobs); return;
-    default: return;
-  }
+  if (cls == 0)
+    hipLaunchKernelGGL((k_gj_reg_jobs<1, 4>), g, b, 0, st, jobs, n_jobs);
+  else if (cls == 1)
+    hipLaunchKernelGGL((k_gj_reg_jobs<2, 8>), g, b, 0, st, jobs, n_jobs);
+  else
+    gj_tiles(cls, GjRun{nullptr, nullptr, max_n, n_blocks, nullptr, nullptr, 0, jobs, n_jobs}, st);
 }
 
 void launch_nolfe_diag(const cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,

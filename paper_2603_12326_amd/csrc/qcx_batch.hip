@@ -464,7 +464,7 @@ int build_plan(qcx_ctx* ctx, qcx_ctx* const* ctxs, int n_ctx, const qcx_item* it
         launch_gj_jobs(g.cls, g.jobs.as<GjJob>(), g.n_jobs, g.n_blocks, g.max_n, cs);
       for (int i : single_gj) {
         PlanItem& it = P->items[i];
-        launch_gj_diag(it.eps.as<cplx>(), ctxs[it.ctx]->n_g, it.g.n_w, it.diag.as<cplx>(),
+        launch_gj_diag(it.eps.as<cplx>(), it.eps.as<cplx>(), ctxs[it.ctx]->n_g, it.g.n_w, it.diag.as<cplx>(),
                        P->d_sing.as<int>() + i, cs);
       }
     }

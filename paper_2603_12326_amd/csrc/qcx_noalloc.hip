@@ -72,9 +72,12 @@ int qcx_eps_inv_given_noalloc(qcx_ctx* ctx, int n_w, int n_G, const void* eps, i
     const int m = std::min(chunk, n_w - w0);
     cplx* diag = dout ? dout + (size_t)w0 * n : dscr;
     if (lfe) {
-      HIPCK(hipMemcpyAsync(work, src + (size_t)w0 * n * n, sizeof(cplx) * (size_t)m * n * n,
-                           hipMemcpyDeviceToDevice, st));
-      launch_gj_diag(work, n_G, m, diag, status_out, st, w0);
+      const cplx* from = src + (size_t)w0 * n * n;
+      if (overlaps(from, (size_t)m * n * n, diag, (size_t)m * n)) {  // diag inside eps: from a copy
+        HIPCK(hipMemcpyAsync(work, from, sizeof(cplx) * (size_t)m * n * n, hipMemcpyDeviceToDevice, st));
+        from = work;
+      }
+      launch_gj_diag(from, work, n_G, m, diag, status_out, st, w0);
     } else {
       launch_nolfe_diag(src + (size_t)w0 * n * n, n_G, m, diag, status_out, st, w0);
     }

@@ -1139,7 +1139,7 @@ int qcx_eps_inv(qcx_ctx* ctx, int lfe, void* diag_out, void* epsM_out) {
   launch_eps_assemble(a, g, ctx->d_eps.as<cplx>(), st);
   LAUNCHCK("eps_assemble");
   if (lfe)
-    launch_gj_diag(ctx->d_eps.as<cplx>(), n, nw, ctx->d_diag.as<cplx>(), ctx->d_sing.as<int>(), st);
+    launch_gj_diag(ctx->d_eps.as<cplx>(), ctx->d_eps.as<cplx>(), n, nw, ctx->d_diag.as<cplx>(), ctx->d_sing.as<int>(), st);
   else
     launch_nolfe_diag(ctx->d_eps.as<cplx>(), n, nw, ctx->d_diag.as<cplx>(), ctx->d_sing.as<int>(), st);
   LAUNCHCK("inverse");
@@ -1167,8 +1167,8 @@ int qcx_eps_inv_given(qcx_ctx* ctx, int n_w, int n_G, const void* eps, int lfe, 
   HIPCK(hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
   const size_t n = (size_t)n_G, nw = (size_t)n_w;
-  // the inversion overwrites its matrices: work on a copy
-  HIPCK(ctx->d_eps.reserve(sizeof(cplx) * nw * n * n));
+  // the inversion sweeps in the context's storage; up to kGjRegMax it needs none
+  if (lfe && n_G > kGjRegMax) HIPCK(ctx->d_eps.reserve(sizeof(cplx) * nw * n * n));
   cplx* diag = static_cast<cplx*>(diag_out);
   if (!diag) {
     HIPCK(ctx->d_diag.reserve(sizeof(cplx) * nw * n));
@@ -1177,13 +1177,18 @@ int qcx_eps_inv_given(qcx_ctx* ctx, int n_w, int n_G, const void* eps, int lfe, 
   HIPCK(ctx->d_sing.reserve(sizeof(int)));
   // the context's own inversion results are no longer the latest
   ctx->have_eps = false;
-  HIPCK(hipMemcpyAsync(ctx->d_eps.p, eps, sizeof(cplx) * nw * n * n, hipMemcpyDeviceToDevice, st));
+  const cplx* src = static_cast<const cplx*>(eps);
+  if (overlaps(src, nw * n * n, diag, nw * n)) {  // diag inside eps: from a copy
+    HIPCK(ctx->d_eps.reserve(sizeof(cplx) * nw * n * n));
+    HIPCK(hipMemcpyAsync(ctx->d_eps.p, eps, sizeof(cplx) * nw * n * n, hipMemcpyDeviceToDevice, st));
+    src = ctx->d_eps.as<cplx>();
+  }
   launch_set_int(ctx->d_sing.as<int>(), INT_MAX, st);
   ctx->sing_armed = true;
   if (lfe)
-    launch_gj_diag(ctx->d_eps.as<cplx>(), n_G, n_w, diag, ctx->d_sing.as<int>(), st);
+    launch_gj_diag(src, ctx->d_eps.as<cplx>(), n_G, n_w, diag, ctx->d_sing.as<int>(), st);
   else
-    launch_nolfe_diag(ctx->d_eps.as<cplx>(), n_G, n_w, diag, ctx->d_sing.as<int>(), st);
+    launch_nolfe_diag(src, n_G, n_w, diag, ctx->d_sing.as<int>(), st);
   LAUNCHCK("inverse (given eps)");
   launch_loss(diag, n_G, n_w, loss_out, static_cast<cplx*>(epsM_out), st);
   LAUNCHCK("loss (given eps)");

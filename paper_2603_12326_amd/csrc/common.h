@@ -73,10 +73,13 @@ struct ShellTab {
   int n_sh;
   int n_ao;
 };
+// The pieces of the pair densities take an optional device flag `run`: where
+// it is given and zero, they do nothing (densities queued before it is known
+// whether they are needed).
 // F[g][T][mu][nu] (G-major); pair_order lists the shell pairs sa * n_sh + sb
 // sorted by (l_a, l_b)
 void launch_cell_ft(const ShellTab& sh, const int* pair_order, const double* tvec, int n_t,
-                    const double* Q, int n_q, cplx* F, hipStream_t st);
+                    const double* Q, int n_q, cplx* F, hipStream_t st, const int* run = nullptr);
 // Pair densities in one pass (Bloch sum on FP64 MFMA, valence-first band
 // contraction, M in LDS only) into R[g][t] (stride ldt) for every k and the
 // n_g rows of F[g][T][mu][nu]; Cb holds the bra states.  rho_fused_fits:
@@ -84,7 +87,7 @@ void launch_cell_ft(const ShellTab& sh, const int* pair_order, const double* tve
 bool rho_fused_fits(int n_ao, int n_occ, int n_t);
 void launch_rho_fused(const cplx* F, const cplx* ph, const cplx* Ck, const cplx* Cb, int n_ao,
                       int n_b, int n_occ, int n_k, int n_t, int n_g, cplx* R, size_t ldt,
-                      hipStream_t st);
+                      hipStream_t st, const int* run = nullptr);
 // optical limit (App. C): D[c][T][mu][nu] = <chi_mu| d/dr_c |chi_nu(. - T)>
 // (real values in complex storage), and the G = 0 row R0[t] = -/+ i qhat.P / dt
 // from the band matrices Rp[c][t] (stride ldt) of the resonant / anti-resonant
@@ -119,9 +122,9 @@ struct Mat3 {
 // vq[g] = sqrt(4 pi)/|Q[g]| (the G = 0 row sqrt(4 pi) in the optical limit);
 // q is read from device memory
 void launch_q_plus_g(const double* q, const int* G_int, const double rec[9], int n_g, bool optical,
-                     double* Q, double* vq, hipStream_t st);
+                     double* Q, double* vq, hipStream_t st, const int* run = nullptr);
 // zero columns n_t .. ldt-1 of the n_g rows of R
-void launch_zero_tail(cplx* R, size_t ldt, int n_t, int n_g, hipStream_t st);
+void launch_zero_tail(cplx* R, size_t ldt, int n_t, int n_g, hipStream_t st, const int* run = nullptr);
 
 // chi0 pieces
 struct Chi0Geom {

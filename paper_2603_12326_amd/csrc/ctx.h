@@ -71,8 +71,9 @@ struct qcx_ctx {
   double tune_ms = 0.0;       // time spent tuning in the last qcx_chi0
   Geom64 geom64{};
   DevBuf d_w, d_A, d_Alo, d_R32, d_pairs, d_rows, d_pairs64, d_C, d_C64, d_XY, d_hwP;
-  // what d_pairs, d_rows and d_pairs64 last received (upload_cached)
-  std::vector<int> h_pairs_up, h_rows_up, h_pairs64_up;
+  // what d_pairs, d_rows, d_pairs64, d_G and d_w last received (upload_cached)
+  std::vector<int> h_pairs_up, h_rows_up, h_pairs64_up, h_G_up;
+  std::vector<double> h_w_up;
   // Kramers-Kronig route: energy order, sorted energies and sides, K ranges
   // per row tile, reduced bins, transform matrix
   DevBuf d_kk_rank, d_kk_ib, d_kk_xf, d_kk_chunks, d_kk_Rs, d_kk_S, d_kk_K;
@@ -166,7 +167,10 @@ int check_deferred(qcx_ctx* ctx);
 // device G list, tail zeroing, cell Fourier integrals, densities), so that
 // it can be captured into a graph.
 int rho_prepare(qcx_ctx* ctx, int n_G, const int* G_int, bool need_g0, bool optical);
-int rho_enqueue(qcx_ctx* ctx, const int* d_G, int n_G, bool optical, hipStream_t st);
+// With a device flag `run` the kernels do
+// nothing where it is zero (bases of the fused kernel only).
+int rho_enqueue(qcx_ctx* ctx, const int* d_G, int n_G, bool optical, hipStream_t st,
+                const int* run = nullptr);
 // address of the no-allocation scratch array on `device`, looked up once per
 // device with that device current (qcx_noalloc.hip)
 hipError_t noalloc_init(int device);

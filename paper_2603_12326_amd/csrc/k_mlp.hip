@@ -1,8 +1,8 @@
-// Kernels of the loss surrogate: a 5 -> 256x4 -> 1 SiLU network trained and
+// Kernels of the loss surrogate: a 49 -> 256x4 -> 1 SiLU network trained and
 // evaluated on the GPU.
 //
 // Arithmetic (BF16 weights, FP32 accumulation):
-//   layer 1 (5 inputs): FP32 on the vector ALUs with bf16-rounded weights;
+//   layer 1 (49 inputs): FP32 on the vector ALUs with bf16-rounded weights;
 //   layers 2..4: v_mfma_f32_32x32x16_bf16 on bf16(h) and bf16(W), FP32 sums;
 //   output: FP32 dot product of bf16(h4) and bf16(w5);
 //   backward: the same products with bf16(dz); bias gradients, the loss and
@@ -131,6 +131,158 @@ __global__ void __launch_bounds__(256) k_gemm_nt(const uint16_t* __restrict__ A,
       *reinterpret_cast<uint2*>(e.b.dZbT + (size_t)n * e.b.ldt + mb) = v;
     }
   }
+}
+
+// ---------------------------------------------------------------------------
+// Fused forward pass (inference): a block of 4 waves takes 128 (or 64) rows through
+// all layers of one member; their activations stay in LDS (one buffer of 128
+// rows x 256 bf16, rows padded by 16 bytes against bank conflicts; 66 KB, two
+// blocks per CU).  Layer 1 as in training: FP32 in the order of the features, four
+// neurons per lane with their weights in registers, the features of a row
+// (one address for the wave) in scalar registers.  The hidden products are taken transposed, D[neuron][row] =
+// W H^T: W fragments stream from L2 in operand order (1 KB per wave load, a
+// few K steps ahead), wave w owning neurons 64 w .. 64 w + 63, and the four
+// consecutive neurons that a lane holds of a row go back to LDS as one 8-byte
+// store.  The output layer is one more product, row 0 of whose W is w5.  Bound
+// by the vector units: layer 1 and the SiLUs beside the MFMAs.  Layer by layer
+// through memory (a launch per layer and member, 64 x 64 tiles) a query of
+// 100,489 points x 4 members took 1.15 ms, this way 0.39 ms.  64 rows per block
+// where 128 would give each CU fewer than two blocks two rounds running
+// (launch_forward).
+// ---------------------------------------------------------------------------
+constexpr int FW_LD = kW + 8;    // bf16 per row of activations
+// SiLU with the reciprocal from the hardware estimate and one Newton step
+// (the division's result to the last bit but for rare ties, at a third of its
+// instructions)
+__device__ inline float silu_nr(float z) {
+  const float d = 1.0f + __expf(fminf(-z, 80.0f));  // finite: below -80 the result is zero in bf16 terms
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(r, fmaf(-d, r, 1.0f), r);
+  return z * r;
+}
+
+template <int NG>
+__global__ void __launch_bounds__(256, 2) k_forward(const float* __restrict__ x, int n, FwdNets nets,
+                                                    float* __restrict__ y, int ldy) {
+  constexpr int FW_ROWS = 32 * NG, RW = FW_ROWS / 4;  // rows of a block, and of a wave in layer 1
+  __shared__ __attribute__((aligned(16))) uint16_t sH[FW_ROWS * FW_LD];
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = blockIdx.x * FW_ROWS;
+  const uint16_t* __restrict__ frag = nets.frag[blockIdx.y];
+  const float* __restrict__ p = nets.p[blockIdx.y];
+  {  // layer 1: lane's neurons 4 lane .. 4 lane + 3, rows of the wave one by one
+    float w[4][kIn], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = 4 * lane + u;
+      const bf16x8* W1 = reinterpret_cast<const bf16x8*>(frag) + (size_t)(j >> 5) * 4 * 64 + (j & 31);
+#pragma unroll
+      for (int c8 = 0; c8 < (kIn + 7) / 8; ++c8) {
+        const bf16x8 v = W1[(c8 >> 1) * 64 + (c8 & 1) * 32];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          if (8 * c8 + i < kIn) w[u][8 * c8 + i] = (float)v[i];
+      }
+      b[u] = p[kOffB1 + j];
+    }
+    for (int r = RW * wave; r < RW * wave + RW; ++r) {
+      const float* xr = x + (size_t)min(r0 + r, n - 1) * kIn;  // rows past the end: any, never written out
+      float z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) z[u] = b[u];
+#pragma unroll
+      for (int c = 0; c < kIn; ++c) {
+        const float xc = xr[c];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) z[u] = fmaf(xc, w[u][c], z[u]);
+      }
+      uint2 v;
+      v.x = to_bf16(silu_nr(z[0])) | ((uint32_t)to_bf16(silu_nr(z[1])) << 16);
+      v.y = to_bf16(silu_nr(z[2])) | ((uint32_t)to_bf16(silu_nr(z[3])) << 16);
+      *reinterpret_cast<uint2*>(&sH[r * FW_LD + 4 * lane]) = v;
+    }
+  }
+  f32x16 acc[2][NG];  // [neuron block][row block]
+  auto clear = [&] {
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[f][g][i] = 0.0f;
+  };
+  // bias, SiLU and the store of this wave's 64 neurons of all rows
+  auto store = [&](const float* __restrict__ bias) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int nb = 64 * wave + 32 * f + 8 * q + 4 * h;
+        float b[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b[i] = bias[nb + i];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+          uint16_t o[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[i] = to_bf16(silu_nr(acc[f][g][4 * q + i] + b[i]));
+          uint2 v;
+          v.x = o[0] | ((uint32_t)o[1] << 16);
+          v.y = o[2] | ((uint32_t)o[3] << 16);
+          *reinterpret_cast<uint2*>(&sH[(32 * g + (lane & 31)) * FW_LD + nb]) = v;
+        }
+      }
+  };
+  const bf16x8* WL = reinterpret_cast<const bf16x8*>(frag + kFrag1) + (size_t)(2 * wave) * 16 * 64 + lane;
+  constexpr int AHEAD = 4;  // K steps of W in flight
+  for (int l = 0; l < 3; ++l) {
+    const bf16x8* W = WL + (size_t)l * (kFragL / 8);
+    bf16x8 w[AHEAD][2];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) {
+      w[k][0] = W[k * 64];
+      w[k][1] = W[(16 + k) * 64];
+    }
+    __syncthreads();  // every wave is done reading the previous layer
+    if (l > 0) {
+      store(p + kOffW2 + (l - 1) * kLayerStride + kW * kW);
+      __syncthreads();
+    }
+    clear();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const bf16x8 w0 = w[k % AHEAD][0], w1 = w[k % AHEAD][1];
+      if (k + AHEAD < 16) {
+        w[k % AHEAD][0] = W[(k + AHEAD) * 64];
+        w[k % AHEAD][1] = W[(16 + k + AHEAD) * 64];
+      }
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const bf16x8 b =
+            *reinterpret_cast<const bf16x8*>(&sH[(32 * g + (lane & 31)) * FW_LD + 16 * k + 8 * h]);
+        acc[0][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w0, b, acc[0][g], 0, 0, 0);
+        acc[1][g] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, b, acc[1][g], 0, 0, 0);
+      }
+    }
+  }
+  __syncthreads();
+  store(p + kOffW2 + 2 * kLayerStride + kW * kW);
+  __syncthreads();
+  // output: wave w takes row block w
+  if (wave >= NG) return;
+  const bf16x8* W5 = reinterpret_cast<const bf16x8*>(frag + kFrag1 + 3 * kFragL) + lane;
+  f32x16 o;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) o[i] = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const bf16x8 b =
+        *reinterpret_cast<const bf16x8*>(&sH[(32 * wave + (lane & 31)) * FW_LD + 16 * k + 8 * h]);
+    o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(W5[k * 64], b, o, 0, 0, 0);
+  }
+  const int r = r0 + 32 * wave + (lane & 31);
+  if (h == 0 && r < n) y[(size_t)blockIdx.y * ldy + r] = o[0] + p[kOffB5];
 }
 
 // ---------------------------------------------------------------------------
@@ -363,6 +515,27 @@ __global__ void k_adam(float* p, const float* __restrict__ g, float* m, float* v
   p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
+// element e of the fragment copy of the weights (see WeightsB::frag)
+__device__ inline float frag_value(const float* __restrict__ p, int e) {
+  const int j = e & 7, l = (e >> 3) & 63, row = l & 31, k8 = 8 * (l >> 5) + j;
+  if (e < kFrag1) {
+    const int f = e >> 9, k = 16 * (f & 3) + k8;
+    return k < kIn ? p[kOffW1 + (32 * (f >> 2) + row) * kIn + k] : 0.0f;
+  }
+  e -= kFrag1;
+  if (e < 3 * kFragL) {
+    const int f = (e % kFragL) >> 9;
+    return p[kOffW2 + (e / kFragL) * kLayerStride + (32 * (f >> 4) + row) * kW + 16 * (f & 15) + k8];
+  }
+  e -= 3 * kFragL;
+  return row == 0 ? p[kOffW5 + 16 * (e >> 9) + k8] : 0.0f;
+}
+
+__global__ void k_fragments(const float* __restrict__ p, WeightsB wb) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e < kFragAll) wb.frag[e] = to_bf16(frag_value(p, e));
+}
+
 __global__ void k_refresh(const float* __restrict__ p, WeightsB wb) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < kW * kIn) wb.w1[i] = to_bf16(p[kOffW1 + i]);
@@ -403,12 +576,15 @@ __global__ void __launch_bounds__(256) k_mean(const float* __restrict__ sq, int 
 // which is how the loss of a crystal depends on the part of Q inside the
 // zone; the Fourier features give the first layer scales finer than the
 // plain coordinates.
-__global__ void k_encode(const double* __restrict__ qw, const double* __restrict__ loss, int n,
-                         double qmax, double wmax, Lattice lat, double mu, double sigma, float* x,
-                         float* t) {
+// The queries are qw[n][4], or, with n_g > 0, the grid of n_g momenta qw[n_g][3]
+// at the frequencies ws (frequency-major).
+__global__ void k_encode(const double* __restrict__ qw, const double* __restrict__ ws, int n_g,
+                         const double* __restrict__ loss, int n, double qmax, double wmax, Lattice lat,
+                         double mu, double sigma, float* x, float* t) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const double qx = qw[4 * i], qy = qw[4 * i + 1], qz = qw[4 * i + 2], w = qw[4 * i + 3];
+  const double* qp = n_g ? qw + 3 * (i % n_g) : qw + 4 * (size_t)i;
+  const double qx = qp[0], qy = qp[1], qz = qp[2], w = n_g ? ws[i / n_g] : qp[3];
   const double q = sqrt(qx * qx + qy * qy + qz * qz);
   const double inv = q > 0.0 ? 1.0 / q : 0.0;
   float* xi = x + (size_t)kIn * i;
@@ -444,8 +620,9 @@ __global__ void k_encode(const double* __restrict__ qw, const double* __restrict
 }
 
 __global__ void k_decode(const float* __restrict__ ys, int K, int n, double mu, double sigma,
-                         double calib, double* loss, double* err) {
+                         double calib, double* loss, double* err, int* clear, int n_clear) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n_clear) clear[i] = 0;
   if (i >= n) return;
   double s = 0.0, s2 = 0.0;
   for (int k = 0; k < K; ++k) {
@@ -554,6 +731,17 @@ void launch_gemm_store(const uint16_t* A, const uint16_t* B, int M, int N, int K
                        nullptr);
 }
 
+void launch_forward(const float* x, int n, const FwdNets& nets, int n_nets, float* y, int ldy,
+                    hipStream_t st) {
+  // blocks of 64 rows where those of 128 would not fill two rounds of two blocks
+  // per CU
+  const int nb = (n + 127) / 128;
+  if (nb * n_nets <= 1024)
+    hipLaunchKernelGGL(k_forward<2>, dim3((n + 63) / 64, n_nets), dim3(256), 0, st, x, n, nets, y, ldy);
+  else
+    hipLaunchKernelGGL(k_forward<4>, dim3(nb, n_nets), dim3(256), 0, st, x, n, nets, y, ldy);
+}
+
 void launch_layer1(const float* x, const int* order, long off, int n, int rows_p,
                    const uint16_t* w1b, const float* b1, float* Z1, uint16_t* H1b, uint16_t* H1T,
                    int ldt, hipStream_t st) {
@@ -604,6 +792,10 @@ void launch_adam(float* p, const float* g, float* m, float* v, int n, float lr, 
                      beta2, c1, c2, eps);
 }
 
+void launch_fragments(const float* p, const WeightsB& wb, hipStream_t st) {
+  hipLaunchKernelGGL(k_fragments, dim3((kFragAll + 255) / 256), dim3(256), 0, st, p, wb);
+}
+
 void launch_refresh(const float* p, const WeightsB& wb, hipStream_t st) {
   hipLaunchKernelGGL(k_refresh, dim3(kW * kW / 256), dim3(256), 0, st, p, wb);
 }
@@ -612,17 +804,18 @@ void launch_mean(const float* sq, int rows, int n, float* out, hipStream_t st) {
   hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, sq, rows, n, out);
 }
 
-void launch_encode(const double* qw, const double* loss, int n, double qmax, double wmax,
-                   const Lattice& lat, double mu, double sigma, float* x, float* t,
+void launch_encode(const double* qw, const double* ws, int n_g, const double* loss, int n, double qmax,
+                   double wmax, const Lattice& lat, double mu, double sigma, float* x, float* t,
                    hipStream_t st) {
-  hipLaunchKernelGGL(k_encode, dim3((n + 255) / 256), dim3(256), 0, st, qw, loss, n, qmax, wmax,
+  hipLaunchKernelGGL(k_encode, dim3((n + 255) / 256), dim3(256), 0, st, qw, ws, n_g, loss, n, qmax, wmax,
                      lat, mu, sigma, x, t);
 }
 
 void launch_decode(const float* ys, int K, int n, double mu, double sigma, double calib,
-                   double* loss, double* err, hipStream_t st) {
-  hipLaunchKernelGGL(k_decode, dim3((n + 255) / 256), dim3(256), 0, st, ys, K, n, mu, sigma,
-                     calib, loss, err);
+                   double* loss, double* err, int* clear, int n_clear, hipStream_t st) {
+  const int nt = n > n_clear ? n : n_clear;
+  hipLaunchKernelGGL(k_decode, dim3((nt + 255) / 256), dim3(256), 0, st, ys, K, n, mu, sigma,
+                     calib, loss, err, clear, n_clear);
 }
 
 int select_blocks(int n) { return (n + SEL_BLOCK - 1) / SEL_BLOCK; }

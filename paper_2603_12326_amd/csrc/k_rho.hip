@@ -206,7 +206,8 @@ __device__ void pair_block(double a, double b, const double* A, const double* B,
 __global__ void __launch_bounds__(256) k_cell_ft(ShellTab sh, const int* __restrict__ pair_order,
                                                  const double* __restrict__ tvec, int n_t,
                                                  const double* __restrict__ Q, int n_q,
-                                                 cplx* __restrict__ F) {
+                                                 cplx* __restrict__ F, const int* run) {
+  if (run && !*run) return;
   const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const long per_pair = (long)n_t * n_q;
   if (tid >= per_pair * sh.n_sh * sh.n_sh) return;
@@ -764,10 +765,10 @@ __global__ void __launch_bounds__(256) k_orth_check(const cplx* __restrict__ S,
 }  // namespace
 
 void launch_cell_ft(const ShellTab& sh, const int* pair_order, const double* tvec, int n_t,
-                    const double* Q, int n_q, cplx* F, hipStream_t st) {
+                    const double* Q, int n_q, cplx* F, hipStream_t st, const int* run) {
   const long total = (long)sh.n_sh * sh.n_sh * n_t * n_q;
   hipLaunchKernelGGL(k_cell_ft, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, sh,
-                     pair_order, tvec, n_t, Q, n_q, F);
+                     pair_order, tvec, n_t, Q, n_q, F, run);
 }
 
 void launch_grad_ft(const ShellTab& sh, const double* tvec, int n_t, cplx* D, hipStream_t st) {
@@ -929,9 +930,10 @@ void launch_state_flags(const double* Ek, const double* Ekq, int n_k, int n_b, i
 // G = 0 row keeps sqrt(4 pi) alone: its 1/|q| goes into the k.p row.  The
 // host rejects a vanishing q + G before enqueueing; such a row would get 0.
 __global__ void k_q_plus_g(const double* __restrict__ q, const int* __restrict__ G, Mat3 rec,
-                           int n_g, int optical, double* __restrict__ Q, double* __restrict__ vq) {
+                           int n_g, int optical, double* __restrict__ Q, double* __restrict__ vq,
+                           const int* run) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_g) return;
+  if (g >= n_g || (run && !*run)) return;
   double n2 = 0.0;
   for (int x = 0; x < 3; ++x) {
     double v = q[x];
@@ -945,7 +947,8 @@ __global__ void k_q_plus_g(const double* __restrict__ q, const int* __restrict__
 
 // Zero the columns n_t..ldt-1 of every row of R[n_g][ldt] (readers that work
 // in K chunks run past n_t into them)
-__global__ void k_zero_tail(cplx* R, size_t ldt, int n_t, int n_g) {
+__global__ void k_zero_tail(cplx* R, size_t ldt, int n_t, int n_g, const int* run) {
+  if (run && !*run) return;
   const size_t tail = ldt - n_t;
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= tail * n_g) return;
@@ -953,18 +956,18 @@ __global__ void k_zero_tail(cplx* R, size_t ldt, int n_t, int n_g) {
 }
 
 void launch_q_plus_g(const double* q, const int* G, const double rec[9], int n_g, bool optical,
-                     double* Q, double* vq, hipStream_t st) {
+                     double* Q, double* vq, hipStream_t st, const int* run) {
   Mat3 r;
   for (int i = 0; i < 9; ++i) r.m[i] = rec[i];
   hipLaunchKernelGGL(k_q_plus_g, dim3((n_g + 255) / 256), dim3(256), 0, st, q, G, r, n_g,
-                     optical ? 1 : 0, Q, vq);
+                     optical ? 1 : 0, Q, vq, run);
 }
 
-void launch_zero_tail(cplx* R, size_t ldt, int n_t, int n_g, hipStream_t st) {
+void launch_zero_tail(cplx* R, size_t ldt, int n_t, int n_g, hipStream_t st, const int* run) {
   const size_t n = (ldt - n_t) * (size_t)n_g;
   if (n == 0) return;
   hipLaunchKernelGGL(k_zero_tail, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, R, ldt, n_t,
-                     n_g);
+                     n_g, run);
 }
 
 void launch_orth_check(const cplx* S, const cplx* C, int n_ao, int n_b, int n_k, double* dev,

@@ -81,7 +81,8 @@ __global__ void __launch_bounds__(512) k_rho_fused(const cplx* __restrict__ F,
                                                    const cplx* __restrict__ Ck,
                                                    const cplx* __restrict__ Cb, int n_ao, int n_b,
                                                    int n_occ, int n_k, int n_t, int n_g, int gs,
-                                                   int ks, cplx* __restrict__ R, size_t ldt) {
+                                                   int ks, cplx* __restrict__ R, size_t ldt, const int* run) {
+  if (run && !*run) return;
   constexpr int NA4 = 4 * NQ;
   // two chunks of M tiles [tile][pair in tile][k] (chunk s in buffer s % 2);
   // after the chunks X [mu][v][k] in the first
@@ -332,7 +333,7 @@ bool rho_fused_fits(int n_ao, int n_occ, int n_t) {
 
 void launch_rho_fused(const cplx* F, const cplx* ph, const cplx* Ck, const cplx* Cb, int n_ao,
                       int n_b, int n_occ, int n_k, int n_t, int n_g, cplx* R, size_t ldt,
-                      hipStream_t st) {
+                      hipStream_t st, const int* run) {
   const int nq = (n_ao + 3) / 4;
   const int n_kt = (n_k + kKT - 1) / kKT;
   const int gs = 4, ks = n_kt < 8 ? n_kt : 8;
@@ -341,7 +342,7 @@ void launch_rho_fused(const cplx* F, const cplx* ph, const cplx* Ck, const cplx*
 #define QCX_RF(N)                                                                               \
   case N:                                                                                       \
     hipLaunchKernelGGL(k_rho_fused<N>, grid, dim3(512), 0, st, F, ph, Ck, Cb, n_ao, n_b, n_occ, \
-                       n_k, n_t, n_g, gs, ks, R, ldt);                                          \
+                       n_k, n_t, n_g, gs, ks, R, ldt, run);                                     \
     return;
   switch (nq) {
     QCX_RF(1)

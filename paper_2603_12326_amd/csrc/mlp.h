@@ -34,6 +34,20 @@ struct WeightsB {
   uint16_t* w[3];     // layers 2..4, [out][in]
   uint16_t* wt[3];    // layers 2..4, [in][out]
   uint16_t* w5;       // [256]
+  // the same weights in the A-operand order of v_mfma_f32_32x32x16_bf16 for the
+  // fused forward pass: fragments of 64 lanes x 8, lane l holding row l % 32,
+  // k = 8 (l / 32) .. + 7 of a 32 x 16 block; layer 1 (K padded to 64) as [8
+  // row blocks][4], layers 2..4 as [8][16], the output layer as one row block
+  // whose row 0 is w5 and whose other rows are zero [16]
+  uint16_t* frag;
+};
+constexpr int kFrag1 = 8 * 4 * 512, kFragL = 8 * 16 * 512, kFrag5 = 16 * 512;
+constexpr int kFragAll = kFrag1 + 3 * kFragL + kFrag5;
+constexpr int kMaxMembers = 16;
+// members evaluated by one fused launch
+struct FwdNets {
+  const uint16_t* frag[kMaxMembers];
+  const float* p[kMaxMembers];  // FP32 parameters (biases)
 };
 
 // Epilogue variants of the bf16 NT GEMM C[M][N] = sum_k A[m][k] B[n][k].
@@ -62,6 +76,11 @@ int store_ksplit(int K);
 void launch_gemm_store(const uint16_t* A, const uint16_t* B, int M, int N, int K, float* C,
                        float* P, hipStream_t st);
 
+// y[k * ldy + r] for the rows r < n of x and the first n_nets members: all layers
+// in one kernel, activations in LDS
+void launch_forward(const float* x, int n, const FwdNets& nets, int n_nets, float* y, int ldy,
+                    hipStream_t st);
+
 // first layer: rows r < n read x[idx(r)] (idx = order[off + r] or r), rows
 // n..rows_p-1 read zeros
 void launch_layer1(const float* x, const int* order, long off, int n, int rows_p,
@@ -89,7 +108,8 @@ void launch_w1_grad(const float* dZ1, const float* x, const int* order, long off
                     float* dW1, float* db1, float* P, hipStream_t st);
 void launch_adam(float* p, const float* g, float* m, float* v, int n, float lr, float beta1,
                  float beta2, float c1, float c2, float eps, hipStream_t st);
-void launch_refresh(const float* p, const WeightsB& wb, hipStream_t st);
+void launch_refresh(const float* p, const WeightsB& wb, hipStream_t st);    // all but frag
+void launch_fragments(const float* p, const WeightsB& wb, hipStream_t st);  // frag, after the last step
 // sum of sq[0..rows) / n into *out
 void launch_mean(const float* sq, int rows, int n, float* out, hipStream_t st);
 
@@ -98,12 +118,14 @@ void launch_mean(const float* sq, int rows, int n, float* out, hipStream_t st);
 struct Lattice {
   double a[9];  // primitive vectors a_i = (a[3i], a[3i+1], a[3i+2]), bohr
 };
-void launch_encode(const double* qw, const double* loss, int n, double qmax, double wmax,
-                   const Lattice& lat, double mu, double sigma, float* x, float* t,
+// queries qw[n][4], or (n_g > 0) the grid of momenta qw[n_g][3] x frequencies ws
+void launch_encode(const double* qw, const double* ws, int n_g, const double* loss, int n, double qmax,
+                   double wmax, const Lattice& lat, double mu, double sigma, float* x, float* t,
                    hipStream_t st);
-// ensemble of K outputs ys[k][n] -> loss = exp(mu + sigma mean), err = calib sigma sd
+// ensemble of K outputs ys[k][n] -> loss = exp(mu + sigma mean), err = calib sigma sd;
+// also clears n_clear ints
 void launch_decode(const float* ys, int K, int n, double mu, double sigma, double calib,
-                   double* loss, double* err, hipStream_t st);
+                   double* loss, double* err, int* clear, int n_clear, hipStream_t st);
 // indices i with err[i] > tol, ascending, count in *count (device int)
 void launch_select(const double* err, int n, double tol, int* block_counts, int n_blocks,
                    int* idx, int* count, hipStream_t st);

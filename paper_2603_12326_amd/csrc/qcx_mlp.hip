@@ -13,7 +13,7 @@ namespace {
 
 struct Member {
   DevBuf p, m, v, g;                    // FP32 parameters, Adam moments, gradient
-  DevBuf w1b, w[3], wt[3], w5b;         // bf16 copies
+  DevBuf w1b, w[3], wt[3], w5b, frag;   // bf16 copies
   long step = 0;
   WeightsB wb() const {
     WeightsB b;
@@ -23,16 +23,16 @@ struct Member {
       b.wt[l] = wt[l].as<uint16_t>();
     }
     b.w5 = w5b.as<uint16_t>();
+    b.frag = frag.as<uint16_t>();
     return b;
   }
   void release() {
-    DevBuf* all[] = {&p, &m, &v, &g, &w1b, &w[0], &w[1], &w[2], &wt[0], &wt[1], &wt[2], &w5b};
+    DevBuf* all[] = {&p, &m, &v, &g, &w1b, &w[0], &w[1], &w[2], &wt[0], &wt[1], &wt[2], &w5b, &frag};
     for (DevBuf* b : all) b->release();
   }
 };
 
 constexpr int kMaxBatch = 16384;   // training rows per step
-constexpr int kInferChunk = 65536; // rows per inference pass
 
 }  // namespace
 
@@ -44,9 +44,12 @@ struct qcx_mlp {
   DevBuf Z[4], Hb[4], HT[3], dZ[2], dZb[2], dZbT[2], y, dy, sq, hist, flag, red;
   // inference / query workspace
   DevBuf xq, ys, sel_counts;
-  // qcx_mlp_infer: Q list, frequencies, the query grid, estimates, rejected
-  // indices, the method's rows and where they go
-  DevBuf iQ, iw, iqw, ierr, iidx, irows, isel;
+  // qcx_mlp_infer: Q list, frequencies, estimates, rejected frequencies
+  DevBuf iQ, iw, ierr, iflag;
+  std::vector<double> h_w;  // what iw last received
+  int* h_flag = nullptr;  // pinned copy of iflag
+  int h_flag_cap = 0;
+  hipEvent_t ev_flag = nullptr;
   int cap_query = 0;
   double qmax = 1.0, wmax = 1.0, mu = 0.0, sigma = 1.0, calib = 1.0;
   Lattice lat{};
@@ -55,33 +58,31 @@ struct qcx_mlp {
     for (Member& m : mem) m.release();
     DevBuf* all[] = {&Z[0], &Z[1], &Z[2], &Z[3], &Hb[0], &Hb[1], &Hb[2], &Hb[3], &HT[0], &HT[1],
                      &HT[2], &dZ[0], &dZ[1], &dZb[0], &dZb[1], &dZbT[0], &dZbT[1], &y, &dy, &sq,
-                     &hist, &flag, &red, &xq, &ys, &sel_counts, &iQ, &iw, &iqw, &ierr, &iidx, &irows,
-                     &isel};
+                     &hist, &flag, &red, &xq, &ys, &sel_counts, &iQ, &iw, &ierr, &iflag};
     for (DevBuf* b : all) b->release();
+    if (h_flag) (void)hipHostFree(h_flag);
+    if (ev_flag) (void)hipEventDestroy(ev_flag);
   }
 };
 
 namespace {
 
-// qw[(iw, g)] = (Q_g, w_iw): the query grid of one momentum, w-major.
-__global__ void k_fill_qw(const double* __restrict__ Q, int n_g, const double* __restrict__ w,
-                          int n_w, double* qw) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)n_g * n_w) return;
-  const int g = (int)(i % n_g), iw = (int)(i / n_g);
-  qw[4 * i] = Q[3 * g];
-  qw[4 * i + 1] = Q[3 * g + 1];
-  qw[4 * i + 2] = Q[3 * g + 2];
-  qw[4 * i + 3] = w[iw];
-}
-
-// out[sel[r]][g] = rows[r][g]: the method's rows into the answer.
-__global__ void k_scatter_rows(const double* __restrict__ rows, const int* __restrict__ sel,
-                               int n_sel, int n_g, double* out) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)n_sel * n_g) return;
-  const int r = (int)(i / n_g), g = (int)(i % n_g);
-  out[(size_t)sel[r] * n_g + g] = rows[i];
+// Row w of out = row r of rows where flag[w] is set, r the flags set before w:
+// the method's rows into the answer.  One block per row of out.
+__global__ void __launch_bounds__(256) k_scatter_rows(const double* __restrict__ rows,
+                                                      const int* __restrict__ flag, int n_g,
+                                                      double* __restrict__ out) {
+  __shared__ int part[4];
+  const int w = blockIdx.x;
+  if (!flag[w]) return;
+  int r = 0;
+  for (int i = threadIdx.x; i < w; i += 256) r += flag[i];
+#pragma unroll
+  for (int d = 32; d; d >>= 1) r += __shfl_xor(r, d);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = r;
+  __syncthreads();
+  r = part[0] + part[1] + part[2] + part[3];
+  for (int g = threadIdx.x; g < n_g; g += 256) out[(size_t)w * n_g + g] = rows[(size_t)r * n_g + g];
 }
 
 // The error estimate of each point in units of its curve's maximum (the
@@ -90,69 +91,100 @@ __global__ void k_scatter_rows(const double* __restrict__ rows, const int* __res
 // e being the estimate relative to the point's own value, so that e bounds
 // |L - L_method| / max_w |L| where the relative estimate bounds the relative
 // error.  A non-finite estimate or prediction becomes infinite (rejected).
-__global__ void k_normwise_err(const double* __restrict__ L, double* __restrict__ e, int n_w,
-                               int n_g) {
-  const int g = blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_g) return;
+// flag[w] is set where a point of row w exceeds tol, and flag[n_w] with any of
+// them (cleared by the caller).
+// A block takes 16 G, 16 frequencies at a time.
+__global__ void __launch_bounds__(256) k_normwise_err(const double* __restrict__ L, double* __restrict__ e,
+                                                      int n_w, int n_g, double tol, int* __restrict__ flag) {
+  __shared__ double part[16][17];
+  const int g = blockIdx.x * 16 + (threadIdx.x & 15), w0 = threadIdx.x >> 4;
   double mx = 0.0;
-  for (int w = 0; w < n_w; ++w) mx = fmax(mx, fabs(L[(size_t)w * n_g + g]));
+  if (g < n_g)
+    for (int w = w0; w < n_w; w += 16) mx = fmax(mx, fabs(L[(size_t)w * n_g + g]));
+  part[w0][threadIdx.x & 15] = mx;
+  __syncthreads();
+  if (g >= n_g) return;
+  for (int i = 0; i < 16; ++i) mx = fmax(mx, part[i][threadIdx.x & 15]);
   const double s = mx > 0.0 ? 1.0 / mx : 0.0;
-  for (int w = 0; w < n_w; ++w) {
+  for (int w = w0; w < n_w; w += 16) {
     const size_t i = (size_t)w * n_g + g;
-    const double v = e[i] * fabs(L[i]) * s;
-    e[i] = v == v ? v : INFINITY;
+    double v = e[i] * fabs(L[i]) * s;
+    v = v == v ? v : INFINITY;
+    e[i] = v;
+    if (v > tol) flag[w] = flag[n_w] = 1;  // every writer stores the same
   }
 }
 
-int reserve_rows(qcx_mlp* m, int rows_p, bool training) {
+// pinned copy of n flags, and the event after its last copy
+int reserve_flags(qcx_mlp* m, int n) {
+  qcx_ctx* ctx = m->ctx;
+  if (!m->ev_flag) HIPCK(hipEventCreateWithFlags(&m->ev_flag, hipEventDisableTiming));
+  if (m->h_flag_cap >= n) return QCX_OK;
+  if (m->h_flag) {
+    HIPCK(hipStreamSynchronize(ctx->stream));  // a call that failed may have left a copy in flight
+    (void)hipHostFree(m->h_flag);
+  }
+  m->h_flag = nullptr;
+  m->h_flag_cap = 0;
+  HIPCK(hipHostMalloc((void**)&m->h_flag, sizeof(int) * (size_t)n));
+  m->h_flag_cap = n;
+  return QCX_OK;
+}
+
+// training workspace of rows_p rows
+int reserve_rows(qcx_mlp* m, int rows_p) {
   qcx_ctx* ctx = m->ctx;
   const size_t r = (size_t)rows_p;
   for (int l = 0; l < 4; ++l) {
     HIPCK(m->Hb[l].reserve(sizeof(uint16_t) * r * kW));
-    if (training) HIPCK(m->Z[l].reserve(sizeof(float) * r * kW));
+    HIPCK(m->Z[l].reserve(sizeof(float) * r * kW));
   }
-  if (training) {
-    for (int l = 0; l < 3; ++l) HIPCK(m->HT[l].reserve(sizeof(uint16_t) * r * kW));
-    for (int s = 0; s < 2; ++s) {
-      HIPCK(m->dZ[s].reserve(sizeof(float) * r * kW));
-      HIPCK(m->dZb[s].reserve(sizeof(uint16_t) * r * kW));
-      HIPCK(m->dZbT[s].reserve(sizeof(uint16_t) * r * kW));
-    }
-    HIPCK(m->dy.reserve(sizeof(float) * r));
-    HIPCK(m->sq.reserve(sizeof(float) * r));
-    HIPCK(m->red.reserve(sizeof(float) * std::max(red_floats(rows_p),
-                                                   (size_t)store_ksplit(rows_p) * kW * kW)));
+  for (int l = 0; l < 3; ++l) HIPCK(m->HT[l].reserve(sizeof(uint16_t) * r * kW));
+  for (int s = 0; s < 2; ++s) {
+    HIPCK(m->dZ[s].reserve(sizeof(float) * r * kW));
+    HIPCK(m->dZb[s].reserve(sizeof(uint16_t) * r * kW));
+    HIPCK(m->dZbT[s].reserve(sizeof(uint16_t) * r * kW));
   }
+  HIPCK(m->dy.reserve(sizeof(float) * r));
+  HIPCK(m->sq.reserve(sizeof(float) * r));
+  HIPCK(m->red.reserve(sizeof(float) * std::max(red_floats(rows_p), (size_t)store_ksplit(rows_p) * kW * kW)));
   HIPCK(m->y.reserve(sizeof(float) * r));
   return QCX_OK;
 }
 
-// forward of one member over n rows of x (rows of order[off..] when order is
-// set); training keeps Z, Hb and the transposes for the backward pass
+// training forward of one member over n rows of x (rows of order[off..] when
+// order is set): keeps Z, Hb and the transposes for the backward pass
 void forward_rows(qcx_mlp* m, const Member& w, const float* x, const int* order, long off, int n,
-                  int rows_p, bool training, float* y, hipStream_t st) {
+                  int rows_p, hipStream_t st) {
   WeightsB wb = w.wb();
   const float* p = w.p.as<float>();
-  launch_layer1(x, order, off, n, rows_p, wb.w1, p + kOffB1, training ? m->Z[0].as<float>() : nullptr,
-                m->Hb[0].as<uint16_t>(), training ? m->HT[0].as<uint16_t>() : nullptr, rows_p, st);
+  launch_layer1(x, order, off, n, rows_p, wb.w1, p + kOffB1, m->Z[0].as<float>(),
+                m->Hb[0].as<uint16_t>(), m->HT[0].as<uint16_t>(), rows_p, st);
   for (int l = 2; l <= 4; ++l) {
     EpiFwd e;
     e.bias = p + off_b(l);
-    e.Z = training ? m->Z[l - 1].as<float>() : nullptr;
+    e.Z = m->Z[l - 1].as<float>();
     e.Hb = m->Hb[l - 1].as<uint16_t>();
-    e.HT = (training && l < 4) ? m->HT[l - 1].as<uint16_t>() : nullptr;
+    e.HT = l < 4 ? m->HT[l - 1].as<uint16_t>() : nullptr;
     e.ldt = rows_p;
     launch_gemm_fwd(m->Hb[l - 2].as<uint16_t>(), wb.w[l - 2], rows_p, kW, kW, e, st);
   }
-  if (!training)
-    launch_output(m->Hb[3].as<uint16_t>(), wb.w5, p + kOffB5, n, rows_p, y, nullptr, nullptr, 0,
-                  nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, 0, st);
+}
+
+// outputs of members [k0, k0 + n_nets) for n rows of x into y[k][ldy]
+void infer_rows(qcx_mlp* m, int k0, int n_nets, const float* x, int n, float* y, int ldy, hipStream_t st) {
+  FwdNets nets{};
+  for (int k = 0; k < n_nets; ++k) {
+    nets.frag[k] = m->mem[k0 + k].frag.as<uint16_t>();
+    nets.p[k] = m->mem[k0 + k].p.as<float>();
+  }
+  launch_forward(x, n, nets, n_nets, y, ldy, st);
 }
 
 // one gradient evaluation into w.g; the mean squared error into *loss_dev
 void grad_rows(qcx_mlp* m, Member& w, const float* x, const float* t, const int* order, long off,
                int n, int rows_p, float* loss_dev, hipStream_t st) {
-  forward_rows(m, w, x, order, off, n, rows_p, true, nullptr, st);
+  forward_rows(m, w, x, order, off, n, rows_p, st);
   WeightsB wb = w.wb();
   const float* p = w.p.as<float>();
   float* g = w.g.as<float>();
@@ -179,6 +211,23 @@ void grad_rows(qcx_mlp* m, Member& w, const float* x, const float* t, const int*
   }
   launch_w1_grad(m->dZ[s].as<float>(), x, order, off, n, g + kOffW1, g + kOffB1, red, st);
   launch_mean(m->sq.as<float>(), rows_p, n, loss_dev, st);
+}
+
+// loss and estimate of every member for n queries (as launch_encode takes them)
+// (clear: n_clear ints to set to zero on the way)
+int answer(qcx_mlp* m, int n, const double* qw, const double* ws, int n_g, double* loss, double* err,
+           int* clear = nullptr, int n_clear = 0) {
+  qcx_ctx* ctx = m->ctx;
+  hipStream_t st = ctx->stream;
+  const int K = (int)m->mem.size();
+  HIPCK(m->xq.reserve(sizeof(float) * kIn * (size_t)n));
+  HIPCK(m->ys.reserve(sizeof(float) * (size_t)K * n));
+  launch_encode(qw, ws, n_g, nullptr, n, m->qmax, m->wmax, m->lat, m->mu, m->sigma, m->xq.as<float>(),
+                nullptr, st);
+  infer_rows(m, 0, K, m->xq.as<float>(), n, m->ys.as<float>(), n, st);
+  launch_decode(m->ys.as<float>(), K, n, m->mu, m->sigma, m->calib, loss, err, clear, n_clear, st);
+  LAUNCHCK("surrogate query");
+  return QCX_OK;
 }
 
 __global__ void k_check_order(const int* order, long n, int n_data, int* flag) {
@@ -218,10 +267,12 @@ int qcx_mlp_create(qcx_mlp** out, qcx_ctx* ctx, int n_members) {
       if (e == hipSuccess) e = w.wt[l].reserve(sizeof(uint16_t) * kW * kW);
     }
     if (e == hipSuccess) e = w.w5b.reserve(sizeof(uint16_t) * kW);
+    if (e == hipSuccess) e = w.frag.reserve(sizeof(uint16_t) * kFragAll);
     if (e == hipSuccess) e = hipMemsetAsync(w.p.p, 0, np, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(w.m.p, 0, np, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(w.v.p, 0, np, ctx->stream);
     if (e == hipSuccess) launch_refresh(w.p.as<float>(), w.wb(), ctx->stream);
+    if (e == hipSuccess) launch_fragments(w.p.as<float>(), w.wb(), ctx->stream);
     if (e != hipSuccess) {
       delete m;
       return fail(ctx, e == hipErrorOutOfMemory ? QCX_ENOMEM : QCX_EDEVICE,
@@ -255,6 +306,7 @@ int qcx_mlp_set_params(qcx_mlp* m, int member, const float* params) {
   HIPCK(hipMemsetAsync(w.v.p, 0, sizeof(float) * kNParam, st));
   w.step = 0;
   launch_refresh(w.p.as<float>(), w.wb(), st);
+  launch_fragments(w.p.as<float>(), w.wb(), st);
   LAUNCHCK("refresh");
   HIPCK(hipStreamSynchronize(st));  // params is the caller's pageable memory
   return QCX_OK;
@@ -279,13 +331,7 @@ int qcx_mlp_forward(qcx_mlp* m, int member, int n, const float* x, float* y) {
   if (n < 0 || (n > 0 && (!x || !y))) return fail(ctx, QCX_EINVAL, "bad n or NULL buffer");
   HIPCK(hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
-  for (int r0 = 0; r0 < n; r0 += kInferChunk) {
-    const int nn = std::min(kInferChunk, n - r0), rp = rows_padded(nn);
-    if (int rc = reserve_rows(m, rp, false)) return rc;
-    forward_rows(m, m->mem[member], x + (size_t)r0 * kIn, nullptr, 0, nn, rp, false,
-                 m->y.as<float>(), st);
-    HIPCK(hipMemcpyAsync(y + r0, m->y.p, sizeof(float) * nn, hipMemcpyDeviceToDevice, st));
-  }
+  if (n > 0) infer_rows(m, member, 1, x, n, y, n, st);
   LAUNCHCK("surrogate forward");
   return QCX_OK;
 }
@@ -300,7 +346,7 @@ int qcx_mlp_grad(qcx_mlp* m, int member, int n, const float* x, const float* t, 
   HIPCK(hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
   const int rp = rows_padded(n);
-  if (int rc = reserve_rows(m, rp, true)) return rc;
+  if (int rc = reserve_rows(m, rp)) return rc;
   HIPCK(m->hist.reserve(sizeof(float)));
   Member& w = m->mem[member];
   grad_rows(m, w, x, t, nullptr, 0, n, rp, m->hist.as<float>(), st);
@@ -336,7 +382,7 @@ int qcx_mlp_train(qcx_mlp* m, int member, int n_data, const float* x, const floa
   HIPCK(hipStreamSynchronize(st));
   if (bad) return fail(ctx, QCX_EINVAL, "order holds an index outside [0, n_data)");
   const int rp = rows_padded(batch);
-  if (int rc = reserve_rows(m, rp, true)) return rc;
+  if (int rc = reserve_rows(m, rp)) return rc;
   HIPCK(m->hist.reserve(sizeof(float) * (size_t)n_steps));
   Member& w = m->mem[member];
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
@@ -350,6 +396,7 @@ int qcx_mlp_train(qcx_mlp* m, int member, int n_data, const float* x, const floa
                 (float)lr, b1, b2, c1, c2, eps, st);
     launch_refresh(w.p.as<float>(), w.wb(), st);
   }
+  launch_fragments(w.p.as<float>(), w.wb(), st);
   LAUNCHCK("surrogate training");
   if (loss_hist) {
     HIPCK(hipMemcpyAsync(loss_hist, m->hist.p, sizeof(float) * n_steps, hipMemcpyDeviceToHost, st));
@@ -384,7 +431,7 @@ int qcx_mlp_encode(qcx_mlp* m, int n, const double* qw, const double* loss, floa
   if (n < 0 || (n > 0 && (!qw || !x))) return fail(ctx, QCX_EINVAL, "bad n or NULL buffer");
   if (n == 0) return QCX_OK;
   HIPCK(hipSetDevice(ctx->device));
-  launch_encode(qw, loss, n, m->qmax, m->wmax, m->lat, m->mu, m->sigma, x, t, ctx->stream);
+  launch_encode(qw, nullptr, 0, loss, n, m->qmax, m->wmax, m->lat, m->mu, m->sigma, x, t, ctx->stream);
   LAUNCHCK("encode");
   return QCX_OK;
 }
@@ -401,20 +448,7 @@ int qcx_mlp_query(qcx_mlp* m, int n, const double* qw, double* loss, double* err
   if (n == 0) return QCX_OK;
   HIPCK(hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
-  const int K = (int)m->mem.size();
-  HIPCK(m->xq.reserve(sizeof(float) * kIn * (size_t)n));
-  HIPCK(m->ys.reserve(sizeof(float) * (size_t)K * n));
-  launch_encode(qw, nullptr, n, m->qmax, m->wmax, m->lat, m->mu, m->sigma, m->xq.as<float>(),
-                nullptr, st);
-  for (int k = 0; k < K; ++k)
-    for (int r0 = 0; r0 < n; r0 += kInferChunk) {
-      const int nn = std::min(kInferChunk, n - r0), rp = rows_padded(nn);
-      if (int rc = reserve_rows(m, rp, false)) return rc;
-      forward_rows(m, m->mem[k], m->xq.as<float>() + (size_t)r0 * kIn, nullptr, 0, nn, rp, false,
-                   m->ys.as<float>() + (size_t)k * n + r0, st);
-    }
-  launch_decode(m->ys.as<float>(), K, n, m->mu, m->sigma, m->calib, loss, err, st);
-  LAUNCHCK("surrogate query");
+  if (int rc = answer(m, n, qw, nullptr, 0, loss, err)) return rc;
   if (reject_idx) {
     const int nb = select_blocks(n);
     HIPCK(m->sel_counts.reserve(sizeof(int) * ((size_t)nb + 1)));
@@ -467,50 +501,58 @@ int qcx_mlp_infer(qcx_mlp* m, qcx_ctx* ctx, int n_G, const int* G_int, int n_w,
   hipStream_t ms = mc->stream;
   HIPCK(stage_begin(mc));
   HIPCK(upload(mc, m->iQ, Q.data(), Q.size()));
-  HIPCK(upload(mc, m->iw, w_eV, (size_t)n_w));
-  HIPCK(m->iqw.reserve(sizeof(double) * 4 * n));
-  HIPCK(m->iidx.reserve(sizeof(int) * n));
+  HIPCK(upload_cached(mc, m->iw, m->h_w, std::vector<double>(w_eV, w_eV + n_w)));
   double* err = err_out;
   if (!err) {
     HIPCK(m->ierr.reserve(sizeof(double) * n));
     err = m->ierr.as<double>();
   }
-  hipLaunchKernelGGL(k_fill_qw, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, ms,
-                     m->iQ.as<double>(), n_G, m->iw.as<double>(), n_w, m->iqw.as<double>());
-  LAUNCHCK("infer grid");
-  if (int rc = qcx_mlp_query(m, (int)n, m->iqw.as<double>(), loss_out, err, 0.0, nullptr, nullptr))
+  HIPCK(m->iflag.reserve(sizeof(int) * ((size_t)n_w + 1)));
+  if (int rc = reserve_flags(m, n_w + 1)) return rc;
+  int* flag = m->iflag.as<int>();  // per frequency, then for any
+  if (int rc = answer(m, (int)n, m->iQ.as<double>(), m->iw.as<double>(), n_G, loss_out, err, flag, n_w + 1))
     return rc;
   // the estimates in units of each G's curve maximum over these frequencies,
-  // then the points above tol
-  hipLaunchKernelGGL(k_normwise_err, dim3((unsigned)((n_G + 255) / 256)), dim3(256), 0, ms, loss_out,
-                     err, n_w, n_G);
-  const int nb = select_blocks((int)n);
-  HIPCK(m->sel_counts.reserve(sizeof(int) * ((size_t)nb + 1)));
-  int* counts = m->sel_counts.as<int>();
-  launch_select(err, (int)n, tol, counts, nb, m->iidx.as<int>(), counts + nb, ms);
+  // and the frequencies with a point above tol
+  hipLaunchKernelGGL(k_normwise_err, dim3((unsigned)((n_G + 15) / 16)), dim3(256), 0, ms, loss_out, err,
+                     n_w, n_G, tol, flag);
   LAUNCHCK("infer rejections");
-  int nrej = 0;
-  HIPCK(hipMemcpyAsync(&nrej, counts + nb, sizeof(int), hipMemcpyDeviceToHost, ms));
-  HIPCK(hipStreamSynchronize(ms));  // the answers and rejections are complete
-  if (nrej == 0) return QCX_OK;
-  // frequencies with any rejected point (indices ascend, rows are w-major)
-  std::vector<int> idx(nrej), sel;
-  HIPCK(hipMemcpy(idx.data(), m->iidx.p, sizeof(int) * nrej, hipMemcpyDeviceToHost));
-  for (int i : idx)
-    if (sel.empty() || sel.back() != i / n_G) sel.push_back(i / n_G);
+  HIPCK(hipMemcpyAsync(m->h_flag, flag, sizeof(int) * ((size_t)n_w + 1), hipMemcpyDeviceToHost, ms));
+  HIPCK(hipEventRecord(m->ev_flag, ms));
+  // The method's pair densities do not depend on which frequencies it gets.
+  // On the networks' own stream, and where ctx holds no densities that they
+  // would replace, they are queued now behind the device flag, so that the
+  // device runs them while the host waits for and reads the rejections (and
+  // skips them if there is none).
+  bool ahead = ms == ctx->stream && !ctx->have_rho &&
+               rho_fused_fits(ctx->n_ao, ctx->n_occ, ctx->n_cells) &&
+               rho_prepare(ctx, n_G, G_int, true, false) == QCX_OK;
+  if (ahead) {
+    HIPCK(stage_begin(ctx));
+    HIPCK(upload_cached(ctx, ctx->d_G, ctx->h_G_up, std::vector<int>(G_int, G_int + 3 * (size_t)n_G)));
+    int sp;
+    HIPCK(span_begin(ctx, 0, &sp));
+    if (int rc = rho_enqueue(ctx, ctx->d_G.as<int>(), n_G, false, ms, flag + n_w)) return rc;
+    HIPCK(span_end(ctx, sp));
+  }
+  HIPCK(hipEventSynchronize(m->ev_flag));  // the answers and rejections are complete
+  std::vector<int> sel;
+  for (int w = 0; w < n_w; ++w)
+    if (m->h_flag[w]) sel.push_back(w);
+  if (sel.empty()) return QCX_OK;
   std::vector<double> wsel(sel.size());
   for (size_t r = 0; r < sel.size(); ++r) wsel[r] = w_eV[sel[r]];
   const int ns = (int)sel.size();
-  if (int rc = qcx_pair_density(ctx, n_G, G_int, nullptr)) return rc;
+  if (ahead)
+    ctx->have_rho = true;
+  else if (int rc = qcx_pair_density(ctx, n_G, G_int, nullptr))
+    return rc;
   if (int rc = qcx_chi0(ctx, ns, wsel.data(), eta_eV, precision, 1, nullptr)) return rc;
   if (int rc = qcx_eps_inv(ctx, 1, nullptr, nullptr)) return rc;
-  HIPCK(m->irows.reserve(sizeof(double) * (size_t)ns * n_G));
-  if (int rc = qcx_loss(ctx, m->irows.as<double>(), QCX_MEM_DEVICE)) return rc;
-  HIPCK(stage_begin(ctx));
-  HIPCK(upload(ctx, m->isel, sel.data(), sel.size()));
-  const size_t nr = (size_t)ns * n_G;
-  hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, ctx->stream,
-                     m->irows.as<double>(), m->isel.as<int>(), ns, n_G, loss_out);
+  // the rows to their places: row r of the context's loss is the r-th rejected
+  // frequency, counted from the flags on the device
+  hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)n_w), dim3(256), 0, ctx->stream,
+                     ctx->d_loss.as<double>(), flag, n_G, loss_out);
   LAUNCHCK("infer fallback rows");
   // asynchronous from here: deferred state checks and a singular eps of these
   // rows are reported by the next synchronising call on ctx

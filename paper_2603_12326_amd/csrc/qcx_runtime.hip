@@ -488,11 +488,11 @@ int qcx::rho_prepare(qcx_ctx* ctx, int n_G, const int* G_int, bool need_g0, bool
 // pass with M in LDS, or (large bases, many valence bands) through M chunks
 // in ctx->d_M, whose capacity sets the k chunk
 static int densities(qcx_ctx* ctx, const cplx* F, int rows, const cplx* bra, cplx* Rout,
-                     hipStream_t st) {
+                     hipStream_t st, const int* run = nullptr) {
   const int nT = ctx->n_cells, nao = ctx->n_ao;
   if (rho_fused_fits(nao, ctx->n_occ, nT)) {
     launch_rho_fused(F, ctx->d_ph.as<cplx>(), ctx->d_Ck.as<cplx>(), bra, nao, ctx->n_b, ctx->n_occ,
-                     ctx->n_k, nT, rows, Rout, ctx->ldt, st);
+                     ctx->n_k, nT, rows, Rout, ctx->ldt, st, run);
     LAUNCHCK("rho_fused");
     return QCX_OK;
   }
@@ -509,17 +509,18 @@ static int densities(qcx_ctx* ctx, const cplx* F, int rows, const cplx* bra, cpl
   return QCX_OK;
 }
 
-int qcx::rho_enqueue(qcx_ctx* ctx, const int* d_G, int n_G, bool optical, hipStream_t st) {
+int qcx::rho_enqueue(qcx_ctx* ctx, const int* d_G, int n_G, bool optical, hipStream_t st,
+                     const int* run) {
   launch_q_plus_g(ctx->d_qc.as<double>(), d_G, ctx->rec, n_G, optical, ctx->d_Q.as<double>(),
-                  ctx->d_vq.as<double>(), st);
-  launch_zero_tail(ctx->d_R.as<cplx>(), ctx->ldt, ctx->n_t, n_G, st);
+                  ctx->d_vq.as<double>(), st, run);
+  launch_zero_tail(ctx->d_R.as<cplx>(), ctx->ldt, ctx->n_t, n_G, st, run);
   LAUNCHCK("q_plus_g/zero_tail");
   launch_cell_ft(shell_tab(ctx), ctx->d_shp.as<int>(), ctx->d_tvec.as<double>(), ctx->n_cells,
-                 ctx->d_Q.as<double>(), n_G, ctx->d_F.as<cplx>(), st);
+                 ctx->d_Q.as<double>(), n_G, ctx->d_F.as<cplx>(), st, run);
   LAUNCHCK("cell_ft");
   // the bra states: k + q, or in the optical limit k itself
   const cplx* bra = optical ? ctx->d_Ck.as<cplx>() : ctx->d_Ckq.as<cplx>();
-  return densities(ctx, ctx->d_F.as<cplx>(), n_G, bra, ctx->d_R.as<cplx>(), st);
+  return densities(ctx, ctx->d_F.as<cplx>(), n_G, bra, ctx->d_R.as<cplx>(), st, run);
 }
 
 extern "C" {
@@ -546,7 +547,7 @@ static int pair_density_impl(qcx_ctx* ctx, int n_G, const int* G_int, void* rho_
   if (int rc = rho_prepare(ctx, n_G, G_int, need_g0, optical)) return rc;
   hipStream_t st = ctx->stream;
   HIPCK(stage_begin(ctx));
-  HIPCK(upload(ctx, ctx->d_G, G_int, 3 * (size_t)n_G));
+  HIPCK(upload_cached(ctx, ctx->d_G, ctx->h_G_up, std::vector<int>(G_int, G_int + 3 * (size_t)n_G)));
   int sp_rho;
   HIPCK(span_begin(ctx, 0, &sp_rho));
   if (int rc = rho_enqueue(ctx, ctx->d_G.as<int>(), n_G, optical, st)) return rc;

@@ -227,6 +227,7 @@ struct AsmArgs {
   int n_pairs64;        // pairs (flat indices 0..n_pairs64-1) held by XY
   const double* vq;     // sqrt(4 pi)/|q+G|
   double pref;
+  int parts;            // 1: real columns only (launch_diag_loss over squares), else (Re, Im)
 };
 void launch_eps_assemble(const AsmArgs& a, const Chi0Geom& g, cplx* eps, hipStream_t st);
 // Gauss-Jordan diag(eps^-1) of n_w matrices; a zero or non-finite pivot in

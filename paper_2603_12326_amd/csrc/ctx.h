@@ -15,6 +15,7 @@
 
 
 #include "common.h"
+#include "panel.h"
 
 using namespace qcx;
 
@@ -77,6 +78,11 @@ struct qcx_ctx {
   // Kramers-Kronig route: energy order, sorted energies and sides, K ranges
   // per row tile, reduced bins, transform matrix
   DevBuf d_kk_rank, d_kk_ib, d_kk_xf, d_kk_chunks, d_kk_Rs, d_kk_S, d_kk_K;
+  // panel route of qcx_chi0 and qcx_loss_diag (qcx_panel.hip): the panels of
+  // the last frequency list (kept by content) and the buffers
+  qcx::PanelSet pan_set;
+  qcx::PanelBuf pan_buf;
+  std::vector<int> h_pan_tasks_up;  // what pan_buf.tasks last received
   DevBuf d_Fg, d_Rp;  // optical limit: gradient integrals, band momentum matrices
   bool bulk_c64 = false;      // bulk partials reduced to FP64 (row chunks)
 
@@ -135,10 +141,12 @@ struct qcx_ctx {
   }
   qcx_ctx() {
     for (DevBuf* b : buffers()) b->budget = &budget;
+    for (DevBuf* b : pan_buf.all()) b->budget = &budget;
   }
   ~qcx_ctx() {
     if (plan) qcx::destroy_plan(plan);
     for (DevBuf* b : buffers()) b->release();
+    for (DevBuf* b : pan_buf.all()) b->release();
     if (ev_order) (void)hipEventDestroy(ev_order);
     for (const Span& sp : spans) {
       (void)hipEventDestroy(sp.a);

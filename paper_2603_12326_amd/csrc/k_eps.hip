@@ -737,18 +737,19 @@ __global__ void k_diag_loss(AsmArgs a, Chi0Geom g, int n_g, int n_w, double* __r
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (long)n_w * n_g) return;
   const int j = (int)(i / n_g), b = (int)(i % n_g);
+  const int parts = a.parts == 1 ? 1 : 2;
   double Xr = 0.0, Yr = 0.0;
   if (a.XY) {
     for (int ks = 0; ks < a.ks64; ++ks) {
-      const double* x0 = a.XY + ((size_t)ks * a.n_rowsp64 + 2 * j) * a.n_colp64 + 2 * b;
+      const double* x0 = a.XY + ((size_t)ks * a.n_rowsp64 + 2 * j) * a.n_colp64 + parts * b;
       Xr += x0[0];
       Yr += x0[a.n_colp64];
     }
   } else {
     for (int ks = 0; ks < a.ks; ++ks) {
-      const size_t r0 = ((size_t)ks * g.n_rowsp + 2 * j) * 2;
+      const size_t r0 = ((size_t)ks * g.n_rowsp + 2 * j) * parts;
       Xr += (double)a.C[r0 * g.n_bulkp + b];
-      Yr += (double)a.C[(r0 + 2) * g.n_bulkp + b];
+      Yr += (double)a.C[(r0 + parts) * g.n_bulkp + b];
     }
   }
   const double vv = a.vq[b] * a.vq[b];

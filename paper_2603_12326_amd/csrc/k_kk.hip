@@ -355,12 +355,12 @@ constexpr int KG_M1 = 128, KG_M2 = KG_M - KG_M1;
 constexpr int KG_LA1 = KG_M1 + 16;
 typedef __attribute__((address_space(3))) void* kg_lds_t;
 __device__ __forceinline__ void kg_issue(const double* __restrict__ Kb, int ldm,
-                                         const double* __restrict__ S, int N, int m0, int n0, int k0,
+                                         const double* __restrict__ S, int lds, int m0, int n0, int k0,
                                          int lane, int wave, double* sA1, double* sA2, double* sB) {
 #pragma unroll
   for (int i = 0; i < KG_K / 4; ++i) {
     const int r = wave + 4 * i;
-    __builtin_amdgcn_global_load_lds((const void*)(S + (size_t)(k0 + r) * N + n0 + 2 * lane),
+    __builtin_amdgcn_global_load_lds((const void*)(S + (size_t)(k0 + r) * lds + n0 + 2 * lane),
                                      (kg_lds_t)(sB + r * KG_LB), 16, 0, 0);
     __builtin_amdgcn_global_load_lds((const void*)(Kb + (size_t)(k0 + r) * ldm + m0 + 2 * lane),
                                      (kg_lds_t)(sA1 + r * KG_LA1), 16, 0, 0);
@@ -371,18 +371,18 @@ __device__ __forceinline__ void kg_issue(const double* __restrict__ Kb, int ldm,
       (kg_lds_t)(sA2 + 4 * wave * KG_M2), 16, 0, 0);
 }
 
-__global__ void __launch_bounds__(256) k_kk_gemm(const double* __restrict__ Kb, int ldm,
-                                                 const double* __restrict__ S, int N, int rows_p,
-                                                 int M, int n_mt, int n_nt,
-                                                 double* __restrict__ C) {
+__global__ void __launch_bounds__(256) k_kk_gemm(KkGemm g, int n_mt, int n_nt) {
+  const double* __restrict__ Kb = g.Kb;
+  const double* __restrict__ S = g.S;
+  const int ldm = g.ldm, N = g.N, M = g.M;
   __shared__ __attribute__((aligned(16))) double sA1[2][KG_K * KG_LA1];
   __shared__ __attribute__((aligned(16))) double sA2[2][KG_K * KG_M2];
   __shared__ __attribute__((aligned(16))) double sB[2][KG_K * KG_LB];
   // XCD-aware placement: consecutive logical tiles on one XCD share n
-  const int total = n_mt * n_nt, per = (total + 7) / 8;
+  const int total = n_mt * n_nt * g.ks, per = (total + 7) / 8;
   const int logical = (blockIdx.x % 8) * per + blockIdx.x / 8;
   if (logical >= total) return;
-  const int nt = logical / n_mt, mt = logical % n_mt;
+  const int z = logical / (n_mt * n_nt), nt = logical / n_mt % n_nt, mt = logical % n_mt;
   const int m0 = mt * KG_M, n0 = nt * KG_N;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = (wave >> 1) * (KG_M / 2), wn = (wave & 1) * (KG_N / 2);
@@ -391,13 +391,15 @@ __global__ void __launch_bounds__(256) k_kk_gemm(const double* __restrict__ Kb, 
   for (int a = 0; a < KG_FA; ++a)
 #pragma unroll
     for (int b = 0; b < KG_FB; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const int nk = rows_p / KG_K;
-  kg_issue(Kb, ldm, S, N, m0, n0, 0, lane, wave, sA1[0], sA2[0], sB[0]);
+  const int nk_all = (g.n_dev ? g.rows_p * *g.n_dev : g.rows_p) / KG_K;
+  const int kper = (nk_all + g.ks - 1) / g.ks, kt0 = z * kper;
+  const int nk = max(0, min(kper, nk_all - kt0)), kb = kt0 * KG_K;
+  if (nk > 0) kg_issue(Kb, ldm, S, g.lds, m0, n0, kb, lane, wave, sA1[0], sA2[0], sB[0]);
   __syncthreads();  // its fence waits for the copies into LDS as well
   for (int s = 0; s < nk; ++s) {
     const int buf = s & 1;
     if (s + 1 < nk)
-      kg_issue(Kb, ldm, S, N, m0, n0, (s + 1) * KG_K, lane, wave, sA1[buf ^ 1], sA2[buf ^ 1],
+      kg_issue(Kb, ldm, S, g.lds, m0, n0, kb + (s + 1) * KG_K, lane, wave, sA1[buf ^ 1], sA2[buf ^ 1],
                sB[buf ^ 1]);
 #pragma unroll
     for (int kk = 0; kk < KG_K; kk += 4) {
@@ -427,7 +429,7 @@ __global__ void __launch_bounds__(256) k_kk_gemm(const double* __restrict__ Kb, 
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int m = m0 + wm + 16 * a + 4 * r + (lane >> 4);
-        if (m < M && n < N) C[(size_t)m * N + n] = acc[a][b][r];
+        if (m < M && n < N) g.C[z * g.c_split + (size_t)m * g.ldc + n] = acc[a][b][r];
       }
     }
 }
@@ -461,12 +463,12 @@ int kk_rows_padded(int rows) { return (rows + KG_K - 1) / KG_K * KG_K; }
 int kk_ldm(int n_w) { return (2 * n_w + KG_M - 1) / KG_M * KG_M; }
 size_t kk_s_slack() { return KG_N; }
 
-void launch_kk_transform(const double* Kb, int ldm, const double* S, int N, int rows_p, int M,
-                         double* C, hipStream_t st) {
-  const int n_mt = ldm / KG_M, n_nt = (N + KG_N - 1) / KG_N;
-  const int total = n_mt * n_nt;
-  hipLaunchKernelGGL(k_kk_gemm, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(256), 0, st, Kb, ldm,
-                     S, N, rows_p, M, n_mt, n_nt, C);
+int kk_tiles(int n_w, int N) { return kk_ldm(n_w) / KG_M * ((N + KG_N - 1) / KG_N); }
+
+void launch_kk_transform(const KkGemm& g, hipStream_t st) {
+  const int n_mt = g.ldm / KG_M, n_nt = (g.N + KG_N - 1) / KG_N;
+  const int total = n_mt * n_nt * g.ks;
+  hipLaunchKernelGGL(k_kk_gemm, dim3((unsigned)(8 * ((total + 7) / 8))), dim3(256), 0, st, g, n_mt, n_nt);
 }
 
 }  // namespace qcx

@@ -48,9 +48,23 @@ void launch_kk_matrix(const double* w, int n_w, double eta, double d, int nr, in
 int kk_rows_padded(int rows);
 int kk_ldm(int n_w);
 size_t kk_s_slack();
-// C[M][N] = Kb^T S over rows_p bins (S: rows_p x N, row-major, rows past the
-// last bin zero, kk_s_slack() doubles of addressable memory after it)
-void launch_kk_transform(const double* Kb, int ldm, const double* S, int N, int rows_p, int M,
-                         double* C, hipStream_t st);
+// C[z][M][ldc] = Kb^T S over the rows of split z: S has rows of lds doubles,
+// N columns (kk_s_slack() doubles of addressable memory after the last row
+// where lds < N rounded up to that slack).  The number of rows (a multiple of
+// the K tile; rows past the last bin zero) is rows_p, or, where n_dev is set,
+// rows_p times the count it holds on the device.
+struct KkGemm {
+  const double* Kb;
+  int ldm;
+  const double* S;
+  int lds, N, rows_p;
+  const int* n_dev;
+  int M, ks;
+  double* C;
+  int ldc;
+  size_t c_split;  // doubles between the splits of C
+};
+void launch_kk_transform(const KkGemm& g, hipStream_t st);
+int kk_tiles(int n_w, int N);  // blocks of one split
 
 }  // namespace qcx

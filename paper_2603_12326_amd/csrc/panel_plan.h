@@ -1,0 +1,154 @@
+// Energy panels for the response of Eq. (RPA) at finite broadening.
+//
+// Every weight of the transition sum is 1 / (x - D + i eta) with x = w
+// (resonant) or x = -w (anti-resonant): a function of the transition energy D
+// that is analytic except for the poles at x + i eta, one per frequency.  On
+// an interval (a panel) that stays clear of the poles it is a short Chebyshev
+// series in D,
+//   1 / (z - y) = (1 / s) (1 + 2 sum_{i >= 1} r^-i T_i(y)),
+//   s = sqrt(z - 1) sqrt(z + 1),  r = z + s,  |r| > 1,
+// so the sum over the transitions of a panel is needed only for the basis
+// functions T_0 .. T_{n-1}, whatever the number of frequencies.  The panels
+// of a side depend on the frequencies and the broadening alone: they cover
+// the whole energy axis, are as wide as the convergence of the series allows
+// (about the broadening between the frequencies, growing with the distance
+// outside), and end on both sides in an unbounded panel, on which
+//   1 / (x - D + i eta) = -(u / S) / (1 - zeta u),  u = S / (D - c),
+//   zeta = (x - c + i eta) / S,
+// is u times a series in 2u - 1 (c lies beyond the frequencies on the other
+// side of the panel, so 0 < u <= 1 and Re zeta > 0).
+//
+// Host code without HIP, so that it can be compiled and checked alone.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <complex>
+#include <limits>
+#include <vector>
+
+namespace qcx {
+
+// kind 0: y = (D - c) s on |y| <= 1, basis T_i(y)
+// kind 1: u = s / (D - c), y = 2u - 1, basis u T_i(y)
+struct PanelDesc {
+  double c, s;
+  int kind, pad;
+};
+
+// Series lengths: the FP32-accumulated products use 16 terms, the FP64 ones
+// 32.  One layout serves both: the remainder after 16 terms is below
+// kPanelTol of the weight, and the remainder after 32 below its square,
+// kPanelTol^2 = 1e-16, the rounding of FP64.
+constexpr int kPanelTerms = 16, kPanelTerms64 = 32;
+constexpr double kPanelTol = 1e-8;
+
+// Remainder of the series after kPanelTerms terms relative to |1 / (z - y)|;
+// |r| is the sum of the semi-axes of the ellipse with foci -1 and 1 through z.
+inline double panel_remainder(std::complex<double> z) {
+  const double x = z.real(), y2 = z.imag() * z.imag();
+  const double m = std::sqrt((x - 1.0) * (x - 1.0) + y2), p = std::sqrt((x + 1.0) * (x + 1.0) + y2);
+  const double a = 0.5 * (m + p);
+  if (!(a > 1.0)) return std::numeric_limits<double>::infinity();
+  const double r = a + std::sqrt(a * a - 1.0);
+  const double r2 = r * r, r4 = r2 * r2, r8 = r4 * r4;
+  return 2.0 / (r8 * r8) / (std::sqrt(m * p) * (1.0 - 1.0 / r)) * (std::sqrt(x * x + y2) + 1.0);
+}
+
+// Panels of one side for poles at x[0] <= x[1] <= ... (+ i eta), eta > 0:
+// panel p holds edge[p - 1] <= D < edge[p] (unbounded outside).  Returns
+// false if more than max_panels are needed or the numbers leave the range in
+// which the recurrences are safe; the caller then sums the transitions
+// directly.
+inline bool panel_side(const std::vector<double>& x, double eta, int max_panels,
+                       std::vector<double>& edge, std::vector<PanelDesc>& desc) {
+  edge.clear();
+  desc.clear();
+  const double lo = x.front(), hi = x.back();
+  const double span = std::max(hi - lo, eta);
+  if (!(eta > 0.0) || !std::isfinite(span) || !(span < 1e12 * eta) ||
+      !(std::max(std::fabs(lo), std::fabs(hi)) < 1e9 * eta))
+    return false;
+  using cd = std::complex<double>;
+  // unbounded panel from X away from the poles (dir = +1 right, -1 left)
+  auto unbounded = [&](double X, int dir) {
+    PanelDesc d{};
+    d.kind = 1;
+    d.c = dir > 0 ? lo - span : hi + span;
+    d.s = X - d.c;
+    return d;
+  };
+  auto unbounded_ok = [&](double X, int dir) {
+    const PanelDesc d = unbounded(X, dir);
+    const cd zeta = cd((dir > 0 ? hi : lo) - d.c, eta) / d.s;
+    return std::abs(zeta) < 1.0 && panel_remainder(2.0 / zeta - 1.0) <= kPanelTol;
+  };
+  // on a bounded panel the pole whose real part is nearest to the centre
+  // lies on the smallest ellipse, so it alone decides
+  auto bounded_ok = [&](double a, double h) {
+    const double c = a + h;
+    const auto it = std::lower_bound(x.begin(), x.end(), c);
+    double d = std::numeric_limits<double>::infinity();
+    if (it != x.end()) d = *it - c;
+    if (it != x.begin()) d = std::min(d, c - *(it - 1));
+    return panel_remainder(cd(d, eta) / h) <= kPanelTol;
+  };
+  // left end: the nearest X to the poles that still converges
+  double d0 = 0.0, d1 = span;
+  while (!unbounded_ok(lo - d1, -1)) {
+    d0 = d1;
+    d1 *= 2.0;
+    if (!(d1 < 1e6 * span)) return false;
+  }
+  for (int i = 0; i < 30; ++i) {
+    const double m = 0.5 * (d0 + d1);
+    (unbounded_ok(lo - m, -1) ? d1 : d0) = m;
+  }
+  double a = lo - d1;
+  desc.push_back(unbounded(a, -1));
+  edge.push_back(a);
+  const double h_min = 0.25 * eta;  // converges wherever the poles are
+  double h = h_min;
+  while (!unbounded_ok(a, 1)) {
+    if ((int)desc.size() + 2 > max_panels) return false;
+    // widest panel from a: the previous width while it still just fits
+    // (between dense frequencies), else a bracket refined by bisection
+    if (!(bounded_ok(a, h) && !bounded_ok(a, 1.05 * h))) {
+      double g0 = h_min, g1 = h_min;
+      if (bounded_ok(a, h)) g0 = g1 = h;
+      do {
+        g0 = g1;
+        g1 *= 2.0;
+      } while (bounded_ok(a, g1) && g1 < 1e6 * span);
+      for (int i = 0; i < 12; ++i) {
+        const double m = 0.5 * (g0 + g1);
+        (bounded_ok(a, m) ? g0 : g1) = m;
+      }
+      h = g0;
+    }
+    const double b = a + 2.0 * h;
+    if (!(b > a)) return false;
+    PanelDesc d{};
+    d.c = a + h;
+    d.s = 1.0 / h;
+    desc.push_back(d);
+    edge.push_back(b);
+    a = b;
+  }
+  desc.push_back(unbounded(a, 1));
+  return true;
+}
+
+// The same panels for poles at -x[j] + i eta (the anti-resonant side).
+inline void panel_mirror(const std::vector<double>& edge, const std::vector<PanelDesc>& desc,
+                         std::vector<double>& m_edge, std::vector<PanelDesc>& m_desc) {
+  m_edge.assign(edge.rbegin(), edge.rend());
+  for (double& e : m_edge) e = -e;
+  m_desc.assign(desc.rbegin(), desc.rend());
+  for (PanelDesc& d : m_desc) {
+    d.c = -d.c;
+    if (d.kind == 1) d.s = -d.s;
+  }
+}
+
+}  // namespace qcx

@@ -588,6 +588,94 @@ int qcx_pair_density_optical(qcx_ctx* ctx, int n_G, const int* G_int, const doub
   return pair_density_impl(ctx, n_G, G_int, rho_out, true, qhat);
 }
 
+// Give the panel route's buffers back (waits for work that uses them)
+static void panels_release(qcx_ctx* ctx) {
+  (void)hipSetDevice(ctx->device);
+  (void)hipStreamSynchronize(ctx->stream);
+  for (DevBuf* b : ctx->pan_buf.all()) b->release();
+  ctx->pan_set.uploaded = false;
+  ctx->h_pan_tasks_up.clear();
+}
+
+// What the assembly reads after qcx_chi0 / qcx_chi0_kk
+static AsmArgs asm_args(const qcx_ctx* ctx) {
+  const Chi0Geom& g = ctx->geom;
+  AsmArgs a{};
+  a.C = (g.n_bulk > 0 && !ctx->bulk_c64) ? ctx->d_C.as<float>() : nullptr;
+  a.C64 = (g.n_bulk > 0 && ctx->bulk_c64) ? ctx->d_C64.as<double>() : nullptr;
+  a.XY = ctx->n_pairs64 > 0 ? ctx->d_XY.as<double>() : nullptr;
+  a.ks = g.ksplit;
+  a.ks64 = ctx->ks64;
+  a.n_rowsp64 = ctx->geom64.n_rowsp;
+  a.n_colp64 = ctx->geom64.n_colp;
+  a.n_pairs64 = ctx->n_pairs64;
+  a.vq = ctx->d_vq.as<double>();
+  a.pref = 2.0 / (ctx->n_k * ctx->vol);
+  return a;
+}
+
+static int chi0_export(qcx_ctx* ctx, void* chi0_out) {
+  launch_chi0_export(asm_args(ctx), ctx->geom, static_cast<cplx*>(chi0_out), ctx->stream);
+  LAUNCHCK("chi0_export");
+  return QCX_OK;
+}
+
+// Plan the panel route for the frequencies w (Hartree) of the call; job.n_g,
+// prec, eta, hw64 and diag are given.  *use: planned, its buffers reserved and its tables
+// on the device.  The transitions are summed directly where the panels do not
+// pay, when a test has forced a pipeline of the direct kernel, under a memory
+// cap (whose users sized it for the direct route's buffers) and when the
+// device has no room for the panels' buffers.
+static int panels_ready(qcx_ctx* ctx, const std::vector<double>& w, PanelJob& job, bool* use) {
+  *use = false;
+  if (ctx->force_nst || ctx->budget.limit) return QCX_OK;
+  job.n_t = ctx->n_t;
+  job.n_w = (int)w.size();
+  ctx->pan_set.plan(w, job.eta);
+  if (!pan_job_plan(job, ctx->pan_set)) return QCX_OK;
+  hipError_t e = pan_job_reserve(job, ctx->pan_set, ctx->pan_buf);
+  if (e == hipSuccess) e = ctx->d_C.reserve(sizeof(float) * job.c_floats);
+  if (e == hipSuccess) e = ctx->d_XY.reserve(sizeof(double) * job.xy_doubles);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    panels_release(ctx);
+    return QCX_OK;
+  }
+  HIPCK(e);
+  if (!ctx->pan_set.uploaded) {
+    HIPCK(upload(ctx, ctx->pan_buf.desc, ctx->pan_set.table.data(), ctx->pan_set.table.size()));
+    ctx->pan_set.uploaded = true;
+  }
+  if (!job.tasks.empty()) HIPCK(upload_cached(ctx, ctx->pan_buf.tasks, ctx->h_pan_tasks_up, job.tasks));
+  job.s.dt = ctx->d_dt.as<double>();
+  *use = true;
+  return QCX_OK;
+}
+
+// chi0 of the current pair densities through a planned panel job
+static int chi0_panels(qcx_ctx* ctx, const PanelJob& job) {
+  hipStream_t st = ctx->stream;
+  ctx->geom = job.g;
+  ctx->geom64 = job.g64;
+  ctx->n_pairs64 = job.n_ps64;
+  ctx->ks64 = job.g64.ksplit;
+  ctx->bulk_c64 = false;
+  ctx->bulk_nst = 3;
+  ctx->bulk_af = pan_row_frags(job.g.n_rows, job.prec == QCX_FP32);
+  ctx->tune_ms = 0.0;
+  int sp_all, sp;
+  HIPCK(span_begin(ctx, 3, &sp_all));
+  HIPCK(span_begin(ctx, job.bulk ? 1 : 2, &sp));
+  pan_enqueue_sort(job, ctx->pan_buf, ctx->d_w.as<double>(), st);
+  pan_enqueue_response(job, ctx->pan_buf, ctx->d_R.as<cplx>(), ctx->ldt, ctx->d_w.as<double>(),
+                       ctx->d_C.as<float>(), ctx->d_XY.as<double>(), st);
+  LAUNCHCK("chi0 panels");
+  HIPCK(span_end(ctx, sp));
+  HIPCK(span_end(ctx, sp_all));
+  ctx->have_chi0 = true;
+  return QCX_OK;
+}
+
 int qcx_loss_diag(qcx_ctx* ctx, int n_G, const int* G_int, int n_w, const double* w_eV,
                   double eta_eV, int precision, double* loss_out, void* inv_out) {
   if (!ctx) return QCX_EINVAL;
@@ -606,10 +694,25 @@ int qcx_loss_diag(qcx_ctx* ctx, int n_G, const int* G_int, int n_w, const double
     w[i] = w_eV[i] / kHartreeEV;
   }
   HIPCK(stage_begin(ctx));
-  HIPCK(upload(ctx, ctx->d_w, w.data(), w.size()));
+  HIPCK(upload_cached(ctx, ctx->d_w, ctx->h_w_up, w));
+  PanelJob job{}, last{};  // whole chunks, and the rest
+  bool panels = false;
+  constexpr int kChunk = 4096;
+  job.n_g = std::min(kChunk, n_G);
+  job.diag = true;
+  job.prec = precision;
+  job.eta = eta_eV / kHartreeEV;
+  if (int rc = panels_ready(ctx, w, job, &panels)) return rc;
+  last = job;
+  if (panels && n_G > kChunk && n_G % kChunk) {
+    last.n_g = n_G % kChunk;
+    if (!pan_job_plan(last, ctx->pan_set, true)) return fail(ctx, QCX_EDEVICE, "internal: panel plan");
+    HIPCK(pan_job_reserve(last, ctx->pan_set, ctx->pan_buf));
+    last.s.dt = job.s.dt;
+    HIPCK(ctx->d_XY.reserve(sizeof(double) * last.xy_doubles));
+  }
   const double eta = eta_eV / kHartreeEV;
   const bool bulk = precision != QCX_FP64, bf = precision == QCX_SPLIT_BF16;
-  constexpr int kChunk = 4096;
   // weights of the bulk once (they do not depend on G)
   Chi0Geom g{};
   g.n_t = ctx->n_t;
@@ -619,7 +722,7 @@ int qcx_loss_diag(qcx_ctx* ctx, int n_G, const int* G_int, int n_w, const double
   g.n_rowsp = (int)roundup(g.n_rows, 32 * af);
   g.c_rows = g.n_rowsp;
   g.n_tp = (int)roundup(g.n_t, KSTEP_T * kMaxKsplit);
-  if (bulk) {
+  if (bulk && !panels) {
     const size_t nA = (size_t)g.n_rowsp * g.n_tp;
     if (bf) {
       HIPCK(ctx->d_A.reserve(sizeof(uint16_t) * nA));
@@ -648,7 +751,21 @@ int qcx_loss_diag(qcx_ctx* ctx, int n_G, const int* G_int, int n_w, const double
     g.p0 = 0;
     g.n_bulk = nch;
     g.n_bulkp = (int)roundup(nch, 128);
-    if (bulk) {
+    if (panels) {
+      const PanelJob& j = nch == job.n_g ? job : last;
+      int sp;
+      HIPCK(span_begin(ctx, 2, &sp));
+      if (g0 == 0) pan_enqueue_sort(j, ctx->pan_buf, ctx->d_w.as<double>(), st);
+      pan_enqueue_response(j, ctx->pan_buf, ctx->d_R.as<cplx>(), ctx->ldt, ctx->d_w.as<double>(),
+                           ctx->d_C.as<float>(), ctx->d_XY.as<double>(), st);
+      HIPCK(span_end(ctx, sp));
+      LAUNCHCK("panels (diagonal)");
+      a.XY = ctx->d_XY.as<double>();
+      a.ks64 = j.g64.ksplit;
+      a.n_rowsp64 = j.g64.n_rowsp;
+      a.n_colp64 = j.g64.n_colp;
+      a.parts = 1;
+    } else if (bulk) {
       pairs.assign(g.n_bulkp, 0);
       for (int b = 0; b < nch; ++b) pairs[b] = b | (b << 16);
       g.gather = nch >= kGatherMinNg ? 1 : 0;
@@ -725,12 +842,23 @@ int qcx_chi0(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, int preci
     w[i] = w_eV[i] / kHartreeEV;
   }
   HIPCK(stage_begin(ctx));
-  HIPCK(upload(ctx, ctx->d_w, w.data(), w.size()));
+  HIPCK(upload_cached(ctx, ctx->d_w, ctx->h_w_up, w));
   ctx->n_w = n_w;
   ctx->eta = eta_eV / kHartreeEV;
   ctx->prec = precision;
   ctx->hw64 = headwings_fp64 ? 1 : 0;
 
+  PanelJob job{};
+  job.n_g = ctx->n_g;
+  job.hw64 = ctx->hw64 != 0;
+  job.prec = precision;
+  job.eta = ctx->eta;
+  bool panels = false;
+  if (int rc = panels_ready(ctx, w, job, &panels)) return rc;
+  if (panels) {
+    if (int rc = chi0_panels(ctx, job)) return rc;
+    return chi0_out ? chi0_export(ctx, chi0_out) : QCX_OK;
+  }
   Chi0Geom& g = ctx->geom;
   g = Chi0Geom{};
   g.n_g = ctx->n_g;
@@ -941,22 +1069,7 @@ int qcx_chi0(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, int preci
   }
   HIPCK(span_end(ctx, sp_all));
   ctx->have_chi0 = true;
-  if (chi0_out) {
-    AsmArgs a{};
-    a.C = (g.n_bulk > 0 && !ctx->bulk_c64) ? ctx->d_C.as<float>() : nullptr;
-  a.C64 = (g.n_bulk > 0 && ctx->bulk_c64) ? ctx->d_C64.as<double>() : nullptr;
-    a.XY = ctx->n_pairs64 > 0 ? ctx->d_XY.as<double>() : nullptr;
-    a.ks = g.ksplit;
-    a.ks64 = ctx->ks64;
-    a.n_rowsp64 = ctx->geom64.n_rowsp;
-    a.n_colp64 = ctx->geom64.n_colp;
-    a.n_pairs64 = ctx->n_pairs64;
-    a.vq = ctx->d_vq.as<double>();
-    a.pref = 2.0 / (ctx->n_k * ctx->vol);
-    launch_chi0_export(a, g, static_cast<cplx*>(chi0_out), st);
-    LAUNCHCK("chi0_export");
-  }
-  return QCX_OK;
+  return chi0_out ? chi0_export(ctx, chi0_out) : QCX_OK;
 }
 
 int qcx_chi0_kk(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, double bin_eV,
@@ -1043,7 +1156,7 @@ int qcx_chi0_kk(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, double
   if (chunks.size() > (size_t)INT_MAX) return fail(ctx, QCX_EINVAL, "too many bins");
 
   HIPCK(stage_begin(ctx));
-  HIPCK(upload(ctx, ctx->d_w, w.data(), w.size()));
+  HIPCK(upload_cached(ctx, ctx->d_w, ctx->h_w_up, w));
   HIPCK(upload(ctx, ctx->d_kk_rank, rank.data(), rank.size()));
   HIPCK(upload(ctx, ctx->d_kk_ib, ib.data(), ib.size()));
   HIPCK(upload(ctx, ctx->d_kk_xf, xf.data(), xf.size()));
@@ -1077,8 +1190,9 @@ int qcx_chi0_kk(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, double
   // C64[2 n_w][2 n_pairs] = Kb^T S over the bins on FP64 MFMA
   const int nc = (int)(2 * n_pairs);
   HIPCK(span_begin(ctx, 6, &sp_tr));
-  launch_kk_transform(ctx->d_kk_K.as<double>(), ldm, ctx->d_kk_S.as<double>(), nc, rows_p, 2 * n_w,
-                      ctx->d_C64.as<double>(), st);
+  launch_kk_transform({ctx->d_kk_K.as<double>(), ldm, ctx->d_kk_S.as<double>(), nc, nc, rows_p, nullptr,
+                       2 * n_w, 1, ctx->d_C64.as<double>(), nc, 0},
+                      st);
   HIPCK(span_end(ctx, sp_tr));
   LAUNCHCK("kk transform");
   HIPCK(span_end(ctx, sp_all));
@@ -1096,16 +1210,7 @@ int qcx_chi0_kk(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, double
   ctx->geom = ga;
   ctx->bulk_c64 = true;
   ctx->have_chi0 = true;
-  if (chi0_out) {
-    AsmArgs a{};
-    a.C64 = ctx->d_C64.as<double>();
-    a.ks = 1;
-    a.vq = ctx->d_vq.as<double>();
-    a.pref = 2.0 / (ctx->n_k * ctx->vol);
-    launch_chi0_export(a, ga, static_cast<cplx*>(chi0_out), st);
-    LAUNCHCK("chi0_export");
-  }
-  return QCX_OK;
+  return chi0_out ? chi0_export(ctx, chi0_out) : QCX_OK;
 }
 
 int qcx_eps_inv(qcx_ctx* ctx, int lfe, void* diag_out, void* epsM_out) {
@@ -1126,17 +1231,7 @@ int qcx_eps_inv(qcx_ctx* ctx, int lfe, void* diag_out, void* epsM_out) {
   ctx->sing_armed = true;
   int sp_eps;
   HIPCK(span_begin(ctx, 4, &sp_eps));
-  AsmArgs a{};
-  a.C = (g.n_bulk > 0 && !ctx->bulk_c64) ? ctx->d_C.as<float>() : nullptr;
-  a.C64 = (g.n_bulk > 0 && ctx->bulk_c64) ? ctx->d_C64.as<double>() : nullptr;
-  a.XY = ctx->n_pairs64 > 0 ? ctx->d_XY.as<double>() : nullptr;
-  a.ks = g.ksplit;
-  a.ks64 = ctx->ks64;
-  a.n_rowsp64 = ctx->geom64.n_rowsp;
-  a.n_colp64 = ctx->geom64.n_colp;
-  a.n_pairs64 = ctx->n_pairs64;
-  a.vq = ctx->d_vq.as<double>();
-  a.pref = 2.0 / (ctx->n_k * ctx->vol);
+  const AsmArgs a = asm_args(ctx);
   launch_eps_assemble(a, g, ctx->d_eps.as<cplx>(), st);
   LAUNCHCK("eps_assemble");
   if (lfe)
@@ -1198,6 +1293,7 @@ int qcx_eps_inv_given(qcx_ctx* ctx, int n_w, int n_G, const void* eps, int lfe, 
 
 int qcx_set_memory_limit(qcx_ctx* ctx, size_t bytes) {
   if (!ctx) return QCX_EINVAL;
+  if (bytes) panels_release(ctx);  // a capped context sums the transitions directly
   ctx->budget.limit = bytes;
   return QCX_OK;
 }

@@ -155,12 +155,35 @@ def timed(ctx, wl, qs, kf, prec, loss_out, steps, warmup, torch):
     return (t1 - t0), st
 
 
+def bulk_pairs(wl):
+    n_g = len(wl.G_int)
+    return n_g * (n_g + 1) // 2 - n_g
+
+
 def bulk_flops_per_launch(wl):
     """Real multiply-adds of the Hermitian-form bulk GEMM for one q:
     2 * (2 n_w rows) * (2 * upper-triangle pairs without G = 0) * N_T."""
     n_g = len(wl.G_int)
     pairs = n_g * (n_g + 1) // 2 - n_g
     return 2.0 * (2 * len(wl.w_eV)) * (2 * pairs) * wl.n_t
+
+
+def bulk_roofline(direct_flops, pairs, n_t, seconds, tile, launches=1):
+    """Roofline entry of the chi0 bulk of one launch.  Direct sum: its three
+    BF16 products.  Through energy panels (tile["stages"] == 0): the moments of
+    16 basis functions, re and im, three products each, a lower bound of what
+    runs (the response of the frequencies comes on top); the rate that the
+    direct sum would need for the same time stands beside it."""
+    panels = tile["stages"] == 0
+    fl = 3.0 * 2.0 * 16 * 2 * pairs * n_t * launches if panels else 3.0 * direct_flops
+    r = {"bound": "mfma", "achieved": fl / seconds / 1e12, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
+         "frac": fl / seconds / 1e12 / PEAK_BF16_TFLOPS,
+         "kernel": "k_pan_* (sort, moments and response of the energy panels, head/wings included)"
+                   if panels else "k_bulk<bf16> (chi0 bulk)",
+         "flops_per_launch_fp32_equiv": fl / 3.0}
+    if panels:
+        r["direct_sum_tflops_for_this_time"] = 3.0 * direct_flops / seconds / 1e12
+    return r
 
 
 def normwise(L, Lref):
@@ -212,9 +235,11 @@ def composite_rooflines(wl, n_w, n_g, n_in, n_out, stm):
     """Rooflines of the composite step's two heavy kernels from the per-step
     stage times: the pair densities of every G (FP64) and the chi0 bulk (the
     LFE block's pairs plus one diagonal pair per noLFE G; split BF16, three
-    products).  Returns ({"rho": ..., "bulk": ...}, key of the dominant one)."""
+    products; the LFE block counted as the moments of its energy panels, see
+    bulk_roofline).  Returns ({"rho": ..., "bulk": ...}, key of the dominant one)."""
     rho_fl = rho_flops_per_kg(wl.n_ao, wl.n_occ, wl.n_cond) * wl.n_k * n_g
-    bulk_fl = 3.0 * 2.0 * (2 * n_w) * 2 * (n_in * (n_in + 1) // 2 - n_in + n_out) * wl.n_t
+    lfe_pairs = n_in * (n_in + 1) // 2 - n_in
+    bulk_fl = 3.0 * 2.0 * (2 * 16 * lfe_pairs + (2 * n_w) * 2 * n_out) * wl.n_t
     rho_s, bulk_s = 1e-3 * stm["pair_density_ms"], 1e-3 * stm["chi0_bulk_ms"]
     rl = {"rho": {"bound": "mfma", "achieved": rho_fl / rho_s / 1e12, "peak": PEAK_FP64_TFLOPS,
                   "unit": "TFLOP/s", "frac": rho_fl / rho_s / 1e12 / PEAK_FP64_TFLOPS,
@@ -222,7 +247,7 @@ def composite_rooflines(wl, n_w, n_g, n_in, n_out, stm):
                   "ms_per_step": 1e3 * rho_s},
           "bulk": {"bound": "mfma", "achieved": bulk_fl / bulk_s / 1e12, "peak": PEAK_BF16_TFLOPS,
                    "unit": "TFLOP/s", "frac": bulk_fl / bulk_s / 1e12 / PEAK_BF16_TFLOPS,
-                   "traffic": None, "kernel": "k_bulk<bf16> (LFE pairs and noLFE diagonal)",
+                   "traffic": None, "kernel": "k_pan_* (LFE pairs) and k_bulk<bf16> (noLFE diagonal)",
                    "ms_per_step": 1e3 * bulk_s}}
     return rl, ("rho" if rho_s >= bulk_s else "bulk")
 
@@ -809,8 +834,7 @@ def main_optical(args):
     points = 3 * n_w
     L = [x.cpu().numpy() for x in loss]
     bulk_s = 1e-3 * st["chi0_bulk_ms"] / max(1, st["bulk_launches"])
-    alg = bulk_flops_per_launch(wl)
-    achieved = 3.0 * alg / bulk_s / 1e12
+    tile = ctx.bulk_config()
     out = {
         "metric": "optical-limit (direction, w) loss points/s at N_G=113 (k.p head and wings)",
         "value": points * args.steps / sec,
@@ -827,10 +851,8 @@ def main_optical(args):
         "config": {"workload": "Si-like fcc a=10.26, 28 GTO, 4+16 bands, 8^3 k, q -> 0 along x, y, z, "
                                "N_G=113, 400 w over 0-60 eV, eta=0.1 eV, split-BF16 bulk, FP64 "
                                "head/wings and inversion"},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                     "kernel": "k_bulk<bf16> (chi0 bulk, one launch per direction)",
-                     "avg_launch_ms": 1e3 * bulk_s, "flops_per_launch_fp32_equiv": alg},
+        "roofline": {**bulk_roofline(bulk_flops_per_launch(wl), bulk_pairs(wl), wl.n_t, bulk_s, tile),
+                     "traffic": None, "avg_launch_ms": 1e3 * bulk_s, "tile": tile},
         "stages_ms_per_step": {k: (v / args.steps if k.endswith("_ms") else v) for k, v in st.items()},
         "build": build_info(),
     }
@@ -885,7 +907,7 @@ def main_allelectron(args):
     pairs = n_g * (n_g + 1) // 2 - n_g
     alg_step = 2.0 * (2 * n_w) * (2 * pairs) * wl.n_t        # FP32-equivalent, per q
     alg_launch = alg_step * args.steps / nb
-    achieved = 3.0 * alg_launch / avg_bulk_s / 1e12
+    tile = ctx.bulk_config()
     points = n_w
     out = {
         "metric": "(q,w) loss points/s at N_G=749, all-electron (split-BF16 chi0, FP64 inversion)",
@@ -905,11 +927,9 @@ def main_allelectron(args):
                                "5 core + 4 valence + 28 conduction bands, 12^3 k, q=0.25*2pi/a x, "
                                "N_G=749, 1000 w over 0-100 eV, eta=0.1 eV",
                    "n_g": n_g, "n_w": n_w, "n_k": wl.n_k, "n_t": wl.n_t},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                     "kernel": "k_bulk<bf16> (chi0 bulk)", "avg_launch_ms": 1e3 * avg_bulk_s,
-                     "launches_per_step": nb / args.steps,
-                     "flops_per_launch_fp32_equiv": alg_launch},
+        "roofline": {**bulk_roofline(alg_launch, pairs, wl.n_t, avg_bulk_s, tile, args.steps / nb),
+                     "traffic": None, "avg_launch_ms": 1e3 * avg_bulk_s,
+                     "launches_per_step": nb / args.steps, "tile": tile},
         "stages_ms_per_step": stm,
         "build": build_info(),
     }
@@ -1048,8 +1068,9 @@ def main_surrogate(args):
     pairs = n_g * (n_g + 1) // 2 - n_g
     bulk_s = 1e-3 * stage["chi0_bulk_ms"]
     nb = max(1, stage["bulk_launches"])
-    bulk_flops = 3.0 * 8.0 * pairs * wl.n_t * st["fallback_points"]
-    achieved = bulk_flops / bulk_s / 1e12 if bulk_s > 0 else 0.0
+    tile = ctx.bulk_config()
+    bulk_flops = 8.0 * pairs * wl.n_t * st["fallback_points"]
+    rl_bulk = bulk_roofline(bulk_flops, pairs, wl.n_t, max(bulk_s, 1e-12), tile, nb)
     # the networks: 2 flops per weight per member and query
     widths = (49, 256, 256, 256, 256, 1)
     weights = sum(widths[i] * widths[i + 1] for i in range(len(widths) - 1))
@@ -1072,11 +1093,8 @@ def main_surrogate(args):
                                "2048 q x 24 w x 259 G; grid 40 new q x 97 w over 0-60 eV x 259 G",
                    "n_query": n_query, "n_train_q": NQ, "n_train_w": NW, "epochs": EPOCHS,
                    "tol": TOL},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
-                     "kernel": "k_bulk<bf16> (chi0 bulk of the fallback rows)",
-                     "avg_launch_ms": 1e3 * bulk_s / nb, "launches": nb,
-                     "flops_fp32_equiv_x3": bulk_flops},
+        "roofline": {**rl_bulk, "traffic": None, "rows": "the fallback's",
+                     "avg_launch_ms": 1e3 * bulk_s / nb, "launches": nb, "tile": tile},
         "network_roofline": {"bound": "mfma", "achieved": net_flops / net_dev_s / 1e12,
                              "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                              "frac": net_flops / net_dev_s / 1e12 / PEAK_BF16_TFLOPS,
@@ -1190,7 +1208,7 @@ def main():
     nb = max(1, s["st"]["bulk_launches"])
     avg_bulk_s = 1e-3 * s["st"]["chi0_bulk_ms"] / nb
     alg = bulk_flops_per_launch(wl)
-    achieved = 3.0 * alg / avg_bulk_s / 1e12       # BF16 MFMA flops (hi*hi, hi*lo, lo*hi)
+    rl_bulk = bulk_roofline(alg, bulk_pairs(wl), wl.n_t, avg_bulk_s, s["tile"])
     out = {
         "metric": "(q,w) loss points/s at N_G=113: MFMA split vs plain FP32, rel err 1e-4",
         "value": value,
@@ -1209,11 +1227,9 @@ def main():
                    "n_g": n_g, "n_q": args.n_q, "n_w": n_w, "n_k": wl.n_k, "n_t": wl.n_t,
                    "chi0_bulk": "split-bf16 MFMA, fp32 accumulation",
                    "head_wings": "fp64", "inversion": "fp64"},
-        "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS,
-                     "unit": "TFLOP/s", "frac": achieved / PEAK_BF16_TFLOPS,
-                     "traffic": recorded_traffic(), "kernel_source_sha256_16": kernel_source_hash(),
-                     "kernel": "k_bulk<bf16> (chi0 bulk)", "avg_launch_ms": 1e3 * avg_bulk_s,
-                     "flops_per_launch_fp32_equiv": alg, "tile": s["tile"]},
+        "roofline": {**rl_bulk, "traffic": None if s["tile"]["stages"] == 0 else recorded_traffic(),
+                     "kernel_source_sha256_16": kernel_source_hash(),
+                     "avg_launch_ms": 1e3 * avg_bulk_s, "tile": s["tile"]},
         "stages_ms_per_step": {k: (v / args.steps if k.endswith("_ms") else v)
                                for k, v in s["st"].items()},
         "build": build_info(),
@@ -1234,9 +1250,12 @@ def main():
         avg32 = 1e-3 * f["st"]["chi0_bulk_ms"] / nbf
         out["fp32_value"] = points * args.steps / f["sec"]
         out["speedup_split_vs_fp32"] = value / out["fp32_value"]
-        out["fp32_roofline"] = {"achieved": alg / avg32 / 1e12, "peak": PEAK_FP32_TFLOPS,
-                                "frac": alg / avg32 / 1e12 / PEAK_FP32_TFLOPS,
-                                "avg_launch_ms": 1e3 * avg32, "tile": f["tile"]}
+        if f["tile"]["stages"] == 0:
+            rl32 = bulk_roofline(alg, bulk_pairs(wl), wl.n_t, avg32, f["tile"])
+        else:
+            rl32 = {"achieved": alg / avg32 / 1e12, "peak": PEAK_FP32_TFLOPS,
+                    "frac": alg / avg32 / 1e12 / PEAK_FP32_TFLOPS}
+        out["fp32_roofline"] = {**rl32, "avg_launch_ms": 1e3 * avg32, "tile": f["tile"]}
     if not args.no_cpu_baseline:
         log("cpu baseline (FP64 oracle on a sample)")
         cb = cpu_baseline(wl, args.cpu_sample_w, res["split_bf16"]["loss0"],

@@ -68,6 +68,11 @@ enum {
   QCX_SPLIT_BF16 = 2   /* x = hi + lo (bf16 each), hi*hi + hi*lo + lo*hi on
                           BF16 MFMA with FP32 accumulation                  */
 };
+/* These are the operands of the direct sum over transitions.  Where qcx_chi0
+ * sums them through energy panels (see there), FP64 stays FP64 and both other
+ * modes take x = hi + lo in fp16 planes (22 bits) scaled by powers of two, with
+ * FP32 accumulation; in the FP32 mode each panel entry enters the accumulator
+ * once and the sum is split further. */
 
 /* Create a context on HIP device `device`, enqueueing on `hip_stream`
  * (a hipStream_t; NULL means the default stream).  *out receives the
@@ -182,6 +187,14 @@ int qcx_pair_density_optical(qcx_ctx* ctx, int n_G, const int* G_int, const doub
  *                  the precision; 0: they use the bulk precision
  *   chi0_out       NULL, or a device buffer [n_w][n_G][n_G] c128 that receives
  *                  chi0 (diagnostic; costs an extra pass)
+ * The weights 1 / (w - D + i eta) are expanded in D on energy panels clear of
+ * their poles (remainder 1e-8, in FP64 1e-16), which needs the sum over
+ * transitions only once for all frequencies.  The transitions are summed
+ * directly for each frequency where that is cheaper (few frequencies or
+ * transitions), for eta = 0, in the 16-bit modes for eta below 1e-4 of the
+ * larger of 1 Ha and the largest |w|, below 10,000 transitions in FP32, under a
+ * forced pipeline (qcx_set_bulk_pipeline) and under a memory cap
+ * (qcx_set_memory_limit).
  * Errors: QCX_ESTATE (no pair densities), QCX_EINVAL, QCX_ENOMEM. */
 int qcx_chi0(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, int precision,
              int headwings_fp64, void* chi0_out);
@@ -334,7 +347,7 @@ typedef struct qcx_item {
  * transitions each) per split, never more than 1024 steps per split in FP32
  * (splits are added in FP64).  With autotuning on (qcx_set_autotune, FP32 and
  * split-BF16), the first call of a signature builds a plan for each target in
- * {128, 256, 512, 1024}, replays and times each with HIP events on ctxs[0]'s
+ * {128, 256}, replays and times each with HIP events on ctxs[0]'s
  * stream and keeps the fastest (that call synchronises the stream).  Every
  * replay computes the complete result, so the outputs are those of the kept
  * plan.  Contexts may use different streams: the batch waits on ctxs[0]'s
@@ -578,7 +591,8 @@ int qcx_qbin_rate_halo(qcx_qbin* b, const double* w_eV, const double* S_iso, con
 int qcx_set_autotune(qcx_ctx* ctx, int mode);
 /* Configuration of the last bulk launch: cfg = {K split, pipeline (2 or 3 LDS stages;
  * 4: three stages with the transition slab one step ahead of the weights),
- * row fragments per wave} (zeros if there was no bulk), and the time spent
+ * 0: through energy panels), row fragments per wave} (zeros if there was no
+ * bulk), and the time spent
  * tuning in that call (ms, 0 when the shape was cached).  Errors:
  * QCX_ESTATE before qcx_chi0. */
 int qcx_bulk_config(qcx_ctx* ctx, int cfg[3], double* tune_ms);
@@ -591,7 +605,8 @@ int qcx_set_bulk_pipeline(qcx_ctx* ctx, int nst);
 
 /* Per-stage device time of the most recent calls, in milliseconds, measured
  * with HIP events on the context's stream (enabled by qcx_set_timing):
- * t[0] pair_density, t[1] chi0 bulk kernel, t[2] chi0 FP64 head/wings,
+ * t[0] pair_density, t[1] chi0 bulk kernel, t[2] chi0 FP64 head/wings (both in
+ * t[1] through energy panels),
  * t[3] chi0 total, t[4] eps assembly + inversion, t[5] launches of the bulk
  * kernel counted (after qcx_chi0_kk: t[1] is the binning kernel), t[6] the
  * FP64 transform product of qcx_chi0_kk.  Synchronises the stream.  Values accumulate until

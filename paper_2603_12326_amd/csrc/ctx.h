@@ -64,7 +64,7 @@ struct qcx_ctx {
   double eta = 0.0;
   Chi0Geom geom{};
   int ks64 = 1, n_pairs64 = 0;
-  int bulk_nst = 2;           // LDS pipeline of the last bulk launch (2, 3; 4: three
+  int bulk_nst = 2;           // LDS pipeline of the last bulk launch (0: energy panels; 2, 3; 4: three
                               // stages with the slab one step ahead of the weights)
   int force_nst = 0;          // 0: tuned or heuristic pipeline; 2..4: this one
   int bulk_af = 4;            // row fragments per wave of the last bulk launch

@@ -660,7 +660,7 @@ static int chi0_panels(qcx_ctx* ctx, const PanelJob& job) {
   ctx->n_pairs64 = job.n_ps64;
   ctx->ks64 = job.g64.ksplit;
   ctx->bulk_c64 = false;
-  ctx->bulk_nst = 3;
+  ctx->bulk_nst = 0;
   ctx->bulk_af = pan_row_frags(job.g.n_rows, job.prec == QCX_FP32);
   ctx->tune_ms = 0.0;
   int sp_all, sp;

@@ -571,12 +571,15 @@ __global__ void __launch_bounds__(256) k_pan_bin64(PanelSort s, const double* __
     }
 }
 
-// FP64 moments of pairs: one wave = one active panel x 4 G x 16 G'; lane n
+// FP64 moments of pairs: one wave = one active panel x 2 G x 16 G'; lane n
 // holds R of G' (one position per MFMA K slot), the G rows are broadcast
-// loads; products in FP64.
-constexpr int PQ_G = 4;
-__global__ void __launch_bounds__(256) k_pan_bin64_pairs(PanelSort s, const double* __restrict__ T64,
-                                                         PanelBin64 b) {
+// loads; products in FP64.  Bound by the loads' latency, then by the moments
+// written (620 MB for 89 G): two G rows leave room for four waves per SIMD with
+// two steps of loads in flight, 478 us there; four rows with one step in flight
+// (one wave per SIMD) 794, at two waves 588 to 626; one row 523, three 530.
+constexpr int PQ_G = 2;
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
+k_pan_bin64_pairs(PanelSort s, const double* __restrict__ T64, PanelBin64 b) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int a, task;
@@ -594,30 +597,36 @@ __global__ void __launch_bounds__(256) k_pan_bin64_pairs(PanelSort s, const doub
   for (int g = 0; g < PQ_G; ++g)
 #pragma unroll
     for (int f = 0; f < 2; ++f) acc[g][f][0] = acc[g][f][1] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const int n4 = (pd.z + 3) / 4;
-  double2 tn;
-  cplx hn, gn[PQ_G];
-  auto fetch = [&](int q) {
-    tn = *reinterpret_cast<const double2*>(Tp + (size_t)4 * q * kPanelTerms64);
-    hn = Rh[(size_t)4 * q * b.ld64];
+  // padded positions hold zeros: whole pairs of steps
+  const int n4 = (pd.z + 7) / 8 * 2;
+  struct In {
+    double2 t;
+    cplx h, g[PQ_G];
+  } in[2];
+  auto fetch = [&](int q, In& x) {
+    x.t = *reinterpret_cast<const double2*>(Tp + (size_t)4 * q * kPanelTerms64);
+    x.h = Rh[(size_t)4 * q * b.ld64];
 #pragma unroll
-    for (int g = 0; g < PQ_G; ++g) gn[g] = Rg[(size_t)4 * q * b.ld64 + g];
+    for (int g = 0; g < PQ_G; ++g) x.g[g] = Rg[(size_t)4 * q * b.ld64 + g];
   };
-  fetch(0);
-  for (int q = 0; q < n4; ++q) {
-    const double2 t = tn;
-    cplx P[PQ_G];
+  fetch(0, in[0]);
+  fetch(1, in[1]);
+  for (int q0 = 0; q0 < n4; q0 += 2)
 #pragma unroll
-    for (int g = 0; g < PQ_G; ++g) P[g] = cmulc(gn[g], hn);
-    if (q + 1 < n4) fetch(q + 1);
+    for (int u = 0; u < 2; ++u) {
+      const double2 t = in[u].t;
+      cplx P[PQ_G];
 #pragma unroll
-    for (int g = 0; g < PQ_G; ++g) {
-      acc[g][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.x, P[g].re, acc[g][0][0], 0, 0, 0);
-      acc[g][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.x, P[g].im, acc[g][0][1], 0, 0, 0);
-      acc[g][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.y, P[g].re, acc[g][1][0], 0, 0, 0);
-      acc[g][1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.y, P[g].im, acc[g][1][1], 0, 0, 0);
+      for (int g = 0; g < PQ_G; ++g) P[g] = cmulc(in[u].g[g], in[u].h);
+      if (q0 + 2 < n4) fetch(q0 + 2 + u, in[u]);
+#pragma unroll
+      for (int g = 0; g < PQ_G; ++g) {
+        acc[g][0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.x, P[g].re, acc[g][0][0], 0, 0, 0);
+        acc[g][0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.x, P[g].im, acc[g][0][1], 0, 0, 0);
+        acc[g][1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.y, P[g].re, acc[g][1][0], 0, 0, 0);
+        acc[g][1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(t.y, P[g].im, acc[g][1][1], 0, 0, 0);
+      }
     }
-  }
   const int Gp = tk.y + n;
 #pragma unroll
   for (int g = 0; g < PQ_G; ++g) {

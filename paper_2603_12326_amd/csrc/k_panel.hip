@@ -199,6 +199,9 @@ __device__ inline double panel_y(const PanelDesc& d, double D, double& f) {
   return 2.0 * u - 1.0;
 }
 
+// An entry's positions go round kTabSplit blocks (grid y): the longest entries
+// (1024 positions and more) set the time.
+constexpr int kTabSplit = 4;
 __global__ void __launch_bounds__(256) k_pan_tab(PanelSort s, uint4* __restrict__ T) {
   const int a = blockIdx.x;
   if (a >= s.n_act[0]) return;
@@ -206,7 +209,7 @@ __global__ void __launch_bounds__(256) k_pan_tab(PanelSort s, uint4* __restrict_
   const PanelDesc d = s.desc[pd.x];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15;
   const int steps = (pd.z + kPanStep - 1) / kPanStep;
-  for (int st = wave; st < steps; st += 4) {
+  for (int st = wave + 4 * blockIdx.y; st < steps; st += 4 * kTabSplit) {
     uint16_t v[NS][8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -249,7 +252,7 @@ __global__ void __launch_bounds__(256) k_pan_tab64(PanelSort s, double* __restri
   const PanelDesc d = s.desc[pd.x];
   const int n = (pd.z + kPanStep - 1) / kPanStep * kPanStep;
   const int m = threadIdx.x & 3;  // terms 8m .. 8m + 7
-  for (int q = threadIdx.x >> 2; q < n; q += 64) {
+  for (int q = (threadIdx.x >> 2) + 64 * blockIdx.y; q < n; q += 64 * kTabSplit) {
     const size_t p = (size_t)pd.y * kPanStep + q;
     double o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (q < pd.z) {
@@ -513,14 +516,22 @@ __global__ void __launch_bounds__(256, 2) k_pan_bin(PanelSort s, const uint4* __
 // columns on v_mfma_f64_16x16x4f64 (A 16x4: lane holds A[l % 16][l / 16]; B
 // 4x16: B[l / 16][l % 16]; D: D[4 r + l / 16][l % 16]).  Fragment f of A holds
 // terms 2 m + f, fragment c of B columns 2 n + c, so that a lane loads both of
-// its values at once.
+// its values at once.  SPLIT: the four waves of a block share a panel and its
+// columns, every fourth group of 16 positions each, and add up through LDS.
+template <bool SPLIT>
 __global__ void __launch_bounds__(256) k_pan_bin64(PanelSort s, const double* __restrict__ T64,
                                                    const double* __restrict__ X, int ldx, int n_task,
                                                    int n_col, double* __restrict__ S64, int lds) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int a, task;
-  pan_task(n_task, wave, 0, a, task);
+  if constexpr (SPLIT) {
+    const int i = blockIdx.x >> 3;
+    a = 8 * (i / n_task) + (int)(blockIdx.x & 7);
+    task = i % n_task;
+  } else {
+    pan_task(n_task, wave, 0, a, task);
+  }
   if (a >= s.n_act[0]) return;
   const int4 pd = s.act[a];
   const int n = lane & 15, kg = lane >> 4, c0 = 32 * task + 2 * n;
@@ -542,15 +553,17 @@ __global__ void __launch_bounds__(256) k_pan_bin64(PanelSort s, const double* __
       xn[u] = *reinterpret_cast<const double2*>(Xp + (size_t)(16 * q + 4 * u) * ldx);
     }
   };
-  fetch(0);
-  for (int q = 0; q < n16; ++q) {
+  constexpr int QS = SPLIT ? 4 : 1;
+  const int q0 = SPLIT ? wave : 0;
+  if (q0 < n16) fetch(q0);
+  for (int q = q0; q < n16; q += QS) {
     double2 t[4], x[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       t[u] = tn[u];
       x[u] = xn[u];
     }
-    if (q + 1 < n16) fetch(q + 1);
+    if (q + QS < n16) fetch(q + QS);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[u].x, x[u].x, acc[0][0], 0, 0, 0);
@@ -558,6 +571,31 @@ __global__ void __launch_bounds__(256) k_pan_bin64(PanelSort s, const double* __
       acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[u].y, x[u].x, acc[1][0], 0, 0, 0);
       acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(t[u].y, x[u].y, acc[1][1], 0, 0, 0);
     }
+  }
+  if constexpr (SPLIT) {
+    // wave w adds and stores element r = w of every fragment
+    __shared__ double part[4][16][64];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][4 * r + 2 * f + c][lane] = acc[f][c][r];
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      double v[2] = {0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) v[c] += part[w][4 * wave + 2 * f + c][lane];
+      double* o = S64 + ((size_t)a * kPanelTerms64 + 2 * (4 * wave + kg) + f) * lds + c0;
+      if (c0 + 1 < n_col)
+        *reinterpret_cast<double2*>(o) = make_double2(v[0], v[1]);
+      else if (c0 < n_col)
+        *o = v[0];
+    }
+    return;
   }
 #pragma unroll
   for (int f = 0; f < 2; ++f)
@@ -918,10 +956,10 @@ void launch_pan_sort(const PanelSort& s, hipStream_t st) {
 }
 
 void launch_pan_tab(const PanelSort& s, uint4* T, hipStream_t st) {
-  hipLaunchKernelGGL(k_pan_tab, dim3(pan_active(s)), dim3(256), 0, st, s, T);
+  hipLaunchKernelGGL(k_pan_tab, dim3(pan_active(s), kTabSplit), dim3(256), 0, st, s, T);
 }
 void launch_pan_tab64(const PanelSort& s, double* T64, hipStream_t st) {
-  hipLaunchKernelGGL(k_pan_tab64, dim3(pan_active(s)), dim3(256), 0, st, s, T64);
+  hipLaunchKernelGGL(k_pan_tab64, dim3(pan_active(s), kTabSplit), dim3(256), 0, st, s, T64);
 }
 
 int pan_pack_blocks(int n_t) { return (n_t + PP_T * PP_N - 1) / (PP_T * PP_N); }
@@ -965,8 +1003,15 @@ void launch_pan_bin(const PanelSort& s, const uint4* T, const PanelBin& b, hipSt
 void launch_pan_bin64(const PanelSort& s, const double* T64, const double* X, int ldx, int n_col,
                       double* S64, int lds, hipStream_t st) {
   const int n_task = (n_col + 31) / 32;
-  hipLaunchKernelGGL(k_pan_bin64, dim3(pan_grid(s, n_task)), dim3(256), 0, st, s, T64, X, ldx, n_task,
-                     n_col, S64, lds);
+  // where the blocks of one entry each fit a few rounds of the chip (head and
+  // wings), the longest entry's chain of loads is the time: split it
+  const long split = 8L * ((pan_active(s) + 7) / 8) * n_task;
+  if (split <= 16384)
+    hipLaunchKernelGGL(k_pan_bin64<true>, dim3((unsigned)split), dim3(256), 0, st, s, T64, X, ldx, n_task,
+                       n_col, S64, lds);
+  else
+    hipLaunchKernelGGL(k_pan_bin64<false>, dim3(pan_grid(s, n_task)), dim3(256), 0, st, s, T64, X, ldx, n_task,
+                       n_col, S64, lds);
 }
 
 void launch_pan_bin64_pairs(const PanelSort& s, const double* T64, const PanelBin64& b, hipStream_t st) {

@@ -375,8 +375,8 @@ __device__ __forceinline__ void gj_reg_body(const cplx* __restrict__ A, int n,
 // 0.5 ms of pivot steps, 1.3 ms of updates).  With a block per column tile the
 // updates fill the chip and the pivot steps, 1.9 us each (instruction issue of
 // the 16 waves of a sweep), bound it: 175 matrices of 259 1.09 ms (1.89 before),
-// 44 0.63 (1.72), 875 6.7 (9.7); 500 x 128 5.4 (11.6); 749 x 512 75 (87);
-// 953 x 16 10.0 (63), 953 x 256 79 (93).
+// 44 0.58 (1.72), 875 6.7 (9.7); 500 x 128 5.4 (11.6); 749 x 512 75 (87);
+// 953 x 16 6.4 (63), 953 x 256 76 (93).
 //
 // T[:, j] += Z Y[:, j] on the tile of MB columns j = jt .., by one block of NT
 // threads: Z = swept panel k0 .. with 1 subtracted at (p_a, a), Y the panel's
@@ -498,32 +498,49 @@ struct GjTile {
         const int p = __builtin_amdgcn_readfirstlane(L.prow[par]);
         const int pl = p & 63, pa = p >> 6;
         if (l == pl) live &= ~(1u << pa);
-        auto update1 = [&](int b, cplx w) __attribute__((always_inline)) {
-#pragma unroll
-          for (int a = 0; a < RP; ++a) {
-            const cplx u = L.ucol[par][l + 64 * a];
-            m[a][b].re = fma(-u.re, w.re, m[a][b].re);
-            m[a][b].re = fma(u.im, w.im, m[a][b].re);
-            m[a][b].im = fma(-u.re, w.im, m[a][b].im);
-            m[a][b].im = fma(-u.im, w.re, m[a][b].im);
-          }
-        };
+        // Row p of this wave's columns, wave-uniform, by one scalar branch on its
+        // slot, and u read once for all of them (the LDS pipe is shared by every
+        // wave): 259 x 44 matrices 633 -> 576 us, 953 x 16 10.1 -> 6.4 ms.  Not
+        // where it spills (eight row slots: 500 x 128 5.4 -> 5.8 ms) or where the
+        // unrolled columns outgrow the instruction cache (CP = 4: 1.09 -> 1.12).
+        constexpr bool ONCE = CP < 4 && RP != 8;
+        const cplx w0 = wk;  // owner of column k: w_k = piv + 1
+        cplx wr[CP];
         auto row = [&](int b) __attribute__((always_inline)) {
           cplx c[RP];
 #pragma unroll
           for (int a = 0; a < RP; ++a) c[a] = m[a][b];
-          return readlane_slot<RP>(c, pa, pl);
+          wr[b] = readlane_slot<RP>(c, pa, pl);
         };
-        const bool next = kk == NW - 1;
-        const bool owner1 = k + 1 < ms && v == (k + 1) % NW;
+        if constexpr (ONCE) {
+#pragma unroll
+          for (int a = 0; a < RP; ++a)
+            if (a == pa) {
+#pragma unroll
+              for (int b = 0; b < CP; ++b) wr[b] = {readlane_d(m[a][b].re, pl), readlane_d(m[a][b].im, pl)};
+            }
+          if (v == kk) wr[kb] = w0;
+        }
+        auto axpy = [&](int a, int b, cplx u) __attribute__((always_inline)) {
+          m[a][b].re = fma(-u.re, wr[b].re, m[a][b].re);
+          m[a][b].re = fma(u.im, wr[b].im, m[a][b].re);
+          m[a][b].im = fma(-u.re, wr[b].im, m[a][b].im);
+          m[a][b].im = fma(-u.im, wr[b].re, m[a][b].im);
+        };
+        auto column = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+          for (int a = 0; a < RP; ++a) axpy(a, b, L.ucol[par][l + 64 * a]);
+        };
         auto step1 = [&](int b) __attribute__((always_inline)) {
-          update1(b, row(b));
+          if constexpr (!ONCE) row(b);
+          column(b);
           cplx c[RP];
 #pragma unroll
           for (int a = 0; a < RP; ++a) c[a] = m[a][b];
           choose(c, k + 1, par ^ 1);
+          if constexpr (ONCE) wr[b] = {0.0, 0.0};  // done
         };
-        cplx w0 = wk;  // owner of column k: w_k = piv + 1
+        const bool next = kk == NW - 1, owner1 = k + 1 < ms && v == (k + 1) % NW;
         if (owner1) {
           if (!next)
             step1(kb);
@@ -531,11 +548,23 @@ struct GjTile {
             step1(kb + 1 < CP ? kb + 1 : CP - 1);  // k + 1 < ms keeps kb + 1 < CP
         }
         __builtin_amdgcn_s_setprio(0);
+        if constexpr (ONCE) {
 #pragma unroll
-        for (int b = 0; b < CP; ++b) {
-          const bool done = owner1 && b == (next ? kb + 1 : kb);
-          if (done) continue;
-          update1(b, v == kk && b == kb ? w0 : row(b));
+          for (int a = 0; a < RP; ++a) {
+            const cplx u = L.ucol[par][l + 64 * a];
+#pragma unroll
+            for (int b = 0; b < CP; ++b) axpy(a, b, u);
+          }
+        } else {
+#pragma unroll
+          for (int b = 0; b < CP; ++b) {
+            if (owner1 && b == (next ? kb + 1 : kb)) continue;  // done
+            if (v == kk && b == kb)
+              wr[b] = w0;
+            else
+              row(b);
+            column(b);
+          }
         }
       }
     }

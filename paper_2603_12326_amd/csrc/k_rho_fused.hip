@@ -75,14 +75,16 @@ __device__ inline void cmac(cplx& acc, cplx a, cplx b) {
   acc.im += a.re * b.im + a.im * b.re;
 }
 
-template <int NQ>
+// (GATED: nothing is done where *run is zero; a form of its own, so that the
+// ungated kernel stays as it is without the test)
+template <int NQ, bool GATED>
 __global__ void __launch_bounds__(512) k_rho_fused(const cplx* __restrict__ F,
                                                    const cplx* __restrict__ ph,
                                                    const cplx* __restrict__ Ck,
                                                    const cplx* __restrict__ Cb, int n_ao, int n_b,
                                                    int n_occ, int n_k, int n_t, int n_g, int gs,
                                                    int ks, cplx* __restrict__ R, size_t ldt, const int* run) {
-  if (run && !*run) return;
+  if (GATED && !*run) return;
   constexpr int NA4 = 4 * NQ;
   // two chunks of M tiles [tile][pair in tile][k] (chunk s in buffer s % 2);
   // after the chunks X [mu][v][k] in the first
@@ -339,10 +341,15 @@ void launch_rho_fused(const cplx* F, const cplx* ph, const cplx* Ck, const cplx*
   const int gs = 4, ks = n_kt < 8 ? n_kt : 8;
   const long total = (long)((n_g + gs - 1) / gs) * gs * ((n_kt + ks - 1) / ks) * ks;
   const dim3 grid((unsigned)(8 * ((total + 7) / 8)));
-#define QCX_RF(N)                                                                               \
-  case N:                                                                                       \
-    hipLaunchKernelGGL(k_rho_fused<N>, grid, dim3(512), 0, st, F, ph, Ck, Cb, n_ao, n_b, n_occ, \
-                       n_k, n_t, n_g, gs, ks, R, ldt, run);                                     \
+#define QCX_RF1(N, GATED)                                                                              \
+  hipLaunchKernelGGL((k_rho_fused<N, GATED>), grid, dim3(512), 0, st, F, ph, Ck, Cb, n_ao, n_b, n_occ, \
+                     n_k, n_t, n_g, gs, ks, R, ldt, run)
+#define QCX_RF(N)         \
+  case N:                 \
+    if (run)              \
+      QCX_RF1(N, true);   \
+    else                  \
+      QCX_RF1(N, false);  \
     return;
   switch (nq) {
     QCX_RF(1)
@@ -356,6 +363,7 @@ void launch_rho_fused(const cplx* F, const cplx* ph, const cplx* Ck, const cplx*
     default: return;
   }
 #undef QCX_RF
+#undef QCX_RF1
 }
 
 }  // namespace qcx

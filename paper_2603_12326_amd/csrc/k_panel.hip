@@ -108,7 +108,7 @@ __global__ void __launch_bounds__(1024) k_pan_scan(PanelSort s) {
   for (int d = 32; d; d >>= 1) full += __shfl_xor(full, d);
   if (lane == 0) ws[0][wave] = full;
   __syncthreads();
-  int tot[3] = {0, 0, 0};  // steps, full entries, rests before this round
+  int tot[3] = {0, 0, 0};  // steps, full entries, rests before this pass
 #pragma unroll
   for (int w = 0; w < 16; ++w) tot[2] += ws[0][w];
   __syncthreads();

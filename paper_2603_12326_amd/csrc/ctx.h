@@ -84,6 +84,9 @@ struct qcx_ctx {
   qcx::PanelBuf pan_buf;
   std::vector<int> h_pan_tasks_up;  // what pan_buf.tasks last received
   DevBuf d_Fg, d_Rp;  // optical limit: gradient integrals, band momentum matrices
+  // qcx_mlp_infer: the rejected frequencies of the rows under way on this stream
+  // (outside the budget, as the networks' buffers are)
+  DevBuf d_rows_infer;
   bool bulk_c64 = false;      // bulk partials reduced to FP64 (row chunks)
 
   // eps
@@ -147,6 +150,7 @@ struct qcx_ctx {
     if (plan) qcx::destroy_plan(plan);
     for (DevBuf* b : buffers()) b->release();
     for (DevBuf* b : pan_buf.all()) b->release();
+    d_rows_infer.release();
     if (ev_order) (void)hipEventDestroy(ev_order);
     for (const Span& sp : spans) {
       (void)hipEventDestroy(sp.a);

@@ -550,9 +550,18 @@ int qcx_mlp_infer(qcx_mlp* m, qcx_ctx* ctx, int n_G, const int* G_int, int n_w,
   if (int rc = qcx_chi0(ctx, ns, wsel.data(), eta_eV, precision, 1, nullptr)) return rc;
   if (int rc = qcx_eps_inv(ctx, 1, nullptr, nullptr)) return rc;
   // the rows to their places: row r of the context's loss is the r-th rejected
-  // frequency, counted from the flags on the device
+  // frequency, counted from the flags on the device.  The networks' next call
+  // rewrites its flags on its own stream, so a context on another stream reads a
+  // copy of its own (waiting instead would hold the networks back until these
+  // rows are done).
+  const int* rows = flag;
+  if (ms != ctx->stream) {
+    HIPCK(stage_begin(ctx));
+    HIPCK(upload(ctx, ctx->d_rows_infer, m->h_flag, (size_t)n_w));
+    rows = ctx->d_rows_infer.as<int>();
+  }
   hipLaunchKernelGGL(k_scatter_rows, dim3((unsigned)n_w), dim3(256), 0, ctx->stream,
-                     ctx->d_loss.as<double>(), flag, n_G, loss_out);
+                     ctx->d_loss.as<double>(), rows, n_G, loss_out);
   LAUNCHCK("infer fallback rows");
   // asynchronous from here: deferred state checks and a singular eps of these
   // rows are reported by the next synchronising call on ctx

@@ -68,11 +68,11 @@ enum {
   QCX_SPLIT_BF16 = 2   /* x = hi + lo (bf16 each), hi*hi + hi*lo + lo*hi on
                           BF16 MFMA with FP32 accumulation                  */
 };
-/* These are the operands of the direct sum over transitions.  Where qcx_chi0
- * sums them through energy panels (see there), FP64 stays FP64 and both other
- * modes take x = hi + lo in fp16 planes (22 bits) scaled by powers of two, with
- * FP32 accumulation; in the FP32 mode each panel entry enters the accumulator
- * once and the sum is split further. */
+/* These are the operands of the direct sum over transitions (and of every
+ * batch).  Where qcx_chi0 sums them through energy panels (see there), FP64
+ * stays FP64 and both other modes take FP32 operands: on FP32 MFMA for the sums
+ * over transitions, in three bf16 planes (24 bits) for the product over panels,
+ * with FP32 accumulation; the FP32 mode splits that sum further. */
 
 /* Create a context on HIP device `device`, enqueueing on `hip_stream`
  * (a hipStream_t; NULL means the default stream).  *out receives the
@@ -191,9 +191,9 @@ int qcx_pair_density_optical(qcx_ctx* ctx, int n_G, const int* G_int, const doub
  * their poles (remainder 1e-8, in FP64 1e-16), which needs the sum over
  * transitions only once for all frequencies.  The transitions are summed
  * directly for each frequency where that is cheaper (few frequencies or
- * transitions), for eta = 0, in the 16-bit modes for eta below 1e-4 of the
- * larger of 1 Ha and the largest |w|, below 10,000 transitions in FP32, under a
- * forced pipeline (qcx_set_bulk_pipeline) and under a memory cap
+ * transitions), for eta = 0, in the FP32 and split-BF16 modes for eta below 1e-4
+ * of the larger of 1 Ha and the largest |w|, in FP32 below 10,000 transitions
+ * and where its splits would take more than 4 GiB, under a forced pipeline (qcx_set_bulk_pipeline) and under a memory cap
  * (qcx_set_memory_limit).
  * Errors: QCX_ESTATE (no pair densities), QCX_EINVAL, QCX_ENOMEM. */
 int qcx_chi0(qcx_ctx* ctx, int n_w, const double* w_eV, double eta_eV, int precision,

@@ -15,39 +15,33 @@ namespace qcx {
 
 namespace {
 
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// Operands of the 16-bit products are split into two fp16 planes, x = hi + lo,
-// each the fp16 nearest to what is left: 22 bits at the rate of bf16 (whose two planes keep 16 bits: with those the moments and
-// coefficients, each shared by a whole panel, lost a factor 4 in the loss
-// against the direct sum, whose 65,536 separate roundings average out).  Every
-// operand is scaled by a power of two into the range of fp16, undone when the
-// result is stored:
-//   basis functions  |T| <= 1                  times 2^12
-//   densities        per row of G, from the largest component of the row
-//                    (rmax), to below 2^7, so that |P| < 2^15
-//   moments          at most ch terms: times 2^-12 2^-log2(ch), so |S| <= 2^15
-//   coefficients     |c| < 1 / eta             times 2^(14 + exponent of eta)
-constexpr int NS = 2;  // planes
-__device__ inline uint16_t h_bits(float x) { return __builtin_bit_cast(uint16_t, (_Float16)x); }
-__device__ inline float h_val(uint16_t b) { return (float)__builtin_bit_cast(_Float16, b); }
+// The reduced-precision modes hold every operand in 24 bits of FP32's range:
+// basis functions and densities enter the moments as FP32, on FP32 MFMA; the
+// moments and the coefficients enter the product over panels as three bf16
+// planes, x = p0 + p1 + p2, each the bf16 nearest to what is left, with the six
+// products of planes down to 2^-16 of the first.  Two fp16 planes (22 bits, one
+// power-of-two scale per row of G) took 0.3 ms less for 113 G, 65,536
+// transitions and 400 frequencies (1.7 against 2.0 ms), but have an absolute
+// floor: where the densities of a row span three orders of magnitude the
+// absorptive part far from every pole came out 3e-4 off (directly 1.4e-6).
+constexpr int NS = 3;  // planes
+__device__ inline uint16_t b_bits(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
+__device__ inline float b_val(uint16_t b) { return __uint_as_float((unsigned)b << 16); }
 
-__device__ inline void split_h(float x, uint16_t (&o)[NS]) {
+template <class F>
+__device__ inline void split_b(F x, uint16_t (&o)[NS]) {
 #pragma unroll
   for (int p = 0; p < NS; ++p) {
-    o[p] = h_bits(x);
-    x -= h_val(o[p]);
+    o[p] = b_bits((float)x);
+    x -= (F)b_val(o[p]);
   }
 }
-
-// exponent of the scale of a row whose largest |component| has the float bits
-// m (0 for a row of zeros; infinities and NaN stay what they are)
-__device__ inline int row_exp(unsigned m) { return 6 - max((int)(m >> 23) - 127, -100); }
-__device__ inline float pow2f(int e) { return __uint_as_float((unsigned)(e + 127) << 23); }  // |e| <= 126
 
 // ------------------------------------------------------------------- sorting
 // panel of energy D on its side: the number of edges at or below D (a NaN
@@ -202,7 +196,7 @@ __device__ inline double panel_y(const PanelDesc& d, double D, double& f) {
 // An entry's positions go round kTabSplit blocks (grid y): the longest entries
 // (1024 positions and more) set the time.
 constexpr int kTabSplit = 4;
-__global__ void __launch_bounds__(256) k_pan_tab(PanelSort s, uint4* __restrict__ T) {
+__global__ void __launch_bounds__(256) k_pan_tab(PanelSort s, float4* __restrict__ T) {
   const int a = blockIdx.x;
   if (a >= s.n_act[0]) return;
   const int4 pd = s.act[a];
@@ -210,7 +204,7 @@ __global__ void __launch_bounds__(256) k_pan_tab(PanelSort s, uint4* __restrict_
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i = lane & 15;
   const int steps = (pd.z + kPanStep - 1) / kPanStep;
   for (int st = wave + 4 * blockIdx.y; st < steps; st += 4 * kTabSplit) {
-    uint16_t v[NS][8];
+    float v[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int q = st * kPanStep + 8 * (lane >> 4) + j;
@@ -226,22 +220,11 @@ __global__ void __launch_bounds__(256) k_pan_tab(PanelSort s, uint4* __restrict_
         }
         x = t0;
       }
-      double r = x * (double)kPanelTScale;
-#pragma unroll
-      for (int p = 0; p < NS; ++p) {
-        v[p][j] = h_bits((float)r);
-        r -= (double)h_val(v[p][j]);
-      }
+      v[j] = (float)x;
     }
 #pragma unroll
-    for (int p = 0; p < NS; ++p) {
-      uint4 w;
-      w.x = v[p][0] | ((uint32_t)v[p][1] << 16);
-      w.y = v[p][2] | ((uint32_t)v[p][3] << 16);
-      w.z = v[p][4] | ((uint32_t)v[p][5] << 16);
-      w.w = v[p][6] | ((uint32_t)v[p][7] << 16);
-      T[((size_t)(pd.y + st) * NS + p) * 64 + lane] = w;
-    }
+    for (int h = 0; h < 2; ++h)
+      T[((size_t)(pd.y + st) * 2 + h) * 64 + lane] = make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]);
   }
 }
 
@@ -286,7 +269,6 @@ constexpr int PP_T = 32, PP_G = 64, PP_N = 4;
 __global__ void __launch_bounds__(256) k_pan_pack(PanelSort s, PanelPack p, int n_tb) {
   __shared__ cplx tile[PP_T][PP_G + 1];
   __shared__ cplx r0[PP_T];
-  __shared__ float pm[4][PP_G];
   if ((int)blockIdx.x >= n_tb) {
     const int a = blockIdx.x - n_tb;
     if (blockIdx.y || a >= s.n_act[0]) return;
@@ -306,7 +288,6 @@ __global__ void __launch_bounds__(256) k_pan_pack(PanelSort s, PanelPack p, int 
     return;
   }
   const int g0 = blockIdx.y * PP_G, gg = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  float m = 0.f;  // largest |component| of row g0 + gg (infinite where one is NaN)
   for (int i = 0; i < PP_N; ++i) {
     const int t0 = (blockIdx.x * PP_N + i) * PP_T;
     if (t0 >= s.n_t) break;
@@ -325,83 +306,34 @@ __global__ void __launch_bounds__(256) k_pan_pack(PanelSort s, PanelPack p, int 
       if (t >= s.n_t) break;
       const size_t r = (size_t)s.pos[t];
       const cplx v = tile[tt][gg];
-      if (p.R32) {
-        const float2 f = make_float2((float)v.re, (float)v.im);
-        if (g >= p.g_lo && g - p.g_lo < p.ld32) p.R32[r * p.ld32 + g - p.g_lo] = f;
-        const float a = fabsf(f.x), b = fabsf(f.y);
-        m = (a == a && b == b) ? fmaxf(m, fmaxf(a, b)) : INFINITY;
-      }
+      if (p.R32 && g >= p.g_lo && g - p.g_lo < p.ld32)
+        p.R32[r * p.ld32 + g - p.g_lo] = make_float2((float)v.re, (float)v.im);
       if (p.R64 && g < p.ld64) p.R64[r * p.ld64 + g] = v;
       if (p.W64 && g < p.ldw) p.W64[r * p.ldw + g] = cmulc(r0[tt], v);
       if (p.A64 && g < p.lda64) p.A64[r * p.lda64 + g] = v.re * v.re + v.im * v.im;
     }
   }
-  if (p.R32) {
-    pm[wv][gg] = m;
-    __syncthreads();
-    if (wv == 0 && g0 + gg >= p.g_lo && g0 + gg - p.g_lo < p.ld32)
-      p.bmax[(size_t)blockIdx.x * p.ld32 + g0 + gg - p.g_lo] =
-          fmaxf(fmaxf(pm[0][gg], pm[1][gg]), fmaxf(pm[2][gg], pm[3][gg]));
-  }
-}
-
-// rmax[g] = bits of the maximum over the blocks of the packing
-__global__ void __launch_bounds__(1024) k_pan_rmax(const float* __restrict__ bmax, int n_tb, int ld,
-                                                   unsigned* __restrict__ rmax) {
-  __shared__ float pm[16][64];
-  const int gg = threadIdx.x & 63, w = threadIdx.x >> 6, g = blockIdx.x * 64 + gg;
-  float m = 0.f;
-  if (g < ld)
-#pragma unroll 8
-    for (int i = w; i < n_tb; i += 16) m = fmaxf(m, bmax[(size_t)i * ld + g]);
-  pm[w][gg] = m;
-  __syncthreads();
-  if (w == 0 && g < ld) {
-#pragma unroll
-    for (int i = 1; i < 16; ++i) m = fmaxf(m, pm[i][gg]);
-    rmax[g] = __float_as_uint(m);
-  }
 }
 
 // -------------------------------------------------------------------- moments
-// One wave = one entry x 8 G x 16 G'.  Per step of 32 positions a lane holds R
-// of its G' (lane % 16) at its 8 positions (8 (lane / 16) ..) in registers; the
-// 8 rows of G go through the wave's own LDS (each is read by all lanes of a
-// position group); the pair products are formed in FP32 and split into fp16
-// planes, which are the B operand, the Chebyshev planes the A operand (16
-// terms).  No barriers: the LDS is private to the wave.  Bound by forming and
-// splitting the products (8 VALU instructions per pair of transitions and
-// part, against 6 MFMAs per G and step).
+// One wave = one entry x 8 G x 16 G' on v_mfma_f32_16x16x4_f32 (A 16x4: lane
+// holds A[l % 16][l / 16]; B 4x16: B[l / 16][l % 16]; D: D[4 (l / 16) + r][l %
+// 16]).  Per step of 32 positions a lane holds R of its G' (lane % 16) at its 8
+// positions (8 (lane / 16) ..) in registers, which are its K slots of the
+// step's eight MFMAs; the 8 rows of G go through the wave's own LDS (each is
+// read by all lanes of a position group); the pair products are formed in FP32
+// and are the B operand, the Chebyshev functions the A operand (16 terms).  No
+// barriers: the LDS is private to the wave.  Bound by the FP32 MFMAs and the
+// forming of the products, whose times add up (113 G, 65,536 transitions: 395
+// us, of which the MFMAs are 200 and the vector instructions 100; forming the
+// products of one or two G ahead changed nothing).
 constexpr int PB_G = 8;
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 
-// (x0, x1) = hi + lo in fp16: the conversions in pairs, the remainder by the
-// mixed-precision FMA, which reads an fp16 half without converting it first
-__device__ __forceinline__ void split_pair(float x0, float x1, f16x2& hi, f16x2& lo) {
-  float r0, r1;
-  asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(hi) : "v"(x0), "v"(x1));
-  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[0,0,0] op_sel_hi:[1,0,0]" : "=v"(r0) : "v"(hi), "v"(x0));
-  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r1) : "v"(hi), "v"(x1));
-  asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(lo) : "v"(r0), "v"(r1));
-}
-
-// both parts of one G: six MFMAs, alternating accumulators
-__device__ __forceinline__ void pan_mfma(f32x4& re, f32x4& im, const f16x8 (&t)[NS], const f16x8& rh,
-                                         const f16x8& rl, const f16x8& ih, const f16x8& il) {
-  re = __builtin_amdgcn_mfma_f32_16x16x32_f16(t[0], rl, re, 0, 0, 0);
-  im = __builtin_amdgcn_mfma_f32_16x16x32_f16(t[0], il, im, 0, 0, 0);
-  re = __builtin_amdgcn_mfma_f32_16x16x32_f16(t[1], rh, re, 0, 0, 0);
-  im = __builtin_amdgcn_mfma_f32_16x16x32_f16(t[1], ih, im, 0, 0, 0);
-  re = __builtin_amdgcn_mfma_f32_16x16x32_f16(t[0], rh, re, 0, 0, 0);
-  im = __builtin_amdgcn_mfma_f32_16x16x32_f16(t[0], ih, im, 0, 0, 0);
-}
-
-// store terms 4 q .. 4 q + 3 (q = lane / 16) of one column, times f
-__device__ __forceinline__ void pan_store(uint2* __restrict__ S, size_t tile0, int col, int q,
-                                          const f32x4& v, float f) {
+// store terms 4 q .. 4 q + 3 (q = lane / 16) of one column
+__device__ __forceinline__ void pan_store(uint2* __restrict__ S, size_t tile0, int col, int q, const f32x4& v) {
   uint16_t o[4][NS];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) split_h(v[r] * f, o[r]);
+  for (int r = 0; r < 4; ++r) split_b(v[r], o[r]);
   const size_t fr = (tile0 + (col >> 5)) * NS;
 #pragma unroll
   for (int p = 0; p < NS; ++p) {
@@ -424,7 +356,7 @@ __device__ inline void pan_task(int n_task, int wave, int round, int& a, int& ta
   task = i % n_task;
 }
 
-__global__ void __launch_bounds__(256, 2) k_pan_bin(PanelSort s, const uint4* __restrict__ T, PanelBin b) {
+__global__ void __launch_bounds__(256, 2) k_pan_bin(PanelSort s, const float4* __restrict__ T, PanelBin b) {
   __shared__ __attribute__((aligned(16))) f32x2 sG[4][PB_G][34];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -442,10 +374,10 @@ __global__ void __launch_bounds__(256, 2) k_pan_bin(PanelSort s, const uint4* __
     const int steps = (pd.z + kPanStep - 1) / kPanStep;
     // addresses: a part common to the wave and the lane's own 32-bit offset
     const float2* Ru = b.R32 + (size_t)pd.y * row_step;
-    const uint4* Tu = T + (size_t)pd.y * NS * 64;
+    const float4* Tu = T + (size_t)pd.y * 2 * 64;
     float4 gn[2];
     float2 hn[8];
-    uint4 tn[NS];
+    float4 tn[2];
     auto fetch = [&](int st) {
       const float2* r = Ru + st * row_step;
       const float4* src = reinterpret_cast<const float4*>(r + tk.x + og);
@@ -454,47 +386,39 @@ __global__ void __launch_bounds__(256, 2) k_pan_bin(PanelSort s, const uint4* __
 #pragma unroll
       for (int j = 0; j < 8; ++j) hn[j] = (r + tk.y + (size_t)j * b.ld32)[oh];
 #pragma unroll
-      for (int p = 0; p < NS; ++p) tn[p] = (Tu + ((size_t)st * NS + p) * 64)[lane];
+      for (int p = 0; p < 2; ++p) tn[p] = (Tu + ((size_t)st * 2 + p) * 64)[lane];
     };
     fetch(0);
-    const int eh = row_exp((b.rmax + tk.y)[n]);
-    const float sh = pow2f(eh);
-    float sg[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) sg[i] = pow2f(row_exp((b.rmax + tk.x)[g4 + i]));
     f32x4 ar[PB_G], ai[PB_G];
 #pragma unroll
     for (int g = 0; g < PB_G; ++g) ar[g] = ai[g] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int st = 0; st < steps; ++st) {
       float2 h[8];
-      f16x8 t[NS];
       __builtin_amdgcn_wave_barrier();
-      sG[wave][g4 + 0][tt] = f32x2{gn[0].x * sg[0], gn[0].y * sg[0]};
-      sG[wave][g4 + 1][tt] = f32x2{gn[0].z * sg[1], gn[0].w * sg[1]};
-      sG[wave][g4 + 2][tt] = f32x2{gn[1].x * sg[2], gn[1].y * sg[2]};
-      sG[wave][g4 + 3][tt] = f32x2{gn[1].z * sg[3], gn[1].w * sg[3]};
+      sG[wave][g4 + 0][tt] = f32x2{gn[0].x, gn[0].y};
+      sG[wave][g4 + 1][tt] = f32x2{gn[0].z, gn[0].w};
+      sG[wave][g4 + 2][tt] = f32x2{gn[1].x, gn[1].y};
+      sG[wave][g4 + 3][tt] = f32x2{gn[1].z, gn[1].w};
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int j = 0; j < 8; ++j) h[j] = make_float2(hn[j].x * sh, hn[j].y * sh);
-#pragma unroll
-      for (int p = 0; p < NS; ++p) t[p] = __builtin_bit_cast(f16x8, tn[p]);
+      for (int j = 0; j < 8; ++j) h[j] = hn[j];
+      const float t[8] = {tn[0].x, tn[0].y, tn[0].z, tn[0].w, tn[1].x, tn[1].y, tn[1].z, tn[1].w};
       if (st + 1 < steps) fetch(st + 1);
 #pragma unroll
       for (int g = 0; g < PB_G; ++g) {
         const f32x4* rg = reinterpret_cast<const f32x4*>(&sG[wave][g][8 * kg]);
-        f16x2 rh[4], rl[4], ih[4], il[4];
+        f32x4 sr = {0.f, 0.f, 0.f, 0.f}, si = sr;  // the step's sums, then onto the entry's
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const f32x4 x = rg[j];
-          const float2 y0 = h[2 * j], y1 = h[2 * j + 1];
-          split_pair(x.x * y0.x + x.y * y0.y, x.z * y1.x + x.w * y1.y, rh[j], rl[j]);  // conj(x) y
-          split_pair(x.x * y0.y - x.y * y0.x, x.z * y1.y - x.w * y1.x, ih[j], il[j]);
+          const float2 y0 = h[2 * j], y1 = h[2 * j + 1];  // conj(x) y
+          sr = __builtin_amdgcn_mfma_f32_16x16x4f32(t[2 * j], x.x * y0.x + x.y * y0.y, sr, 0, 0, 0);
+          si = __builtin_amdgcn_mfma_f32_16x16x4f32(t[2 * j], x.x * y0.y - x.y * y0.x, si, 0, 0, 0);
+          sr = __builtin_amdgcn_mfma_f32_16x16x4f32(t[2 * j + 1], x.z * y1.x + x.w * y1.y, sr, 0, 0, 0);
+          si = __builtin_amdgcn_mfma_f32_16x16x4f32(t[2 * j + 1], x.z * y1.y - x.w * y1.x, si, 0, 0, 0);
         }
-        auto cat = [](const f16x2 (&v)[4]) {
-          return __builtin_shufflevector(__builtin_shufflevector(v[0], v[1], 0, 1, 2, 3),
-                                         __builtin_shufflevector(v[2], v[3], 0, 1, 2, 3), 0, 1, 2, 3, 4, 5, 6, 7);
-        };
-        pan_mfma(ar[g], ai[g], t, cat(rh), cat(rl), cat(ih), cat(il));
+        ar[g] += sr;
+        ai[g] += si;
       }
     }
     const size_t tile0 = (size_t)a * (2 * b.nbp / 32);
@@ -504,10 +428,8 @@ __global__ void __launch_bounds__(256, 2) k_pan_bin(PanelSort s, const uint4* __
       const int G = tk.x + g;
       if (G > Gp || Gp >= b.n_gl) continue;
       const long pb = (long)G * b.n_gl - (long)G * (G - 1) / 2 + (Gp - G) - b.b0;
-      pan_store(b.S, tile0, (int)pb, kg, ar[g], b.s_scale);
-      pan_store(b.S, tile0, b.nbp + (int)pb, kg, ai[g], b.s_scale);
-      if (a == 0 && kg == 0)  // what the product divides by, once per column
-        b.unscale[pb] = ldexpf(b.c_unscale, -row_exp(b.rmax[G]) - eh);
+      pan_store(b.S, tile0, (int)pb, kg, ar[g]);
+      pan_store(b.S, tile0, b.nbp + (int)pb, kg, ai[g]);
     }
   }
 }
@@ -716,7 +638,7 @@ __device__ inline void panel_series(const PanelDesc& d, double x, double eta, cd
 }
 
 __global__ void __launch_bounds__(256) k_pan_coef(PanelSort s, const double* __restrict__ w, int n_w,
-                                                  double eta, double scale, int row0, int n_rb,
+                                                  double eta, int row0, int n_rb,
                                                   uint4* __restrict__ A) {
   const int a = blockIdx.y;
   if (a >= s.n_act[0]) return;
@@ -736,13 +658,10 @@ __global__ void __launch_bounds__(256) k_pan_coef(PanelSort s, const double* __r
   }
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const double f = (k || (lane >> 5)) ? 2.0 * scale : scale;
-    double r = f * ((row & 1) ? amp.im : amp.re);
+    uint16_t o[NS];
+    split_b((k || (lane >> 5) ? 2.0 : 1.0) * ((row & 1) ? amp.im : amp.re), o);
 #pragma unroll
-    for (int p = 0; p < NS; ++p) {
-      v[p][k] = h_bits((float)r);
-      r -= (double)h_val(v[p][k]);
-    }
+    for (int p = 0; p < NS; ++p) v[p][k] = o[p];
     amp = cd_mul(amp, q);
   }
 #pragma unroll
@@ -776,12 +695,15 @@ __global__ void __launch_bounds__(256) k_pan_coef64(PanelSort s, const double* _
 }
 
 // ------------------------------------------------------------------- response
-// C = A S on v_mfma_f32_32x32x16_f16, both operands in fragment order (one
+// C = A S on v_mfma_f32_32x32x16_bf16, both operands in fragment order (one
 // active panel = one K step of 16 terms).  A block of 4 waves owns AF x 32
 // rows x 256 columns: each wave all rows and 64 columns (AF x 2 accumulators
-// of 16 registers, two waves per SIMD from two blocks).  The 1 KB fragments of
-// a step are copied straight into LDS, three stages; every wave issues the same
-// number of copies per stage (a few are repeated), so the waits count exactly.
+// of 16 registers, two waves per SIMD from two blocks).  An entry's six products
+// are summed apart and enter the accumulators once, rounded to nearest (six
+// MFMAs straight into them: the loss of 113 G 1.6e-6 off instead of 2.3e-7).  The 1 KB fragments of
+// a step are copied straight into LDS one step ahead, two stages (39 KB each
+// for AF = 5, so that two blocks fit a CU); a step's 60 MFMAs per wave outlast
+// the copies.
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 template <int AF>
 struct GemmStage {
@@ -789,10 +711,9 @@ struct GemmStage {
   float4 b[8 * NS * 64];
 };
 
-template <int AF, bool EACH>
+template <int AF>
 __device__ __forceinline__ void pan_gemm_tile(const PanelSort& s, const PanelGemm& g,
-                                              GemmStage<AF>& s0, GemmStage<AF>& s1,
-                                              GemmStage<AF>& s2) {
+                                              GemmStage<AF>& s0, GemmStage<AF>& s1) {
   using L = GemmStage<AF>;
   const int lane = threadIdx.x & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -833,7 +754,6 @@ __device__ __forceinline__ void pan_gemm_tile(const PanelSort& s, const PanelGem
       __builtin_amdgcn_global_load_lds((const void*)(src[i] + stride[i] * st), (lds_ptr_t)to, 16, 0, 0);
     }
   };
-  constexpr int WAIT_ONE = (NCP & 15) | ((NCP >> 4) << 14) | (7 << 4) | (15 << 8);
 
   f32x16 acc[AF][2];
 #pragma unroll
@@ -842,67 +762,46 @@ __device__ __forceinline__ void pan_gemm_tile(const PanelSort& s, const PanelGem
     for (int r = 0; r < 16; ++r) acc[f][0][r] = acc[f][1][r] = 0.f;
 
   auto compute = [&](const L& cur) {
-    f16x8 B[2][NS];
+    bf16x8 B[2][NS];
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int p = 0; p < NS; ++p)
-        B[c][p] = __builtin_bit_cast(f16x8, cur.b[((2 * wave + c) * NS + p) * 64 + lane]);
-    if constexpr (EACH) {
+        B[c][p] = __builtin_bit_cast(bf16x8, cur.b[((2 * wave + c) * NS + p) * 64 + lane]);
 #pragma unroll
-      for (int f = 0; f < AF; ++f) {
-        const f16x8 A0 = __builtin_bit_cast(f16x8, cur.a[(f * NS) * 64 + lane]);
-        const f16x8 A1 = __builtin_bit_cast(f16x8, cur.a[(f * NS + 1) * 64 + lane]);
-        f32x16 t[2];
+    for (int f = 0; f < AF; ++f) {
+      f32x16 t[2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) t[0][r] = t[1][r] = 0.f;
+      for (int r = 0; r < 16; ++r) t[0][r] = t[1][r] = 0.f;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) t[c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A1, B[c][0], t[c], 0, 0, 0);
+      for (int p = NS - 1; p >= 0; --p) {  // the small products first
+        const bf16x8 A = __builtin_bit_cast(bf16x8, cur.a[(f * NS + p) * 64 + lane]);
 #pragma unroll
-        for (int c = 0; c < 2; ++c) t[c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A0, B[c][1], t[c], 0, 0, 0);
+        for (int q = NS - 1 - p; q >= 0; --q)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) t[c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A0, B[c][0], t[c], 0, 0, 0);
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[f][c][r] += t[c][r];
+          for (int c = 0; c < 2; ++c) t[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, B[c][q], t[c], 0, 0, 0);
       }
-      return;
-    }
 #pragma unroll
-    for (int p = 0; p < NS; ++p) {
-      f16x8 A[AF];
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int f = 0; f < AF; ++f) A[f] = __builtin_bit_cast(f16x8, cur.a[(f * NS + p) * 64 + lane]);
-#pragma unroll
-      for (int q = 0; q + p < NS; ++q)
-#pragma unroll
-        for (int f = 0; f < AF; ++f) {
-          acc[f][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[f], B[0][q], acc[f][0], 0, 0, 0);
-          acc[f][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[f], B[1][q], acc[f][1], 0, 0, 0);
-        }
+        for (int r = 0; r < 16; ++r) acc[f][c][r] += t[c][r];
     }
   };
-  auto barrier = [] { asm volatile("s_barrier" ::: "memory"); };
+  // this wave's copies have landed and its reads are done, then everyone's
+  auto barrier = [] { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
   auto one = [&](int st, const L& cur, L& nxt) {
-    stage(min(st + 2, steps - 1), nxt);
+    if (st + 1 < steps) stage(st + 1, nxt);
     compute(cur);
     __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(WAIT_ONE);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     barrier();
   };
   if (steps > 0) {
     stage(0, s0);
-    stage(min(1, steps - 1), s1);
-    __builtin_amdgcn_s_waitcnt(WAIT_ONE);
     barrier();
-    for (int st = 0; st < steps; st += 3) {
-      one(st, s0, s2);
+    for (int st = 0; st < steps; st += 2) {
+      one(st, s0, s1);
       if (st + 1 < steps) one(st + 1, s1, s0);
-      if (st + 2 < steps) one(st + 2, s2, s1);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
@@ -910,22 +809,21 @@ __device__ __forceinline__ void pan_gemm_tile(const PanelSort& s, const PanelGem
     if (ct >= nct) continue;
     const int part = 32 * ct / g.nbp, b = 32 * ct - part * g.nbp + (lane & 31);
     if (b >= g.nb) continue;
-    const float un = g.unscale[b];
 #pragma unroll
     for (int f = 0; f < AF; ++f)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = g.row0 + (mt * AF + f) * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
-        g.C[(((size_t)z * g.c_rows + row) * 2 + part) * g.n_bulkp + g.b0 + b] = acc[f][c][r] * un;
+        g.C[(((size_t)z * g.c_rows + row) * 2 + part) * g.n_bulkp + g.b0 + b] = acc[f][c][r];
       }
   }
 }
 
-template <int AF, bool EACH>
+template <int AF>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_pan_gemm(PanelSort s, PanelGemm g) {
-  __shared__ GemmStage<AF> s0, s1, s2;
-  pan_gemm_tile<AF, EACH>(s, g, s0, s1, s2);
+  __shared__ GemmStage<AF> s0, s1;
+  pan_gemm_tile<AF>(s, g, s0, s1);
 }
 
 unsigned pan_grid(const PanelSort& s, int n_task) {
@@ -940,10 +838,10 @@ void pan_sort_geom(PanelSort& s) {
   // blocks of at least 1024 transitions: the scan walks one count per block
   s.nb = std::max(1, std::min(512, s.n_t / 1024));
   s.per = (s.n_t + s.nb - 1) / s.nb;
-  // entries of about a 128th of the transitions, 1024 (32 steps) to 32768:
-  // the FP32 sums of one entry stay within 1024 steps
+  // entries of about a 128th of the transitions, 1024 (32 steps) to 16384: the
+  // FP32 sums of one entry stay within 16384 transitions, as the direct sum's do
   const int c = (s.n_t + 127) / 128;
-  s.ch = std::max(1024, std::min(32768, (c + kPanStep - 1) / kPanStep * kPanStep));
+  s.ch = std::max(1024, std::min(16384, (c + kPanStep - 1) / kPanStep * kPanStep));
   s.max_act = std::min(s.P, s.n_t) + s.n_t / s.ch + 1;
   s.cap = s.n_t / kPanStep + std::min(s.P, s.n_t) + 1;
 }
@@ -955,26 +853,21 @@ void launch_pan_sort(const PanelSort& s, hipStream_t st) {
   hipLaunchKernelGGL(k_pan_scatter, dim3(s.nb), dim3(256), lds, st, s);
 }
 
-void launch_pan_tab(const PanelSort& s, uint4* T, hipStream_t st) {
+void launch_pan_tab(const PanelSort& s, float4* T, hipStream_t st) {
   hipLaunchKernelGGL(k_pan_tab, dim3(pan_active(s), kTabSplit), dim3(256), 0, st, s, T);
 }
 void launch_pan_tab64(const PanelSort& s, double* T64, hipStream_t st) {
   hipLaunchKernelGGL(k_pan_tab64, dim3(pan_active(s), kTabSplit), dim3(256), 0, st, s, T64);
 }
 
-int pan_pack_blocks(int n_t) { return (n_t + PP_T * PP_N - 1) / (PP_T * PP_N); }
-
 void launch_pan_pack(const PanelSort& s, const PanelPack& p, hipStream_t st) {
-  const int n_tb = pan_pack_blocks(s.n_t);
+  const int n_tb = (s.n_t + PP_T * PP_N - 1) / (PP_T * PP_N);
   int w = p.R32 ? p.g_lo + p.ld32 : 0;
   if (p.R64) w = std::max(w, p.ld64);
   if (p.W64) w = std::max(w, p.ldw);
   if (p.A64) w = std::max(w, p.lda64);
   hipLaunchKernelGGL(k_pan_pack, dim3((unsigned)n_tb + pan_active(s), (unsigned)((w + PP_G - 1) / PP_G)),
                      dim3(256), 0, st, s, p, n_tb);
-  if (p.R32)
-    hipLaunchKernelGGL(k_pan_rmax, dim3((unsigned)((p.ld32 + 63) / 64)), dim3(1024), 0, st, p.bmax, n_tb,
-                       p.ld32, p.rmax);
 }
 
 // tiles of G rows [g_first, g_last) that hold pairs G <= G'
@@ -993,7 +886,7 @@ void pan_bin64_tasks(int n_g, int g_first, int g_last, std::vector<int>& tasks) 
   tile_list(n_g, g_first, g_last, PQ_G, tasks);
 }
 
-void launch_pan_bin(const PanelSort& s, const uint4* T, const PanelBin& b, hipStream_t st) {
+void launch_pan_bin(const PanelSort& s, const float4* T, const PanelBin& b, hipStream_t st) {
   // four and a half rounds of two blocks per CU at most: enough for the
   // hardware to even out the items' lengths, without the thousands of empty
   // blocks of a grid sized for the largest possible number of entries
@@ -1018,18 +911,10 @@ void launch_pan_bin64_pairs(const PanelSort& s, const double* T64, const PanelBi
   hipLaunchKernelGGL(k_pan_bin64_pairs, dim3(pan_grid(s, b.n_task)), dim3(256), 0, st, s, T64, b);
 }
 
-double pan_coef_scale(double eta) { return ldexp(1.0, 14 + ilogb(eta)); }
-float pan_moment_scale(const PanelSort& s) {
-  int e = 0;
-  while ((1 << e) < s.ch) ++e;
-  return ldexpf(1.0f / kPanelTScale, -e);
-}
-
 void launch_pan_coef(const PanelSort& s, const double* w, int n_w, double eta, int row0, int n_rb,
                      uint4* A, hipStream_t st) {
-  const double scale = pan_coef_scale(eta);
   const dim3 grid((unsigned)((n_rb * 64 + 255) / 256), pan_active(s));
-  hipLaunchKernelGGL(k_pan_coef, grid, dim3(256), 0, st, s, w, n_w, eta, scale, row0, n_rb, A);
+  hipLaunchKernelGGL(k_pan_coef, grid, dim3(256), 0, st, s, w, n_w, eta, row0, n_rb, A);
 }
 
 void launch_pan_coef64(const PanelSort& s, const double* w, int n_w, double eta, int ldm, double* K,
@@ -1044,10 +929,10 @@ int pan_gemm_blocks(const PanelGemm& g) {
 
 // the tile height that costs least: padded rows, and per tile the operand
 // columns that every tile stages again (about a third of a row block's time)
-int pan_row_frags(int n_rows, bool each) {
+int pan_row_frags(int n_rows) {
   int best = 1;
   double cost = 1e300;
-  for (int af = each ? 4 : 5; af >= 1; --af) {
+  for (int af = 5; af >= 1; --af) {
     const int rows = (n_rows + 32 * af - 1) / (32 * af) * (32 * af);
     const double c = rows * (1.0 + 0.35 / af);
     if (c < cost) {
@@ -1061,18 +946,12 @@ int pan_row_frags(int n_rows, bool each) {
 void launch_pan_gemm(const PanelSort& s, const PanelGemm& g, hipStream_t st) {
   const int total = pan_gemm_blocks(g) * g.ks;
   const dim3 grid((unsigned)(8 * ((total + 7) / 8)));
-  if (g.each) switch (g.af) {
-      case 1: hipLaunchKernelGGL((k_pan_gemm<1, true>), grid, dim3(256), 0, st, s, g); return;
-      case 2: hipLaunchKernelGGL((k_pan_gemm<2, true>), grid, dim3(256), 0, st, s, g); return;
-      case 3: hipLaunchKernelGGL((k_pan_gemm<3, true>), grid, dim3(256), 0, st, s, g); return;
-      default: hipLaunchKernelGGL((k_pan_gemm<4, true>), grid, dim3(256), 0, st, s, g); return;
-    }
   switch (g.af) {
-    case 1: hipLaunchKernelGGL((k_pan_gemm<1, false>), grid, dim3(256), 0, st, s, g); return;
-    case 2: hipLaunchKernelGGL((k_pan_gemm<2, false>), grid, dim3(256), 0, st, s, g); return;
-    case 3: hipLaunchKernelGGL((k_pan_gemm<3, false>), grid, dim3(256), 0, st, s, g); return;
-    case 4: hipLaunchKernelGGL((k_pan_gemm<4, false>), grid, dim3(256), 0, st, s, g); return;
-    default: hipLaunchKernelGGL((k_pan_gemm<5, false>), grid, dim3(256), 0, st, s, g); return;
+    case 1: hipLaunchKernelGGL(k_pan_gemm<1>, grid, dim3(256), 0, st, s, g); return;
+    case 2: hipLaunchKernelGGL(k_pan_gemm<2>, grid, dim3(256), 0, st, s, g); return;
+    case 3: hipLaunchKernelGGL(k_pan_gemm<3>, grid, dim3(256), 0, st, s, g); return;
+    case 4: hipLaunchKernelGGL(k_pan_gemm<4>, grid, dim3(256), 0, st, s, g); return;
+    default: hipLaunchKernelGGL(k_pan_gemm<5>, grid, dim3(256), 0, st, s, g); return;
   }
 }
 

@@ -11,8 +11,8 @@
 namespace qcx {
 
 constexpr int kPanStep = 32;      // positions per step; panels start on a step
+constexpr int kPanPlane = 16 * 2 * 3;  // bytes of the 16 terms of a moment or coefficient in its planes
 constexpr int kPanMax = 8192;     // panels of both sides
-constexpr float kPanelTScale = 4096.0f;  // scale of the fp16 basis functions
 
 // The transitions of one context in panel order (device arrays).  Panels
 // that hold transitions are listed in energy order, resonant side first, as
@@ -40,10 +40,10 @@ struct PanelSort {
 void pan_sort_geom(PanelSort& s);  // nb, per, ch, max_act, cap from n_t and P
 void launch_pan_sort(const PanelSort& s, hipStream_t st);
 
-// Chebyshev functions at the sorted energies: fp16 planes (hi, lo) in the
-// A-operand order of v_mfma_f32_16x16x32_f16, two fragments per step; or FP64
-// rows T64[position][32].
-void launch_pan_tab(const PanelSort& s, uint4* T, hipStream_t st);
+// Chebyshev functions at the sorted energies: FP32, 2 KB per step, lane l
+// holding function l % 16 at the positions 8 (l / 16) .. + 7 as two float4; or
+// FP64 rows T64[position][32].
+void launch_pan_tab(const PanelSort& s, float4* T, hipStream_t st);
 void launch_pan_tab64(const PanelSort& s, double* T64, hipStream_t st);
 
 // Sorted copies of the pair densities R[g][t], zero in padded positions; any
@@ -60,14 +60,11 @@ struct PanelPack {
   int ldw;
   double* A64;          // [position][lda64]: |R_g|^2
   int lda64;
-  float* bmax;          // [pan_pack_blocks][ld32] scratch, with R32
-  unsigned* rmax;       // [ld32] float bits of the largest |component| of each bulk row
 };
-int pan_pack_blocks(int n_t);
 void launch_pan_pack(const PanelSort& s, const PanelPack& p, hipStream_t st);
 
-// Moments of a range of pairs (G, G') as fp16 planes in the B-operand order
-// of v_mfma_f32_32x32x16_f16: [active][column tile of 32][plane][64 lanes][8].
+// Moments of a range of pairs (G, G') as three bf16 planes in the B-operand
+// order of v_mfma_f32_32x32x16_bf16: [active][column tile of 32][plane][64 lanes][8].
 // Columns: (Re, Im) part x nbp pairs (a multiple of 128), pair b of the range
 // at column part * nbp + b - b0.
 struct PanelBin {
@@ -79,15 +76,9 @@ struct PanelBin {
   long b0;              // first pair of the range (upper-triangle index of local rows)
   int nbp;
   uint2* S;
-  const unsigned* rmax;
-  float s_scale, c_unscale;  // pan_moment_scale; 1 / (its and the coefficients' scales)
-  float* unscale;       // [nbp] receives the factor of each column of the product
 };
-// powers of two that bring the moments and the coefficients into fp16 range
-float pan_moment_scale(const PanelSort& s);
-double pan_coef_scale(double eta);
 void pan_bin_tasks(int n_gl, int g_first, int g_last, std::vector<int>& tasks);
-void launch_pan_bin(const PanelSort& s, const uint4* T, const PanelBin& b, hipStream_t st);
+void launch_pan_bin(const PanelSort& s, const float4* T, const PanelBin& b, hipStream_t st);
 // FP64 moments S64[32 active + i][lds]: of the columns of a table X[position][ldx]
 // (n_col doubles, multiple of 32 readable), or of pairs (columns 2 (b - b0) + part)
 void launch_pan_bin64(const PanelSort& s, const double* T64, const double* X, int ldx, int n_col,
@@ -105,7 +96,7 @@ void pan_bin64_tasks(int n_g, int g_first, int g_last, std::vector<int>& tasks);
 void launch_pan_bin64_pairs(const PanelSort& s, const double* T64, const PanelBin64& b, hipStream_t st);
 
 // Series coefficients of 1 / (x_j - D + i eta), x = w (resonant panels) or -w:
-// fp16 planes in the A-operand order of v_mfma_f32_32x32x16_f16,
+// bf16 planes in the A-operand order of v_mfma_f32_32x32x16_bf16,
 // [active][n_rb row blocks of 32][plane][64][8], rows row0 .. of (Re, Im) per
 // frequency; or FP64 rows K[32 active + i][ldm].
 void launch_pan_coef(const PanelSort& s, const double* w, int n_w, double eta, int row0, int n_rb,
@@ -120,24 +111,22 @@ struct PanelGemm {
   const uint4* A;
   const uint4* S;
   int n_rb, af;
-  bool each;               // an entry's products summed apart before they enter (FP32 mode)
   int nbp, nb;             // padded and real pairs of the range (columns: Re, then Im)
   long b0;                 // first pair of the range in C
   int ks, row0, c_rows;
   int n_bulkp;
-  const float* unscale;    // [nbp]
   float* C;
 };
 int pan_gemm_blocks(const PanelGemm& g);  // tiles of one split
-int pan_row_frags(int n_rows, bool each);  // row blocks per tile for n_rows rows
+int pan_row_frags(int n_rows);  // row blocks per tile for n_rows rows
 void launch_pan_gemm(const PanelSort& s, const PanelGemm& g, hipStream_t st);
 
 // ------------------------------------------------------------ host (qcx_panel.hip)
 // Buffers of one panel run: a context's own, or those of one batch item.
 struct PanelBuf {
-  DevBuf desc, ints, Ds, T, T64, R, W, S, S64, A, K, tasks, scale;
+  DevBuf desc, ints, Ds, T, T64, R, W, S, S64, A, K, tasks;
   std::vector<DevBuf*> all() {
-    return {&desc, &ints, &Ds, &T, &T64, &R, &W, &S, &S64, &A, &K, &tasks, &scale};
+    return {&desc, &ints, &Ds, &T, &T64, &R, &W, &S, &S64, &A, &K, &tasks};
   }
 };
 
@@ -165,7 +154,7 @@ struct PanelJob {
   double eta;
   // geometry
   PanelSort s;
-  bool bulk;                       // a 16-bit bulk (pairs of the rows g_lo ..)
+  bool bulk;                       // a bulk below FP64 (pairs of the rows g_lo ..)
   int g_lo, n_gl, ld32;            // bulk rows
   int n_ps64;                      // FP64 pairs (0: none)
   int ld64;

@@ -44,11 +44,10 @@ static bool panels_pay(const PanelJob& j, int n_panels) {
   const double terms = 16.0 * std::min((double)n_panels, n_t);
   double direct = 0.0, panels = 40e-6;
   if (j.prec != QCX_FP64) {
-    const bool bf = j.prec == QCX_SPLIT_BF16;
-    const double rp = (double)roundup((size_t)rows, 128), rate = bf ? 4.2e14 : 1.3e14;
+    const double rp = (double)roundup((size_t)rows, 128);
     const double cols = 2.0 * pairs;
-    direct += 2.0 * rp * cols * n_t / rate;
-    panels += n_t * pairs / (bf ? 2.2e12 : 1.4e12) + 2.0 * rp * cols * terms / (bf ? 3.5e14 : 1.7e14);
+    direct += 2.0 * rp * cols * n_t / (j.prec == QCX_SPLIT_BF16 ? 4.2e14 : 1.3e14);
+    panels += n_t * pairs / 1.0e12 + 2.0 * rp * cols * terms / 2.0e14;
     if (j.hw64) {
       direct += 2.0 * rows * 2.0 * n_g * n_t / 4.0e13;
       panels += 2.0 * 32.0 * 2.0 * n_g * n_t / 2.0e13 + 2.0 * rows * 2.0 * n_g * 2.0 * terms / 2.0e13;
@@ -86,14 +85,14 @@ void PanelSet::plan(const std::vector<double>& w_ha, double eta_ha) {
 }
 
 bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
-  // the squares alone in 16 bits gain little (their direct sum is a small part
+  // the squares alone below FP64 gain little (their direct sum is a small part
   // of the pair densities they come from)
   if (j.diag && j.prec != QCX_FP64) return false;
-  // fp16 coefficients, scaled by the broadening, keep 22 bits down to 2^-18 of
-  // 1 / eta: a broadening far below the energies is left to the direct sum
+  // a broadening far below the energies (nothing below this was measured) is
+  // left to the direct sum
   if (j.prec != QCX_FP64 && !(j.eta >= 1e-4 * std::max(1.0, set.w_max))) return false;
-  // below about 10,000 transitions the direct FP32 sum in many splits is as
-  // accurate (8000: 0.96e-7 against 1.06e-7; 13824: 1.16e-7 against 1.10e-7)
+  // below about 10,000 transitions a direct FP32 sum in many splits can be as
+  // accurate (its error grows with the transitions, this route's does not)
   if (j.prec == QCX_FP32 && j.n_t < 10000) return false;
   if (!set.ok || j.n_t < 2 || !(force || panels_pay(j, set.P0))) return false;
   const int P0 = set.P0;
@@ -127,11 +126,11 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
   j.row_chunk = 0;
   j.bulk = g.n_bulk > 0;
   if (j.bulk) {
-    const int af = pan_row_frags(g.n_rows, j.prec == QCX_FP32);
+    const int af = pan_row_frags(g.n_rows);
     g.n_rowsp = (int)roundup(g.n_rows, 32 * af);
     g.c_rows = g.n_rowsp;
     j.ld32 = (int)roundup(j.n_gl, 16);
-    const size_t per_pair = (size_t)s.max_act * 16 * 4 * 2;  // moments: 16 terms, two planes, two parts
+    const size_t per_pair = (size_t)s.max_act * kPanPlane * 2;  // moments of two parts
     split_rows(j.n_gl, 16, (long)(kPanMoments / per_pair), false, j.ranges);
     for (PanelJob::Range& r : j.ranges) {
       std::vector<int> t;
@@ -142,20 +141,23 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
     }
     // Splits: two blocks per CU in one round where the tiles are few, entries
     // per split within the FP32 accumulation limit of 1024 steps, and enough
-    // of them for the accuracy: the rounding of the sums grows with the root
-    // of the entries per split and is the largest error of this route.  The
-    // split mode takes two at least (its error is then below the direct sum's;
-    // 0.4% of the time), the FP32 mode eight where that is at most 4 GiB:
-    // 113 G, 400 frequencies, 8000 | 32768 transitions 1.9e-7 | 2.1e-7 with two,
-    // 1.1e-7 | 1.2e-7 with eight (12% of the time of chi0).
+    // of them for the accuracy: the rounding of the sums grows with the root of
+    // the entries per split and is the largest error of this route.  The split
+    // mode takes two at least (2e-7 against the direct sum's 6e-7 to 1.5e-6),
+    // the FP32 mode one per 56 panels of a side and eight at least: rms error
+    // of chi0 at 113 G with two | eight splits, 16,000 transitions 1.8e-7 |
+    // 1.05e-7 (direct 7.2e-7), 65,536 2.1e-7 | 1.05e-7 (direct 1.5e-6); the
+    // most accurate direct sum met (40 G, 64 splits) has 1.25e-7.  Where they
+    // would take more than 4 GiB the FP32 mode sums directly.
     const int tiles = (g.n_rowsp / (32 * af)) * ((2 * g.n_bulkp / 32 + 7) / 8);
     const size_t split = sizeof(float) * g.c_rows * 2 * (size_t)g.n_bulkp;
-    const int least = j.prec == QCX_FP32 ? (int)std::min<size_t>(8, ((size_t)4 << 30) / split) : 2;
-    int ks = std::max({2, least, std::min(8, 512 / std::max(1, tiles))});
+    const int least = j.prec == QCX_FP32 ? std::max(8, (P0 + 55) / 56) : 2;
+    if (j.prec == QCX_FP32 && least * split > (size_t)4 << 30) return false;
+    int ks = std::max(least, std::min(8, 512 / std::max(1, tiles)));
     ks = std::max(ks, (s.max_act + 1023) / 1024);
     g.ksplit = ks;
     j.c_floats = (size_t)ks * g.c_rows * 2 * g.n_bulkp;
-    const size_t per_rb = (size_t)s.max_act * 2 * 1024;
+    const size_t per_rb = (size_t)s.max_act * kPanPlane * 32;
     j.row_chunk = (int)std::max<size_t>(1, kPanCoefs / (per_rb * af)) * af;
     j.row_chunk = std::min(j.row_chunk, g.n_rowsp / 32);
   }
@@ -199,11 +201,10 @@ static std::vector<size_t> job_bytes(const PanelJob& j, const PanelSet& set) {
   const PanelSort& s = j.s;
   const size_t pos = (size_t)s.cap * kPanStep;
   const size_t ints = 2 * (size_t)s.n_t + (size_t)s.nb * s.P + s.P + 4 * (size_t)s.max_act + 64;
-  size_t r = 0, wg = 0, mom = 0, mom64 = 0, max_nbp = 0;
+  size_t r = 0, wg = 0, mom = 0, mom64 = 0;
   if (j.bulk) r = pos * j.ld32 * sizeof(float2);
-  for (const PanelJob::Range& x : j.ranges) max_nbp = std::max(max_nbp, (size_t)x.nbp);
   for (const PanelJob::Range& x : j.ranges)
-    mom = std::max(mom, (size_t)s.max_act * 16 * 4 * 2 * x.nbp);
+    mom = std::max(mom, (size_t)s.max_act * kPanPlane * 2 * x.nbp);
   for (const PanelJob::Range& x : j.ranges64)
     mom64 = std::max(mom64, (size_t)s.max_act * kPanelTerms64 * roundup((j.diag ? 1 : 2) * x.nb, 128));
   if (j.n_ps64) wg = pos * j.ld64 * (j.diag ? sizeof(double) : sizeof(cplx));
@@ -216,10 +217,9 @@ static std::vector<size_t> job_bytes(const PanelJob& j, const PanelSet& set) {
           wg,
           mom,
           mom64 * sizeof(double),
-          j.bulk ? (size_t)s.max_act * j.row_chunk * 2 * 1024 : 0,
+          j.bulk ? (size_t)s.max_act * j.row_chunk * kPanPlane * 32 : 0,
           j.n_ps64 ? (size_t)s.max_act * kPanelTerms64 * kk_ldm(j.n_w) * sizeof(double) : 0,
-          sizeof(int) * std::max<size_t>(1, j.tasks.size()),
-          j.bulk ? sizeof(float) * (j.ld32 + max_nbp + (size_t)pan_pack_blocks(s.n_t) * j.ld32) : 0};
+          sizeof(int) * std::max<size_t>(1, j.tasks.size())};
 }
 
 hipError_t pan_job_reserve(PanelJob& j, const PanelSet& set, PanelBuf& b) {
@@ -253,7 +253,7 @@ hipError_t pan_job_reserve(PanelJob& j, const PanelSet& set, PanelBuf& b) {
 void pan_enqueue_sort(const PanelJob& j, const PanelBuf& b, const double* d_w, hipStream_t st) {
   const PanelSort& s = j.s;
   launch_pan_sort(s, st);
-  if (j.bulk) launch_pan_tab(s, b.T.as<uint4>(), st);
+  if (j.bulk) launch_pan_tab(s, b.T.as<float4>(), st);
   if (j.n_ps64) {
     launch_pan_tab64(s, b.T64.as<double>(), st);
     launch_pan_coef64(s, d_w, j.n_w, j.eta, kk_ldm(j.n_w), b.K.as<double>(), st);
@@ -269,17 +269,9 @@ void pan_enqueue_response(const PanelJob& j, const PanelBuf& b, const cplx* R, s
   p.ldt = ldt;
   p.n_g = j.n_g;
   p.g_lo = j.g_lo;
-  // scratch of the scales: the rows' largest components, the columns' factors
-  unsigned* rmax = b.scale.as<unsigned>();
-  float* unscale = nullptr;
   if (j.bulk) {
-    size_t nbp = 0;
-    for (const PanelJob::Range& r : j.ranges) nbp = std::max(nbp, (size_t)r.nbp);
-    unscale = b.scale.as<float>() + j.ld32;
     p.R32 = b.R.as<float2>();
     p.ld32 = j.ld32;
-    p.rmax = rmax;
-    p.bmax = unscale + nbp;
   }
   if (j.n_ps64) {
     if (j.diag) {
@@ -297,7 +289,6 @@ void pan_enqueue_response(const PanelJob& j, const PanelBuf& b, const cplx* R, s
   const int2* tasks = b.tasks.as<int2>();
   if (j.bulk) {
     const int n_rb = j.g.n_rowsp / 32;
-    const float s_scale = pan_moment_scale(s);
     bool coefs = false;  // one range of rows: its coefficients serve every range of pairs
     for (const PanelJob::Range& r : j.ranges) {
       PanelBin pb{};
@@ -309,19 +300,13 @@ void pan_enqueue_response(const PanelJob& j, const PanelBuf& b, const cplx* R, s
       pb.b0 = r.b0;
       pb.nbp = r.nbp;
       pb.S = b.S.as<uint2>();
-      pb.rmax = rmax;
-      pb.s_scale = s_scale;
-      // the basis functions' scale is part of s_scale: it is not in the moments
-      pb.c_unscale = (float)(1.0 / (pan_coef_scale(j.eta) * (double)s_scale * kPanelTScale));
-      pb.unscale = unscale;
-      launch_pan_bin(s, b.T.as<uint4>(), pb, st);
+      launch_pan_bin(s, b.T.as<float4>(), pb, st);
       for (int rb0 = 0; rb0 < n_rb; rb0 += j.row_chunk) {
         PanelGemm q{};
         q.A = b.A.as<uint4>();
         q.S = b.S.as<uint4>();
         q.n_rb = std::min(j.row_chunk, n_rb - rb0);
-        q.af = pan_row_frags(j.g.n_rows, j.prec == QCX_FP32);
-        q.each = j.prec == QCX_FP32;
+        q.af = pan_row_frags(j.g.n_rows);
         q.nbp = r.nbp;
         q.nb = r.nb;
         q.b0 = r.b0;
@@ -329,7 +314,6 @@ void pan_enqueue_response(const PanelJob& j, const PanelBuf& b, const cplx* R, s
         q.row0 = 32 * rb0;
         q.c_rows = j.g.n_rowsp;
         q.n_bulkp = j.g.n_bulkp;
-        q.unscale = unscale;
         q.C = C;
         if (!coefs || j.row_chunk < n_rb)
           launch_pan_coef(s, d_w, j.n_w, j.eta, 32 * rb0, q.n_rb, b.A.as<uint4>(), st);

@@ -661,7 +661,7 @@ static int chi0_panels(qcx_ctx* ctx, const PanelJob& job) {
   ctx->ks64 = job.g64.ksplit;
   ctx->bulk_c64 = false;
   ctx->bulk_nst = 0;
-  ctx->bulk_af = pan_row_frags(job.g.n_rows, job.prec == QCX_FP32);
+  ctx->bulk_af = pan_row_frags(job.g.n_rows);
   ctx->tune_ms = 0.0;
   int sp_all, sp;
   HIPCK(span_begin(ctx, 3, &sp_all));

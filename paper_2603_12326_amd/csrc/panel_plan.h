@@ -12,11 +12,15 @@
 // of a side depend on the frequencies and the broadening alone: they cover
 // the whole energy axis, are as wide as the convergence of the series allows
 // (about the broadening between the frequencies, growing with the distance
-// outside), and end on both sides in an unbounded panel, on which
+// outside), and end on both sides, kPanelFar from the frequencies, in an
+// unbounded panel, on which
 //   1 / (x - D + i eta) = -(u / S) / (1 - zeta u),  u = S / (D - c),
 //   zeta = (x - c + i eta) / S,
 // is u times a series in 2u - 1 (c lies beyond the frequencies on the other
-// side of the panel, so 0 < u <= 1 and Re zeta > 0).
+// side of the panel, so 0 < u <= 1 and Re zeta > 0).  There Im W falls as u^2
+// and its series only as u: the imaginary part keeps u times the relative
+// accuracy.  Bounded panels keep it whole, so they cover every energy that
+// occurs (a handful more per side: their width grows with the distance).
 //
 // Host code without HIP, so that it can be compiled and checked alone.
 #pragma once
@@ -42,6 +46,7 @@ struct PanelDesc {
 // kPanelTol^2 = 1e-16, the rounding of FP64.
 constexpr int kPanelTerms = 16, kPanelTerms64 = 32;
 constexpr double kPanelTol = 1e-8;
+constexpr double kPanelFar = 1e4;  // Hartree; the deepest core level lies above -5e3
 
 // Remainder of the series after kPanelTerms terms relative to |1 / (z - y)|;
 // |r| is the sum of the semi-axes of the ellipse with foci -1 and 1 through z.
@@ -93,23 +98,18 @@ inline bool panel_side(const std::vector<double>& x, double eta, int max_panels,
     if (it != x.begin()) d = std::min(d, c - *(it - 1));
     return panel_remainder(cd(d, eta) / h) <= kPanelTol;
   };
-  // left end: the nearest X to the poles that still converges
-  double d0 = 0.0, d1 = span;
-  while (!unbounded_ok(lo - d1, -1)) {
-    d0 = d1;
-    d1 *= 2.0;
-    if (!(d1 < 1e6 * span)) return false;
+  // left end
+  double far = kPanelFar;
+  while (!unbounded_ok(lo - far, -1)) {
+    far *= 2.0;
+    if (!(far < 1e6 * std::max(span, kPanelFar))) return false;
   }
-  for (int i = 0; i < 30; ++i) {
-    const double m = 0.5 * (d0 + d1);
-    (unbounded_ok(lo - m, -1) ? d1 : d0) = m;
-  }
-  double a = lo - d1;
+  double a = lo - far;
   desc.push_back(unbounded(a, -1));
   edge.push_back(a);
   const double h_min = 0.25 * eta;  // converges wherever the poles are
   double h = h_min;
-  while (!unbounded_ok(a, 1)) {
+  while (!(a >= hi + kPanelFar && unbounded_ok(a, 1))) {
     if ((int)desc.size() + 2 > max_panels) return false;
     // widest panel from a: the previous width while it still just fits
     // (between dense frequencies), else a bracket refined by bisection
@@ -119,7 +119,7 @@ inline bool panel_side(const std::vector<double>& x, double eta, int max_panels,
       do {
         g0 = g1;
         g1 *= 2.0;
-      } while (bounded_ok(a, g1) && g1 < 1e6 * span);
+      } while (bounded_ok(a, g1));  // ends: the poles are a finite distance away
       for (int i = 0; i < 12; ++i) {
         const double m = 0.5 * (g0 + g1);
         (bounded_ok(a, m) ? g0 : g1) = m;

@@ -139,6 +139,39 @@ inline bool panel_side(const std::vector<double>& x, double eta, int max_panels,
   return true;
 }
 
+// Are the panels the cheaper route?  Estimated seconds of the direct sum, which
+// costs rows x transitions x columns, and of the panels, whose sum over the
+// transitions is formed once (16 or 32 terms each), followed by rows x panels x
+// columns; their dozen small launches cost as much as a whole small problem.
+// The rates are least squares fits to both routes timed on MI355X at 70 random
+// sizes (3^3 to 8^3 k points, 20 to 181 G, 8 to 450 frequencies; nine in ten
+// within 12%, direct 18%, of the time).  Where the rule took the panels they
+// never lost by more than 19%; where it did not they would have won by 47% at
+// most.
+struct PanelWork {
+  bool fp64, fp32;  // else split-BF16
+  bool diag;        // only the squares
+  int n_t, n_g, n_w;
+};
+inline bool panels_pay(const PanelWork& k, int n_panels) {
+  auto up = [](double x, double m) { return std::ceil(x / m) * m; };
+  const double n_t = k.n_t, n_g = k.n_g, rows = 2.0 * k.n_w;
+  const double pairs = k.diag ? n_g : n_g * (n_g + 1) / 2, p = std::min((double)n_panels, n_t);
+  if (k.fp64) {
+    const double direct = 17e-6 + rows * 2 * pairs * n_t / 2.3e13 + n_t * pairs / 3.3e11;
+    return 176e-6 + 0.96e-9 * n_t + n_t * pairs / 2.9e11 + p * pairs / 6.2e10 +
+               up(rows, 160) * up((k.diag ? 1 : 2) * pairs, 128) * p / 1.6e12 <
+           direct;
+  }
+  const double rp = up(rows, 128), direct = k.fp32 ? 66e-6 + rp * 2 * pairs * n_t / 6.75e13 + 0.87e-9 * n_t + rp * n_t / 4.3e11
+                                                   : 60e-6 + rp * 2 * pairs * n_t / 1.64e14 + rp * n_t / 3.9e11;
+  // in FP32 the panels are the more accurate route (rms 1e-7 against 1.3e-7 to
+  // 1.5e-6): they may take 15% longer
+  return 236e-6 + 0.5e-9 * n_t + n_t * pairs / 1.0e12 + up(rows, 160) * 2 * n_g * p / 2.5e11 +
+             up(rows, 32) * up(2 * pairs, 256) * p / (k.fp32 ? 1.27e13 : 3.7e13) <
+         (k.fp32 ? 1.15 : 1.0) * direct;
+}
+
 // The same panels for poles at -x[j] + i eta (the anti-resonant side).
 inline void panel_mirror(const std::vector<double>& edge, const std::vector<PanelDesc>& desc,
                          std::vector<double>& m_edge, std::vector<PanelDesc>& m_desc) {

@@ -32,34 +32,6 @@ void split_rows(int n, int tile, long most, bool diag, std::vector<PanelJob::Ran
 }
 }  // namespace
 
-// Estimated seconds of the direct sum and of the panels (rates of the kernels
-// on MI355X).  The direct sum costs rows x transitions x columns, the panels
-// 16 or 32 rows x transitions x columns (formed once, bound by forming the
-// products) plus rows x terms x columns and a dozen small launches; they lose
-// where the frequencies are few or the panels nearly as many as the
-// transitions.
-static bool panels_pay(const PanelJob& j, int n_panels) {
-  const double n_t = j.n_t, rows = 2.0 * j.n_w;
-  const double n_g = j.n_g, pairs = j.diag ? n_g : n_g * (n_g + 1) / 2;
-  const double terms = 16.0 * std::min((double)n_panels, n_t);
-  double direct = 0.0, panels = 40e-6;
-  if (j.prec != QCX_FP64) {
-    const double rp = (double)roundup((size_t)rows, 128);
-    const double cols = 2.0 * pairs;
-    direct += 2.0 * rp * cols * n_t / (j.prec == QCX_SPLIT_BF16 ? 4.2e14 : 1.3e14);
-    panels += n_t * pairs / 1.0e12 + 2.0 * rp * cols * terms / 2.0e14;
-    if (j.hw64) {
-      direct += 2.0 * rows * 2.0 * n_g * n_t / 4.0e13;
-      panels += 2.0 * 32.0 * 2.0 * n_g * n_t / 2.0e13 + 2.0 * rows * 2.0 * n_g * 2.0 * terms / 2.0e13;
-    }
-  } else {
-    const double cols = 2.0 * pairs;
-    direct += 2.0 * rows * cols * n_t / 4.5e13;
-    panels += 2.0 * 32.0 * cols * n_t / 5.0e13 + 2.0 * rows * cols * 2.0 * terms / 5.0e13;
-  }
-  return panels < direct;
-}
-
 void PanelSet::plan(const std::vector<double>& w_ha, double eta_ha) {
   if (eta == eta_ha && w == w_ha) return;
   w = w_ha;
@@ -94,7 +66,9 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
   // below about 10,000 transitions a direct FP32 sum in many splits can be as
   // accurate (its error grows with the transitions, this route's does not)
   if (j.prec == QCX_FP32 && j.n_t < 10000) return false;
-  if (!set.ok || j.n_t < 2 || !(force || panels_pay(j, set.P0))) return false;
+  if (!set.ok || j.n_t < 2 ||
+      !(force || panels_pay({j.prec == QCX_FP64, j.prec == QCX_FP32, j.diag, j.n_t, j.n_g, j.n_w}, set.P0)))
+    return false;
   const int P0 = set.P0;
   PanelSort& s = j.s;
   s = PanelSort{};

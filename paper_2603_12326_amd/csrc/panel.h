@@ -134,7 +134,7 @@ struct PanelBuf {
 // the list stays the same.
 struct PanelSet {
   std::vector<double> w;
-  double eta = -1.0, w_max = 0.0;
+  double eta = -1.0;
   bool ok = false;
   int P0 = 0;
   std::vector<char> table;  // PanelDesc[2 P0], then the edges of both sides
@@ -170,8 +170,9 @@ struct PanelJob {
   Geom64 g64;                      // and of XY
   size_t c_floats, xy_doubles;     // sizes of C and XY
 };
-// false: sum the transitions directly (no broadening, too many panels, or the
-// direct sum is the cheaper one)
+PanelWork pan_work(const PanelJob& j);
+// false: sum the transitions directly (too many panels, or the direct sum is the
+// cheaper one)
 // (force: whenever possible, as the remainder of a job that pays)
 bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force = false);
 // reserve the buffers of a planned job and bind its device views; the caller

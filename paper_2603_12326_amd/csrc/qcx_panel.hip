@@ -32,6 +32,10 @@ void split_rows(int n, int tile, long most, bool diag, std::vector<PanelJob::Ran
 }
 }  // namespace
 
+PanelWork pan_work(const PanelJob& j) {
+  return {j.prec == QCX_FP64, j.prec == QCX_FP32, j.diag, j.n_t, j.n_g, j.n_w};
+}
+
 void PanelSet::plan(const std::vector<double>& w_ha, double eta_ha) {
   if (eta == eta_ha && w == w_ha) return;
   w = w_ha;
@@ -39,7 +43,6 @@ void PanelSet::plan(const std::vector<double>& w_ha, double eta_ha) {
   uploaded = false;
   std::vector<double> x = w_ha;
   std::sort(x.begin(), x.end());
-  w_max = std::max(std::fabs(x.front()), std::fabs(x.back()));
   std::vector<double> edge, me;
   std::vector<PanelDesc> desc, md;
   ok = panel_side(x, eta, kPanMax / 2, edge, desc);
@@ -57,18 +60,7 @@ void PanelSet::plan(const std::vector<double>& w_ha, double eta_ha) {
 }
 
 bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
-  // the squares alone below FP64 gain little (their direct sum is a small part
-  // of the pair densities they come from)
-  if (j.diag && j.prec != QCX_FP64) return false;
-  // a broadening far below the energies (nothing below this was measured) is
-  // left to the direct sum
-  if (j.prec != QCX_FP64 && !(j.eta >= 1e-4 * std::max(1.0, set.w_max))) return false;
-  // below about 10,000 transitions a direct FP32 sum in many splits can be as
-  // accurate (its error grows with the transitions, this route's does not)
-  if (j.prec == QCX_FP32 && j.n_t < 10000) return false;
-  if (!set.ok || j.n_t < 2 ||
-      !(force || panels_pay({j.prec == QCX_FP64, j.prec == QCX_FP32, j.diag, j.n_t, j.n_g, j.n_w}, set.P0)))
-    return false;
+  if (!set.ok || !(force || panels_pay(pan_work(j), set.P0))) return false;
   const int P0 = set.P0;
   PanelSort& s = j.s;
   s = PanelSort{};

@@ -631,6 +631,9 @@ static int panels_ready(qcx_ctx* ctx, const std::vector<double>& w, PanelJob& jo
   if (ctx->force_nst || ctx->budget.limit) return QCX_OK;
   job.n_t = ctx->n_t;
   job.n_w = (int)w.size();
+  double w_max = 0.0;
+  for (double x : w) w_max = std::max(w_max, std::fabs(x));
+  if (!panels_possible(pan_work(job), job.eta, w_max)) return QCX_OK;
   ctx->pan_set.plan(w, job.eta);
   if (!pan_job_plan(job, ctx->pan_set)) return QCX_OK;
   hipError_t e = pan_job_reserve(job, ctx->pan_set, ctx->pan_buf);

@@ -11,7 +11,8 @@ CSRC = Path(__file__).resolve().parent.parent / "paper_2603_12326_amd" / "csrc"
 HA = 27.211386245988
 
 # reads lines: precision (0 FP64, 1 FP32, 2 split), diag, n_t, n_g, n_w, eta, w_max
-# (0 .. w_max evenly), n_panels (0: of the plan); prints the panels of a side and the choice
+# (0 .. w_max evenly), n_panels (0: of the plan); prints the panels of a side, the
+# choice, and what is known of it before the plan
 _PROGRAM = r"""
 #include "panel_plan.h"
 #include <cstdio>
@@ -22,7 +23,8 @@ int main() {
     std::vector<double> x(n_w), e; std::vector<PanelDesc> d;
     for (int i = 0; i < n_w; ++i) x[i] = n_w > 1 ? top * i / (n_w - 1) : top;
     if (!n_p && panel_side(x, eta, 4096, e, d)) n_p = (int)d.size();
-    printf("%d %d\n", n_p, (int)panels_pay({prec == 0, prec == 1, diag != 0, n_t, n_g, n_w}, n_p));
+    const PanelWork k{prec == 0, prec == 1, diag != 0, n_t, n_g, n_w};
+    printf("%d %d %d\n", n_p, (int)panels_pay(k, n_p), (int)panels_possible(k, eta, top));
   }
 }
 """
@@ -58,5 +60,23 @@ def _run(program, lines):
 def test_faster_route_is_taken(program):
     """Sizes at which one route takes at least a quarter more than the other."""
     got = _run(program, [(p, 0, t, g, w, eta, top, 0) for p, t, g, w, eta, top, _, _ in _MEASURED])
-    for m, (_, panels) in zip(_MEASURED, got):
+    for m, (_, panels, _) in zip(_MEASURED, got):
         assert bool(panels) == (m[7] < m[6]), m
+
+
+def test_no_plan_where_panels_cannot_be_taken(program):
+    """Calls that panels never serve are known as such before any plan is made:
+    small problems, the diagonal below FP64, few FP32 transitions, a vanishing
+    broadening.  And nothing that pays with its own plan is lost."""
+    never = [(0, 0, 3072, 27, 128, 0.2, 40, 0), (2, 0, 3072, 27, 128, 0.2, 40, 0), (2, 1, 27648, 4096, 400, 0.1, 60, 0),
+             (1, 1, 65536, 4096, 400, 0.1, 60, 0), (1, 0, 9999, 181, 400, 0.1, 60, 0), (2, 0, 65536, 113, 400, 0.002, 60, 1),
+             (2, 0, 65536, 113, 400, 0.0, 60, 1), (0, 0, 65536, 113, 400, 0.0, 60, 1), (0, 0, 1296, 60, 100, 0.1, 60, 0)]
+    assert [r[2] for r in _run(program, never)] == [0] * len(never)
+    rng = np.random.default_rng(4)
+    many = [(p, d, int(t), int(g), int(w), float(eta), float(rng.uniform(30, 60)), 0)
+            for p in (0, 1, 2) for d in (0, 1) if p == 0 or not d
+            for t, g, w, eta in zip(np.exp(rng.uniform(7, 11.5, 150)), np.exp(rng.uniform(2, 6.5, 150)),
+                                    np.exp(rng.uniform(1, 6.5, 150)), rng.uniform(0.08, 0.3, 150)) if p != 1 or t >= 10000]
+    got = _run(program, many)
+    assert sum(r[1] for r in got) > 100
+    assert all(r[2] >= r[1] for r in got)

@@ -29,9 +29,13 @@ __host__ __device__ inline cplx cadd(cplx a, cplx b) { return {a.re + b.re, a.im
 // Device buffer owned by a context; grows, never shrinks, freed on destroy.
 // With a budget attached, a growth that would take the budget's total above
 // its limit (limit 0: none) fails with hipErrorOutOfMemory and keeps the old
-// buffer.
+// buffer.  Before a growth fails for want of memory the budget's owner is asked
+// once to free what it can do without.  A failed growth is reported by its
+// return value alone (it leaves no error for the next launch check to find).
 struct DevBudget {
   size_t used = 0, limit = 0;
+  bool (*give_back)(void*) = nullptr;  // true: something was freed
+  void* owner = nullptr;
 };
 struct DevBuf {
   void* p = nullptr;
@@ -39,17 +43,22 @@ struct DevBuf {
   DevBudget* budget = nullptr;
   hipError_t reserve(size_t n) {
     if (n <= bytes) return hipSuccess;
-    if (budget && budget->limit && budget->used - bytes + n > budget->limit)
-      return hipErrorOutOfMemory;
-    release();
-    hipError_t e = hipMalloc(&p, n);
-    if (e == hipSuccess) {
-      bytes = n;
-      if (budget) budget->used += n;
-    } else {
-      p = nullptr;
+    for (bool again = false;; again = true) {
+      hipError_t e = hipErrorOutOfMemory;
+      if (!(budget && budget->limit && budget->used - bytes + n > budget->limit)) {
+        release();
+        e = hipMalloc(&p, n);
+        if (e == hipSuccess) {
+          bytes = n;
+          if (budget) budget->used += n;
+          return e;
+        }
+        p = nullptr;
+        (void)hipGetLastError();
+      }
+      if (e != hipErrorOutOfMemory || again || !budget || !budget->give_back || !budget->give_back(budget->owner))
+        return e;
     }
-    return e;
   }
   void release() {
     if (p) (void)hipFree(p);

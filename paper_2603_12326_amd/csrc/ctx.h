@@ -22,6 +22,10 @@ using namespace qcx;
 namespace qcx {
 struct BatchPlan;
 void destroy_plan(BatchPlan* p);
+// Free the buffers of the panel route, which keep nothing between calls: true
+// if there were any, they are not in use by the call under way and the stream
+// is not being captured (qcx_runtime.hip).  c is a qcx_ctx.
+bool panels_give_back(void* c);
 }  // namespace qcx
 
 namespace qcx {
@@ -83,6 +87,7 @@ struct qcx_ctx {
   qcx::PanelSet pan_set;
   qcx::PanelBuf pan_buf;
   std::vector<int> h_pan_tasks_up;  // what pan_buf.tasks last received
+  bool pan_busy = false;            // a call is using or reserving them
   DevBuf d_Fg, d_Rp;  // optical limit: gradient integrals, band momentum matrices
   // qcx_mlp_infer: the rejected frequencies of the rows under way on this stream
   // (outside the budget, as the networks' buffers are)
@@ -143,6 +148,8 @@ struct qcx_ctx {
                      &d_Fg, &d_Rp};
   }
   qcx_ctx() {
+    budget.give_back = qcx::panels_give_back;
+    budget.owner = this;
     for (DevBuf* b : buffers()) b->budget = &budget;
     for (DevBuf* b : pan_buf.all()) b->budget = &budget;
   }

@@ -122,7 +122,7 @@ int pan_row_frags(int n_rows);  // row blocks per tile for n_rows rows
 void launch_pan_gemm(const PanelSort& s, const PanelGemm& g, hipStream_t st);
 
 // ------------------------------------------------------------ host (qcx_panel.hip)
-// Buffers of one panel run: a context's own, or those of one batch item.
+// Buffers of a context's panel runs.
 struct PanelBuf {
   DevBuf desc, ints, Ds, T, T64, R, W, S, S64, A, K, tasks;
   std::vector<DevBuf*> all() {
@@ -175,6 +175,8 @@ PanelWork pan_work(const PanelJob& j);
 // cheaper one)
 // (force: whenever possible, as the remainder of a job that pays)
 bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force = false);
+// bytes by which the buffers of a planned job would grow
+size_t pan_job_grows(const PanelJob& j, const PanelSet& set, PanelBuf& b);
 // reserve the buffers of a planned job and bind its device views; the caller
 // then uploads desc, edge and tasks
 hipError_t pan_job_reserve(PanelJob& j, const PanelSet& set, PanelBuf& b);

@@ -503,6 +503,13 @@ int time_plan(qcx_ctx* ctx, const BatchPlan* P, double* ms) {
   return QCX_OK;
 }
 
+// the panel buffers of every context of a batch that has run out of memory
+bool give_back_all(qcx_ctx* const* ctxs, int n_ctx) {
+  bool any = false;
+  for (int c = 0; c < n_ctx; ++c) any |= panels_give_back(ctxs[c]);
+  return any;
+}
+
 // Both batch entry points; n_G and G_int are null for qcx_run_batch
 int run_batch_impl(qcx_ctx* const* ctxs, int n_ctx, const int* n_G, const int* const* G_int,
                    const qcx_item* items, int n_items, int precision, int headwings_fp64, int lfe) {
@@ -536,9 +543,11 @@ int run_batch_impl(qcx_ctx* const* ctxs, int n_ctx, const int* n_G, const int* c
   }
   HIPCK(hipSetDevice(ctx->device));
   // the G lists: host checks against each context's q, buffers sized
-  for (int c = 0; n_G && c < n_ctx; ++c)
-    if (int rc = rho_prepare(ctxs[c], n_G[c], G_int[c], true, false))
-      return fail(ctx, rc, "context " + std::to_string(c) + ": " + ctxs[c]->err);
+  for (int c = 0; n_G && c < n_ctx; ++c) {
+    int rc = rho_prepare(ctxs[c], n_G[c], G_int[c], true, false);
+    if (rc == QCX_ENOMEM && give_back_all(ctxs, n_ctx)) rc = rho_prepare(ctxs[c], n_G[c], G_int[c], true, false);
+    if (rc) return fail(ctx, rc, "context " + std::to_string(c) + ": " + ctxs[c]->err);
+  }
   const int hw64 = headwings_fp64 ? 1 : 0;
   std::vector<double> key =
       batch_key(ctxs, n_ctx, items, n_items, precision, lfe ? 1 : 0, hw64, n_G, G_int);
@@ -565,10 +574,15 @@ int run_batch_impl(qcx_ctx* const* ctxs, int n_ctx, const int* n_G, const int* c
     BatchPlan* best = nullptr;
     double best_ms = 0.0;
     for (int target : cands) {
-      BatchPlan* P = new BatchPlan();
-      P->key = key;
-      int rc = build_plan(ctx, ctxs, n_ctx, items, n_items, precision, lfe ? 1 : 0, hw64, target,
-                          n_G, G_int, P);
+      BatchPlan* P = nullptr;
+      int rc = QCX_OK;
+      for (bool again = false;; again = true) {
+        P = new BatchPlan();
+        P->key = key;
+        rc = build_plan(ctx, ctxs, n_ctx, items, n_items, precision, lfe ? 1 : 0, hw64, target, n_G, G_int, P);
+        if (rc != QCX_ENOMEM || again || !give_back_all(ctxs, n_ctx)) break;
+        destroy_plan(P);
+      }
       double ms = 0.0;
       if (rc == QCX_OK && cands.size() > 1) rc = time_plan(ctx, P, &ms);
       if (rc != QCX_OK) {

@@ -26,9 +26,8 @@ struct Member {
     b.frag = frag.as<uint16_t>();
     return b;
   }
-  void release() {
-    DevBuf* all[] = {&p, &m, &v, &g, &w1b, &w[0], &w[1], &w[2], &wt[0], &wt[1], &wt[2], &w5b, &frag};
-    for (DevBuf* b : all) b->release();
+  std::vector<DevBuf*> all() {
+    return {&p, &m, &v, &g, &w1b, &w[0], &w[1], &w[2], &wt[0], &wt[1], &wt[2], &w5b, &frag};
   }
 };
 
@@ -53,13 +52,18 @@ struct qcx_mlp {
   int cap_query = 0;
   double qmax = 1.0, wmax = 1.0, mu = 0.0, sigma = 1.0, calib = 1.0;
   Lattice lat{};
+  DevBudget budget;  // no limit; ctx's panel buffers make room
+  std::vector<DevBuf*> all() {
+    std::vector<DevBuf*> r = {&Z[0], &Z[1], &Z[2], &Z[3], &Hb[0], &Hb[1], &Hb[2], &Hb[3], &HT[0], &HT[1],
+                              &HT[2], &dZ[0], &dZ[1], &dZb[0], &dZb[1], &dZbT[0], &dZbT[1], &y, &dy, &sq,
+                              &hist, &flag, &red, &xq, &ys, &sel_counts, &iQ, &iw, &ierr, &iflag};
+    for (Member& m : mem)
+      for (DevBuf* b : m.all()) r.push_back(b);
+    return r;
+  }
   bool have_encoding = false;
   ~qcx_mlp() {
-    for (Member& m : mem) m.release();
-    DevBuf* all[] = {&Z[0], &Z[1], &Z[2], &Z[3], &Hb[0], &Hb[1], &Hb[2], &Hb[3], &HT[0], &HT[1],
-                     &HT[2], &dZ[0], &dZ[1], &dZb[0], &dZb[1], &dZbT[0], &dZbT[1], &y, &dy, &sq,
-                     &hist, &flag, &red, &xq, &ys, &sel_counts, &iQ, &iw, &ierr, &iflag};
-    for (DevBuf* b : all) b->release();
+    for (DevBuf* b : all()) b->release();
     if (h_flag) (void)hipHostFree(h_flag);
     if (ev_flag) (void)hipEventDestroy(ev_flag);
   }
@@ -255,6 +259,9 @@ int qcx_mlp_create(qcx_mlp** out, qcx_ctx* ctx, int n_members) {
   qcx_mlp* m = new qcx_mlp();
   m->ctx = ctx;
   m->mem.resize(n_members);
+  m->budget.give_back = panels_give_back;
+  m->budget.owner = ctx;
+  for (DevBuf* b : m->all()) b->budget = &m->budget;
   for (Member& w : m->mem) {
     const size_t np = sizeof(float) * kNParam;
     hipError_t e = hipSuccess;

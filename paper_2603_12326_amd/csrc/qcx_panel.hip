@@ -188,6 +188,15 @@ static std::vector<size_t> job_bytes(const PanelJob& j, const PanelSet& set) {
           sizeof(int) * std::max<size_t>(1, j.tasks.size())};
 }
 
+size_t pan_job_grows(const PanelJob& j, const PanelSet& set, PanelBuf& b) {
+  const std::vector<size_t> need = job_bytes(j, set);
+  const std::vector<DevBuf*> bufs = b.all();
+  size_t grow = 0;
+  for (size_t i = 0; i < bufs.size(); ++i)
+    if (need[i] + 64 > bufs[i]->bytes) grow += need[i] + 64 - bufs[i]->bytes;
+  return grow;
+}
+
 hipError_t pan_job_reserve(PanelJob& j, const PanelSet& set, PanelBuf& b) {
   const std::vector<size_t> need = job_bytes(j, set);
   const std::vector<DevBuf*> bufs = b.all();

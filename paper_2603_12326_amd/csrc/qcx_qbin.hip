@@ -36,10 +36,12 @@ struct qcx_qbin {
   double dq = 0.0;
   std::vector<long long> cnt;  // entries per bin
   DevBuf d_sum, d_eps, d_bins, d_off, d_ent, d_cnt, d_state, d_ft, d_fo, d_fi, d_om, d_w;
+  qcx::DevBudget budget;  // no limit; the context's panel buffers make room
+  std::vector<DevBuf*> all() {
+    return {&d_sum, &d_eps, &d_bins, &d_off, &d_ent, &d_cnt, &d_state, &d_ft, &d_fo, &d_fi, &d_om, &d_w};
+  }
   void release() {
-    DevBuf* all[] = {&d_sum, &d_eps, &d_bins, &d_off, &d_ent, &d_cnt,
-                     &d_state, &d_ft, &d_fo, &d_fi, &d_om, &d_w};
-    for (DevBuf* b : all) b->release();
+    for (DevBuf* b : all()) b->release();
   }
 };
 
@@ -220,6 +222,9 @@ int qcx_qbin_create(qcx_qbin** out, qcx_ctx* ctx, int n_w, int n_shell, double d
   HIPCK(hipSetDevice(ctx->device));
   qcx_qbin* b = new qcx_qbin();
   b->ctx = ctx;
+  b->budget.give_back = panels_give_back;
+  b->budget.owner = ctx;
+  for (DevBuf* d : b->all()) d->budget = &b->budget;
   b->n_w = n_w;
   b->n_shell = n_shell;
   b->n_theta = n_theta;

@@ -588,7 +588,7 @@ int qcx_pair_density_optical(qcx_ctx* ctx, int n_G, const int* G_int, const doub
   return pair_density_impl(ctx, n_G, G_int, rho_out, true, qhat);
 }
 
-// Give the panel route's buffers back (waits for work that uses them)
+// Free the panel route's buffers (waits for work that uses them)
 static void panels_release(qcx_ctx* ctx) {
   (void)hipSetDevice(ctx->device);
   (void)hipStreamSynchronize(ctx->stream);
@@ -596,6 +596,34 @@ static void panels_release(qcx_ctx* ctx) {
   ctx->pan_set.uploaded = false;
   ctx->h_pan_tasks_up.clear();
 }
+
+}  // extern "C"
+
+bool qcx::panels_give_back(void* c) {
+  qcx_ctx* ctx = static_cast<qcx_ctx*>(c);
+  bool any = false;
+  for (DevBuf* b : ctx->pan_buf.all()) any = any || b->p;
+  if (ctx->pan_busy || !any) return false;
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &s) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (s != hipStreamCaptureStatusNone) return false;
+  panels_release(ctx);
+  return true;
+}
+
+namespace {
+// the panel buffers stay while a call reserves or uses them
+struct PanelsBusy {
+  qcx_ctx* c;
+  explicit PanelsBusy(qcx_ctx* ctx) : c(ctx) { c->pan_busy = true; }
+  ~PanelsBusy() { c->pan_busy = false; }
+};
+}  // namespace
+
+extern "C" {
 
 // What the assembly reads after qcx_chi0 / qcx_chi0_kk
 static AsmArgs asm_args(const qcx_ctx* ctx) {
@@ -622,11 +650,15 @@ static int chi0_export(qcx_ctx* ctx, void* chi0_out) {
 
 // Plan the panel route for the frequencies w (Hartree) of the call; job.n_g,
 // prec, eta, hw64 and diag are given.  *use: planned, its buffers reserved and its tables
-// on the device.  The transitions are summed directly where the panels do not
-// pay, when a test has forced a pipeline of the direct kernel, under a memory
-// cap (whose users sized it for the direct route's buffers) and when the
-// device has no room for the panels' buffers.
-static int panels_ready(qcx_ctx* ctx, const std::vector<double>& w, PanelJob& job, bool* use) {
+// on the device; last (if given) is the same for the rest of a list of G.  The
+// transitions are summed directly where the panels do not pay, when a test has
+// forced a pipeline of the direct kernel, under a memory cap (whose users sized
+// it for the direct route's buffers) and when the device has no room for the
+// panels' buffers: they may take half of what is free, which leaves the other
+// half to what the direct route would have left it to (other contexts; this
+// one's own later calls get these buffers back, panels_give_back).
+static int panels_ready(qcx_ctx* ctx, const std::vector<double>& w, PanelJob& job, bool* use,
+                        PanelJob* last = nullptr) {
   *use = false;
   if (ctx->force_nst || ctx->budget.limit) return QCX_OK;
   job.n_t = ctx->n_t;
@@ -636,27 +668,45 @@ static int panels_ready(qcx_ctx* ctx, const std::vector<double>& w, PanelJob& jo
   if (!panels_possible(pan_work(job), job.eta, w_max)) return QCX_OK;
   ctx->pan_set.plan(w, job.eta);
   if (!pan_job_plan(job, ctx->pan_set)) return QCX_OK;
-  hipError_t e = pan_job_reserve(job, ctx->pan_set, ctx->pan_buf);
-  if (e == hipSuccess) e = ctx->d_C.reserve(sizeof(float) * job.c_floats);
-  if (e == hipSuccess) e = ctx->d_XY.reserve(sizeof(double) * job.xy_doubles);
-  if (e == hipErrorOutOfMemory) {
-    (void)hipGetLastError();
-    panels_release(ctx);
-    return QCX_OK;
+  if (last) {
+    last->n_t = job.n_t;
+    last->n_w = job.n_w;
+    if (!pan_job_plan(*last, ctx->pan_set, true)) return QCX_OK;
   }
-  HIPCK(e);
+  PanelsBusy busy(ctx);
+  const size_t n_c = sizeof(float) * job.c_floats;
+  const size_t n_xy = sizeof(double) * std::max(job.xy_doubles, last ? last->xy_doubles : 0);
+  auto grows = [](size_t n, const DevBuf& b) { return n > b.bytes ? n - b.bytes : 0; };
+  const size_t grow = pan_job_grows(job, ctx->pan_set, ctx->pan_buf) + grows(n_c, ctx->d_C) + grows(n_xy, ctx->d_XY);
+  if (grow) {
+    size_t free = 0, total = 0;
+    HIPCK(hipMemGetInfo(&free, &total));
+    if (grow > free / 2) return QCX_OK;
+  }
+  hipError_t e = last ? pan_job_reserve(*last, ctx->pan_set, ctx->pan_buf) : hipSuccess;
+  if (e == hipSuccess) e = pan_job_reserve(job, ctx->pan_set, ctx->pan_buf);
+  if (e == hipSuccess && last) e = pan_job_reserve(*last, ctx->pan_set, ctx->pan_buf);  // bound to what job grew
+  if (e == hipSuccess) e = ctx->d_C.reserve(n_c);
+  if (e == hipSuccess) e = ctx->d_XY.reserve(n_xy);
+  if (e != hipSuccess) {
+    panels_release(ctx);  // and with them what the tables below are known to hold
+    if (e == hipErrorOutOfMemory) return QCX_OK;
+    HIPCK(e);
+  }
   if (!ctx->pan_set.uploaded) {
     HIPCK(upload(ctx, ctx->pan_buf.desc, ctx->pan_set.table.data(), ctx->pan_set.table.size()));
     ctx->pan_set.uploaded = true;
   }
   if (!job.tasks.empty()) HIPCK(upload_cached(ctx, ctx->pan_buf.tasks, ctx->h_pan_tasks_up, job.tasks));
   job.s.dt = ctx->d_dt.as<double>();
+  if (last) last->s.dt = job.s.dt;
   *use = true;
   return QCX_OK;
 }
 
 // chi0 of the current pair densities through a planned panel job
 static int chi0_panels(qcx_ctx* ctx, const PanelJob& job) {
+  PanelsBusy busy(ctx);
   hipStream_t st = ctx->stream;
   ctx->geom = job.g;
   ctx->geom64 = job.g64;
@@ -705,15 +755,12 @@ int qcx_loss_diag(qcx_ctx* ctx, int n_G, const int* G_int, int n_w, const double
   job.diag = true;
   job.prec = precision;
   job.eta = eta_eV / kHartreeEV;
-  if (int rc = panels_ready(ctx, w, job, &panels)) return rc;
   last = job;
-  if (panels && n_G > kChunk && n_G % kChunk) {
-    last.n_g = n_G % kChunk;
-    if (!pan_job_plan(last, ctx->pan_set, true)) return fail(ctx, QCX_EDEVICE, "internal: panel plan");
-    HIPCK(pan_job_reserve(last, ctx->pan_set, ctx->pan_buf));
-    last.s.dt = job.s.dt;
-    HIPCK(ctx->d_XY.reserve(sizeof(double) * last.xy_doubles));
-  }
+  last.n_g = n_G % kChunk;
+  // the densities' buffers first: what is left is for the panels
+  if (int rc = rho_prepare(ctx, job.n_g, G_int, false, false)) return rc;
+  if (int rc = panels_ready(ctx, w, job, &panels, n_G > kChunk && n_G % kChunk ? &last : nullptr)) return rc;
+  std::unique_ptr<PanelsBusy> busy(panels ? new PanelsBusy(ctx) : nullptr);
   const double eta = eta_eV / kHartreeEV;
   const bool bulk = precision != QCX_FP64, bf = precision == QCX_SPLIT_BF16;
   // weights of the bulk once (they do not depend on G)

@@ -327,7 +327,7 @@ __global__ void __launch_bounds__(256) k_pan_pack(PanelSort s, PanelPack p, int 
 // forming of the products, whose times add up (113 G, 65,536 transitions: 395
 // us, of which the MFMAs are 200 and the vector instructions 100; forming the
 // products of one or two G ahead changed nothing).
-constexpr int PB_G = 8;
+constexpr int PB_G = kPanBinRows;
 
 // store terms 4 q .. 4 q + 3 (q = lane / 16) of one column
 __device__ __forceinline__ void pan_store(uint2* __restrict__ S, size_t tile0, int col, int q, const f32x4& v) {
@@ -537,7 +537,7 @@ __global__ void __launch_bounds__(256) k_pan_bin64(PanelSort s, const double* __
 // written (620 MB for 89 G): two G rows leave room for four waves per SIMD with
 // two steps of loads in flight, 478 us there; four rows with one step in flight
 // (one wave per SIMD) 794, at two waves 588 to 626; one row 523, three 530.
-constexpr int PQ_G = 2;
+constexpr int PQ_G = kPanBin64Rows;
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_pan_bin64_pairs(PanelSort s, const double* __restrict__ T64, PanelBin64 b) {
   const int lane = threadIdx.x & 63;

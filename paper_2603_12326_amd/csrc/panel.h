@@ -158,12 +158,7 @@ struct PanelJob {
   int g_lo, n_gl, ld32;            // bulk rows
   int n_ps64;                      // FP64 pairs (0: none)
   int ld64;
-  struct Range {
-    int g0, g1, task0, n_task;     // rows of the range and their tiles
-    long b0;
-    int nb, nbp;
-  };
-  std::vector<Range> ranges, ranges64;
+  std::vector<PanelRange> ranges, ranges64;
   std::vector<int> tasks;          // {G, G'} of all ranges, bulk then FP64
   int row_chunk;                   // row blocks of coefficients held at once
   Chi0Geom g;                      // what the assembly reads of C

@@ -139,6 +139,32 @@ inline bool panel_side(const std::vector<double>& x, double eta, int max_panels,
   return true;
 }
 
+// Ranges of rows of G whose pairs' moments are held at once: rows [0, n) in whole
+// tiles of `tile` rows, at most `most` pairs (one tile at least).  The tiles are
+// those of the moments kernels (16 rows for each put the FP64 moments of 1024 G
+// and 1000 frequencies at 14 GB; two take 1.8).
+constexpr int kPanBinRows = 8, kPanBin64Rows = 2;  // FP32, FP64
+struct PanelRange {
+  int g0, g1, task0, n_task;  // rows and their tiles in the task list
+  long b0;                    // upper-triangle index of the first pair
+  int nb, nbp;                // pairs, padded to 128
+};
+inline void panel_ranges(int n, int tile, long most, bool diag, std::vector<PanelRange>& out) {
+  auto first = [&](int g) { return diag ? (long)g : (long)g * n - (long)g * (g - 1) / 2; };
+  out.clear();
+  for (int g = 0; g < n;) {
+    PanelRange r{};
+    r.g0 = g;
+    r.g1 = std::min(n, g + tile);
+    while (r.g1 < n && first(std::min(n, r.g1 + tile)) - first(g) <= most) r.g1 = std::min(n, r.g1 + tile);
+    r.b0 = first(g);
+    r.nb = (int)(first(r.g1) - r.b0);
+    r.nbp = (r.nb + 127) / 128 * 128;
+    out.push_back(r);
+    g = r.g1;
+  }
+}
+
 // Are the panels the cheaper route?  Estimated seconds of the direct sum, which
 // costs rows x transitions x columns, and of the panels, whose sum over the
 // transitions is formed once (16 or 32 terms each), followed by rows x panels x

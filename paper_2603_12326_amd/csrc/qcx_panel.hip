@@ -9,27 +9,6 @@ namespace qcx {
 namespace {
 // moments S of one range of pairs, and coefficients of one range of rows
 constexpr size_t kPanMoments = (size_t)4 << 30, kPanCoefs = (size_t)2 << 30;
-
-// upper-triangle index of the first pair of row g
-long row_start(int n, int g) { return (long)g * n - (long)g * (g - 1) / 2; }
-
-// rows [0, n) in ranges of whole tiles whose pairs fit `most`
-void split_rows(int n, int tile, long most, bool diag, std::vector<PanelJob::Range>& out) {
-  out.clear();
-  for (int g = 0; g < n;) {
-    PanelJob::Range r{};
-    r.g0 = g;
-    auto pairs = [&](int e) { return diag ? (long)(e - g) : row_start(n, e) - row_start(n, g); };
-    int e = std::min(n, g + tile);
-    while (e < n && pairs(std::min(n, e + tile)) <= most) e = std::min(n, e + tile);
-    r.g1 = e;
-    r.b0 = diag ? g : row_start(n, g);
-    r.nb = (int)pairs(e);
-    r.nbp = (int)roundup(r.nb, 128);
-    out.push_back(r);
-    g = e;
-  }
-}
 }  // namespace
 
 PanelWork pan_work(const PanelJob& j) {
@@ -97,8 +76,8 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
     g.c_rows = g.n_rowsp;
     j.ld32 = (int)roundup(j.n_gl, 16);
     const size_t per_pair = (size_t)s.max_act * kPanPlane * 2;  // moments of two parts
-    split_rows(j.n_gl, 16, (long)(kPanMoments / per_pair), false, j.ranges);
-    for (PanelJob::Range& r : j.ranges) {
+    panel_ranges(j.n_gl, kPanBinRows, (long)(kPanMoments / per_pair), false, j.ranges);
+    for (PanelRange& r : j.ranges) {
       std::vector<int> t;
       pan_bin_tasks(j.n_gl, r.g0, r.g1, t);
       r.task0 = (int)j.tasks.size() / 2;
@@ -140,10 +119,10 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
     j.ld64 = (int)roundup(j.n_g, 32);
     const size_t per_col = (size_t)s.max_act * kPanelTerms64 * sizeof(double);
     if (fp64)
-      split_rows(j.n_g, j.diag ? 128 : 16, (long)(kPanMoments / (per_col * parts)), j.diag, j.ranges64);
+      panel_ranges(j.n_g, j.diag ? 128 : kPanBin64Rows, (long)(kPanMoments / (per_col * parts)), j.diag, j.ranges64);
     else
       j.ranges64.push_back({0, j.n_g, 0, 0, 0, j.n_g, j.n_g});
-    for (PanelJob::Range& r : j.ranges64) {
+    for (PanelRange& r : j.ranges64) {
       if (!fp64 || j.diag) continue;
       std::vector<int> t;
       pan_bin64_tasks(j.n_g, r.g0, r.g1, t);
@@ -169,9 +148,9 @@ static std::vector<size_t> job_bytes(const PanelJob& j, const PanelSet& set) {
   const size_t ints = 2 * (size_t)s.n_t + (size_t)s.nb * s.P + s.P + 4 * (size_t)s.max_act + 64;
   size_t r = 0, wg = 0, mom = 0, mom64 = 0;
   if (j.bulk) r = pos * j.ld32 * sizeof(float2);
-  for (const PanelJob::Range& x : j.ranges)
+  for (const PanelRange& x : j.ranges)
     mom = std::max(mom, (size_t)s.max_act * kPanPlane * 2 * x.nbp);
-  for (const PanelJob::Range& x : j.ranges64)
+  for (const PanelRange& x : j.ranges64)
     mom64 = std::max(mom64, (size_t)s.max_act * kPanelTerms64 * roundup((j.diag ? 1 : 2) * x.nb, 128));
   if (j.n_ps64) wg = pos * j.ld64 * (j.diag ? sizeof(double) : sizeof(cplx));
   return {set.table.size(),
@@ -265,7 +244,7 @@ void pan_enqueue_response(const PanelJob& j, const PanelBuf& b, const cplx* R, s
   if (j.bulk) {
     const int n_rb = j.g.n_rowsp / 32;
     bool coefs = false;  // one range of rows: its coefficients serve every range of pairs
-    for (const PanelJob::Range& r : j.ranges) {
+    for (const PanelRange& r : j.ranges) {
       PanelBin pb{};
       pb.R32 = b.R.as<float2>();
       pb.ld32 = j.ld32;
@@ -297,7 +276,7 @@ void pan_enqueue_response(const PanelJob& j, const PanelBuf& b, const cplx* R, s
       }
     }
   }
-  for (const PanelJob::Range& r : j.ranges64) {
+  for (const PanelRange& r : j.ranges64) {
     const int cols = parts * r.nb, lds = (int)roundup(cols, 128);
     double* S64 = b.S64.as<double>();
     if (j.prec != QCX_FP64) {

@@ -193,7 +193,7 @@ int qcx_pair_density_optical(qcx_ctx* ctx, int n_G, const int* G_int, const doub
  * directly for each frequency where that is cheaper (few frequencies or
  * transitions), for eta = 0, in the FP32 and split-BF16 modes for eta below 1e-4
  * of the larger of 1 Ha and the largest |w|, in FP32 below 10,000 transitions
- * and where its splits would take more than 4 GiB, under a forced pipeline
+ * and where its splits would take more than 8 GiB, under a forced pipeline
  * (qcx_set_bulk_pipeline), under a memory cap (qcx_set_memory_limit) and where
  * the panels' buffers would take more than half of the device memory that is
  * free.  The context keeps those buffers for its next call and frees them when

@@ -93,11 +93,12 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
     // of chi0 at 113 G with two | eight splits, 16,000 transitions 1.8e-7 |
     // 1.05e-7 (direct 7.2e-7), 65,536 2.1e-7 | 1.05e-7 (direct 1.5e-6); the
     // most accurate direct sum met (40 G, 64 splits) has 1.25e-7.  Where they
-    // would take more than 4 GiB the FP32 mode sums directly.
+    // would take more than the direct sum's partials may (8 GiB) the FP32 mode
+    // sums directly.
     const int tiles = (g.n_rowsp / (32 * af)) * ((2 * g.n_bulkp / 32 + 7) / 8);
     const size_t split = sizeof(float) * g.c_rows * 2 * (size_t)g.n_bulkp;
     const int least = j.prec == QCX_FP32 ? std::max(8, (P0 + 55) / 56) : 2;
-    if (j.prec == QCX_FP32 && least * split > (size_t)4 << 30) return false;
+    if (j.prec == QCX_FP32 && least * split > (size_t)8 << 30) return false;
     int ks = std::max(least, std::min(8, 512 / std::max(1, tiles)));
     ks = std::max(ks, (s.max_act + 1023) / 1024);
     g.ksplit = ks;

@@ -1343,7 +1343,9 @@ int qcx_eps_inv_given(qcx_ctx* ctx, int n_w, int n_G, const void* eps, int lfe, 
 
 int qcx_set_memory_limit(qcx_ctx* ctx, size_t bytes) {
   if (!ctx) return QCX_EINVAL;
-  if (bytes) panels_release(ctx);  // a capped context sums the transitions directly
+  // a capped context sums the transitions directly (while its stream is being
+  // captured the buffers stay until something needs their room)
+  if (bytes) (void)panels_give_back(ctx);
   ctx->budget.limit = bytes;
   return QCX_OK;
 }

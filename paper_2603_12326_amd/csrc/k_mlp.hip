@@ -155,7 +155,8 @@ constexpr int FW_LD = kW + 8;    // bf16 per row of activations
 // (the division's result to the last bit but for rare ties, at a third of its
 // instructions)
 __device__ inline float silu_nr(float z) {
-  const float d = 1.0f + __expf(fminf(-z, 80.0f));  // finite: below -80 the result is zero in bf16 terms
+  z = z < -80.0f ? -80.0f : z;  // |SiLU| < 2e-33 from there on, and d stays finite for the Newton step
+  const float d = 1.0f + __expf(-z);
   float r = __builtin_amdgcn_rcpf(d);
   r = fmaf(r, fmaf(-d, r, 1.0f), r);
   return z * r;

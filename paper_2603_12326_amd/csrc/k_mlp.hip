@@ -105,7 +105,7 @@ __global__ void __launch_bounds__(256) k_gemm_nt(const uint16_t* __restrict__ A,
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float z = acc[4 * g + i] + bias;
-        if (e.f.Z) e.f.Z[(size_t)(mb + i) * N + n] = z;
+        e.f.Z[(size_t)(mb + i) * N + n] = z;
         hb[i] = to_bf16(silu(z));
         e.f.Hb[(size_t)(mb + i) * N + n] = hb[i];
       }
@@ -317,26 +317,24 @@ __global__ void __launch_bounds__(256) k_layer1(const float* __restrict__ x,
     float z = b;
 #pragma unroll
     for (int c = 0; c < kIn; ++c) z += sx[r][c] * w[c];
-    if (Z1) Z1[(size_t)(r0 + r) * kW + j] = z;
+    Z1[(size_t)(r0 + r) * kW + j] = z;
     hb[r] = to_bf16(silu(z));
     H1b[(size_t)(r0 + r) * kW + j] = hb[r];
   }
-  if (H1T) {
-    uint4* dst = reinterpret_cast<uint4*>(H1T + (size_t)j * ldt + r0);
+  uint4* dst = reinterpret_cast<uint4*>(H1T + (size_t)j * ldt + r0);
 #pragma unroll
-    for (int q = 0; q < L1_ROWS / 8; ++q) {
-      uint4 v;
-      v.x = hb[8 * q + 0] | ((uint32_t)hb[8 * q + 1] << 16);
-      v.y = hb[8 * q + 2] | ((uint32_t)hb[8 * q + 3] << 16);
-      v.z = hb[8 * q + 4] | ((uint32_t)hb[8 * q + 5] << 16);
-      v.w = hb[8 * q + 6] | ((uint32_t)hb[8 * q + 7] << 16);
-      dst[q] = v;
-    }
+  for (int q = 0; q < L1_ROWS / 8; ++q) {
+    uint4 v;
+    v.x = hb[8 * q + 0] | ((uint32_t)hb[8 * q + 1] << 16);
+    v.y = hb[8 * q + 2] | ((uint32_t)hb[8 * q + 3] << 16);
+    v.z = hb[8 * q + 4] | ((uint32_t)hb[8 * q + 5] << 16);
+    v.w = hb[8 * q + 6] | ((uint32_t)hb[8 * q + 7] << 16);
+    dst[q] = v;
   }
 }
 
 // ---------------------------------------------------------------------------
-// output layer (+ loss and layer-4 backward in training): block = 256 threads
+// output layer, loss and layer-4 backward: block = 256 threads
 // = 256 neurons, 16 rows per block; the dot products reduce through LDS.
 // ---------------------------------------------------------------------------
 constexpr int OUT_ROWS = 16;
@@ -362,20 +360,17 @@ __global__ void __launch_bounds__(256) k_output(const uint16_t* __restrict__ H4b
     const int r = r0 + j;
     const float yr = ((red[0][j] + red[1][j]) + (red[2][j] + red[3][j])) + b5[0];
     if (r < n) y[r] = yr;
-    if (t) {
-      float d = 0.0f, s = 0.0f;
-      if (r < n) {
-        const long src = order ? (long)order[off + r] : (long)r;
-        const float e = yr - t[src];
-        d = 2.0f * e / (float)n;
-        s = e * e;
-      }
-      dy[r] = d;
-      sq[r] = s;
-      sdy[j] = d;
+    float d = 0.0f, s = 0.0f;
+    if (r < n) {
+      const long src = order ? (long)order[off + r] : (long)r;
+      const float e = yr - t[src];
+      d = 2.0f * e / (float)n;
+      s = e * e;
     }
+    dy[r] = d;
+    sq[r] = s;
+    sdy[j] = d;
   }
-  if (!t) return;
   __syncthreads();
   uint16_t db[OUT_ROWS];
 #pragma unroll

@@ -51,7 +51,7 @@ struct FwdNets {
 };
 
 // Epilogue variants of the bf16 NT GEMM C[M][N] = sum_k A[m][k] B[n][k].
-struct EpiFwd {       // z = acc + bias; Z (optional) = z; Hb = bf16(silu z); HT (optional)
+struct EpiFwd {       // z = acc + bias; Z = z; Hb = bf16(silu z); HT its transpose, or null
   const float* bias;
   float* Z;
   uint16_t* Hb;
@@ -86,8 +86,8 @@ void launch_forward(const float* x, int n, const FwdNets& nets, int n_nets, floa
 void launch_layer1(const float* x, const int* order, long off, int n, int rows_p,
                    const uint16_t* w1b, const float* b1, float* Z1, uint16_t* H1b, uint16_t* H1T,
                    int ldt, hipStream_t st);
-// output layer: y = bf16(h4) . w5b + b5.  With t != NULL (training) also
-// dy = 2 (y - t) / n_true (0 on padded rows), sq[r] = (y - t)^2, and the
+// output layer: y = bf16(h4) . w5b + b5, dy = 2 (y - t) / n_true (0 on padded
+// rows), sq[r] = (y - t)^2, and the
 // layer-4 backward dz4 = dy w5b silu'(Z4) into dZ / dZb / dZbT.
 void launch_output(const uint16_t* H4b, const uint16_t* w5b, const float* b5, int n, int rows_p,
                    float* y, const float* t, const int* order, long off, float* dy, float* sq,

@@ -242,10 +242,11 @@ void launch_eps_assemble(const AsmArgs& a, const Chi0Geom& g, cplx* eps, hipStre
 // Gauss-Jordan diag(eps^-1) of n_w matrices; a zero or non-finite pivot in
 // matrix j sets *sing to at most w_base + j (atomic minimum).  The matrices are
 // read from src; eps (src itself, or apart from it; not read or written up to
-// n_g = kGjRegMax) holds the sweep.  diag lies outside src.
+// n_g = kGjRegMax) holds the sweep.  diag lies outside src.  Where the matrices
+// are a chunk of a longer call, n_all is the number of that call.
 constexpr int kGjRegMax = 128;
 void launch_gj_diag(const cplx* src, cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,
-                    int w_base = 0);
+                    int w_base = 0, int n_all = 0);
 // noLFE loss from diagonal-only partials of n_g G (chunk columns 0..n_g-1)
 // into loss[j * ldl + g0 + b]
 // loss[w][g0 + b] (and, if inv is not null, inv[w][g0 + b] = 1 / eps_GG) for

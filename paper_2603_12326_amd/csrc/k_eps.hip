@@ -9,6 +9,7 @@
 // which row k served as pivot.
 #include <limits.h>
 
+#include <algorithm>
 #include <utility>
 
 #include "common.h"
@@ -832,6 +833,7 @@ struct GjRun {
   int *sing, w_base;
   const GjJob* jobs;
   int n_jobs;
+  int n_all;  // matrices of the whole call, of which this launch may be a chunk
 };
 
 void gj_gather(const GjRun& r, hipStream_t st) {
@@ -882,7 +884,10 @@ void gj_panels(const GjRun& r, hipStream_t st) {
 // 10522; n = 749, 64 11953 | 12945, 128 23417 | 21449; n = 953, 32 16881 |
 // 17715, 64 33785 | 26906.
 void gj_tiles(int cls, const GjRun& r, hipStream_t st) {
-  const bool few = r.n_w <= (cls == 7 ? 32 : cls == 6 ? 64 : 128);
+  // Up to n = 320 both forms give the same bits.  Above, their rounding differs,
+  // so the whole call decides: the results of a call that runs in chunks are
+  // those of one that does not.
+  const bool few = (cls <= 4 ? r.n_w : r.n_all) <= (cls == 7 ? 32 : cls == 6 ? 64 : 128);
   switch (cls) {
     case 2: return few ? gj_tiles<3, 2, 16>(r, st) : gj_tiles<3, 4, 8>(r, st);
     case 3: return few ? gj_tiles<4, 2, 16>(r, st) : gj_tiles<4, 4, 8>(r, st);
@@ -897,7 +902,7 @@ void gj_tiles(int cls, const GjRun& r, hipStream_t st) {
 }  // namespace
 
 void launch_gj_diag(const cplx* src, cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,
-                    int w_base) {
+                    int w_base, int n_all) {
   const dim3 g(n_w), b(1024);
   const int cls = gj_class(n_g);
   if (cls == 0)
@@ -905,7 +910,7 @@ void launch_gj_diag(const cplx* src, cplx* eps, int n_g, int n_w, cplx* diag, in
   else if (cls == 1)
     hipLaunchKernelGGL((k_gj_reg<2, 8>), g, b, 0, st, src, n_g, diag, sing, w_base);
   else
-    gj_tiles(cls, GjRun{src, eps, n_g, n_w, diag, sing, w_base, nullptr, 0}, st);
+    gj_tiles(cls, GjRun{src, eps, n_g, n_w, diag, sing, w_base, nullptr, 0, std::max(n_w, n_all)}, st);
 }
 
 void launch_gj_jobs(int cls, const GjJob* jobs, int n_jobs, int n_blocks, int max_n, hipStream_t st) {
@@ -915,7 +920,7 @@ void launch_gj_jobs(int cls, const GjJob* jobs, int n_jobs, int n_blocks, int ma
   else if (cls == 1)
     hipLaunchKernelGGL((k_gj_reg_jobs<2, 8>), g, b, 0, st, jobs, n_jobs);
   else
-    gj_tiles(cls, GjRun{nullptr, nullptr, max_n, n_blocks, nullptr, nullptr, 0, jobs, n_jobs}, st);
+    gj_tiles(cls, GjRun{nullptr, nullptr, max_n, n_blocks, nullptr, nullptr, 0, jobs, n_jobs, n_blocks}, st);
 }
 
 void launch_nolfe_diag(const cplx* eps, int n_g, int n_w, cplx* diag, int* sing, hipStream_t st,

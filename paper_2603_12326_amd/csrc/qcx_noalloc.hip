@@ -77,7 +77,7 @@ int qcx_eps_inv_given_noalloc(qcx_ctx* ctx, int n_w, int n_G, const void* eps, i
         HIPCK(hipMemcpyAsync(work, from, sizeof(cplx) * (size_t)m * n * n, hipMemcpyDeviceToDevice, st));
         from = work;
       }
-      launch_gj_diag(from, work, n_G, m, diag, status_out, st, w0);
+      launch_gj_diag(from, work, n_G, m, diag, status_out, st, w0, n_w);
     } else {
       launch_nolfe_diag(src + (size_t)w0 * n * n, n_G, m, diag, status_out, st, w0);
     }

@@ -879,15 +879,16 @@ void gj_panels(const GjRun& r, hipStream_t st) {
 // sweeps leave compute units free for those; past that its 1024-thread update
 // blocks, one per compute unit, are the bound, and smaller ones win: 8 waves
 // holding four columns each up to n = 320, above it panels and updates in two
-// launches (gj_panels).  Measured, us (gj_tiles | the other): n = 259, 97
-// matrices 849 | 891, 160 1225 | 1095; n = 500, 128 5557 | 6276, 256 10963 |
-// 10522; n = 749, 64 11953 | 12945, 128 23417 | 21449; n = 953, 32 16881 |
-// 17715, 64 33785 | 26906.
+// launches (gj_panels).  Measured, us (gj_tiles | the other): n = 180, 160
+// matrices 412 | 423, 200 524 | 458; n = 259, 128 matrices 910 | 936, 160 1113 |
+// 1029; n = 500, 128 5392 | 5931, 192 8110 | 8154, 256 10781 | 10123; n = 749, 96
+// 15930 | 16257, 128 21367 | 20545; n = 800, 32 8051 | 8476, 48 12247 | 10989;
+// n = 953, 16 6369 | 8101, 32 15677 | 14724, 64 31903 | 23775.
 void gj_tiles(int cls, const GjRun& r, hipStream_t st) {
   // Up to n = 320 both forms give the same bits.  Above, their rounding differs,
   // so the whole call decides: the results of a call that runs in chunks are
   // those of one that does not.
-  const bool few = (cls <= 4 ? r.n_w : r.n_all) <= (cls == 7 ? 32 : cls == 6 ? 64 : 128);
+  const bool few = (cls <= 4 ? r.n_w : r.n_all) <= (cls == 7 ? 32 : cls == 6 ? 96 : cls == 5 ? 192 : 128);
   switch (cls) {
     case 2: return few ? gj_tiles<3, 2, 16>(r, st) : gj_tiles<3, 4, 8>(r, st);
     case 3: return few ? gj_tiles<4, 2, 16>(r, st) : gj_tiles<4, 4, 8>(r, st);

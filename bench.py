@@ -5,9 +5,12 @@ One step = the whole path for the Si-like workload with N_G = 113 (28 GTOs,
 4 valence + 16 conduction bands, 8^3 k grid, 10 q along [100], 400 frequencies
 over 0-60 eV, eta = 0.1 eV): for each q, set_states (device-resident inputs,
 orthonormality check included), pair_density, chi0, eps_inv and loss.  The
-metric is (q, w) loss points per second with the chi0 bulk in split-BF16 on
-MFMA (FP64 head/wings and inversion); the plain FP32-MFMA form is timed the
-same way and reported beside it.
+metric is (q, w) loss points per second in the split-BF16 mode (FP64
+head/wings and inversion); the FP32 mode is timed the same way and reported
+beside it.  At this size both modes sum the transitions through energy panels,
+with the same FP32 operands (the FP32 mode splits its sums further); the same
+step with the transitions summed directly, where the modes are split-BF16 and
+plain FP32 MFMA, is reported as direct_sum.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME]
 Prints one JSON line.  --workload mixed-batch measures the batched engine
@@ -171,16 +174,17 @@ def bulk_flops_per_launch(wl):
 def bulk_roofline(direct_flops, pairs, n_t, seconds, tile, launches=1):
     """Roofline entry of the chi0 bulk of one launch.  Direct sum: its three
     BF16 products.  Through energy panels (tile["stages"] == 0): the moments of
-    16 basis functions, re and im, three products each, a lower bound of what
-    runs (the response of the frequencies comes on top); the rate that the
-    direct sum would need for the same time stands beside it."""
+    16 basis functions, re and im, on FP32 MFMA, a lower bound of what runs (the
+    response of the frequencies comes on top); the rate that the direct sum
+    would need for the same time stands beside it."""
     panels = tile["stages"] == 0
-    fl = 3.0 * 2.0 * 16 * 2 * pairs * n_t * launches if panels else 3.0 * direct_flops
-    r = {"bound": "mfma", "achieved": fl / seconds / 1e12, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-         "frac": fl / seconds / 1e12 / PEAK_BF16_TFLOPS,
+    fl = 2.0 * 16 * 2 * pairs * n_t * launches if panels else 3.0 * direct_flops
+    peak = PEAK_FP32_TFLOPS if panels else PEAK_BF16_TFLOPS
+    r = {"bound": "mfma", "achieved": fl / seconds / 1e12, "peak": peak, "unit": "TFLOP/s",
+         "frac": fl / seconds / 1e12 / peak,
          "kernel": "k_pan_* (sort, moments and response of the energy panels, head/wings included)"
                    if panels else "k_bulk<bf16> (chi0 bulk)",
-         "flops_per_launch_fp32_equiv": fl / 3.0}
+         "flops_per_launch_fp32_equiv": fl if panels else fl / 3.0}
     if panels:
         r["direct_sum_tflops_for_this_time"] = 3.0 * direct_flops / seconds / 1e12
     return r
@@ -234,12 +238,12 @@ def cpu_baseline(wl, n_w_sample, gpu_loss_split, gpu_loss_fp32, n_w_1thread=50):
 def composite_rooflines(wl, n_w, n_g, n_in, n_out, stm):
     """Rooflines of the composite step's two heavy kernels from the per-step
     stage times: the pair densities of every G (FP64) and the chi0 bulk (the
-    LFE block's pairs plus one diagonal pair per noLFE G; split BF16, three
+    LFE block's pairs plus one diagonal pair per noLFE G in split BF16, three
     products; the LFE block counted as the moments of its energy panels, see
     bulk_roofline).  Returns ({"rho": ..., "bulk": ...}, key of the dominant one)."""
     rho_fl = rho_flops_per_kg(wl.n_ao, wl.n_occ, wl.n_cond) * wl.n_k * n_g
     lfe_pairs = n_in * (n_in + 1) // 2 - n_in
-    bulk_fl = 3.0 * 2.0 * (2 * 16 * lfe_pairs + (2 * n_w) * 2 * n_out) * wl.n_t
+    bulk_fl = 2.0 * (2 * 16 * lfe_pairs + 3.0 * (2 * n_w) * 2 * n_out) * wl.n_t
     rho_s, bulk_s = 1e-3 * stm["pair_density_ms"], 1e-3 * stm["chi0_bulk_ms"]
     rl = {"rho": {"bound": "mfma", "achieved": rho_fl / rho_s / 1e12, "peak": PEAK_FP64_TFLOPS,
                   "unit": "TFLOP/s", "frac": rho_fl / rho_s / 1e12 / PEAK_FP64_TFLOPS,
@@ -1180,6 +1184,16 @@ def main():
         res[prec] = dict(sec=sec, st=st, loss0=loss_out[0].cpu().numpy().copy(),
                          tile=ctx.bulk_config())
 
+    # and with the transitions summed directly (a memory cap too large to bind
+    # keeps that route)
+    direct = {}
+    ctx.set_memory_limit(1 << 45)
+    n_dir = max(1, min(3, args.steps))
+    for prec in res:
+        sec_d, _ = timed(ctx, wl, qs, kf, prec, loss_out, n_dir, 1, torch)
+        direct[prec] = points * n_dir / sec_d
+    ctx.set_memory_limit(0)
+
     # the same step with the states handed over in host memory (pinned staging
     # and the PCIe copy inside the timed region): reported beside `value`
     kf_host = np.ascontiguousarray(wl.k_frac)
@@ -1209,6 +1223,7 @@ def main():
     avg_bulk_s = 1e-3 * s["st"]["chi0_bulk_ms"] / nb
     alg = bulk_flops_per_launch(wl)
     rl_bulk = bulk_roofline(alg, bulk_pairs(wl), wl.n_t, avg_bulk_s, s["tile"])
+    panels = s["tile"]["stages"] == 0
     out = {
         "metric": "(q,w) loss points/s at N_G=113: MFMA split vs plain FP32, rel err 1e-4",
         "value": value,
@@ -1220,12 +1235,14 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "bf16",
+        "dtype": "fp32" if panels else "bf16",
         "data": "synthetic",
         "config": {"workload": "Si-like fcc a=10.26, 28 GTO (3s2p1d per atom), 4+16 bands, "
                                "8^3 k, 10 q along [100], N_G=113, 400 w over 0-60 eV, eta=0.1 eV",
                    "n_g": n_g, "n_q": args.n_q, "n_w": n_w, "n_k": wl.n_k, "n_t": wl.n_t,
-                   "chi0_bulk": "split-bf16 MFMA, fp32 accumulation",
+                   "chi0_bulk": "energy panels: moments on FP32 MFMA, response in three bf16 planes "
+                                "(24 bits), fp32 accumulation"
+                                if panels else "split-bf16 MFMA, fp32 accumulation",
                    "head_wings": "fp64", "inversion": "fp64"},
         "roofline": {**rl_bulk, "traffic": None if s["tile"]["stages"] == 0 else recorded_traffic(),
                      "kernel_source_sha256_16": kernel_source_hash(),
@@ -1244,7 +1261,9 @@ def main():
                            "frac": rho_fl / rho_s / 1e12 / PEAK_FP64_TFLOPS,
                            "kernel": "k_cell_ft + k_rho_fused (per q, HIP events)",
                            "ms_per_q": 1e3 * rho_s, "flops_per_q": rho_fl}
+    out["direct_sum"] = {f"{p}_value": v for p, v in direct.items()}
     if "fp32" in res:
+        out["direct_sum"]["speedup_split_vs_fp32"] = direct["split_bf16"] / direct["fp32"]
         f = res["fp32"]
         nbf = max(1, f["st"]["bulk_launches"])
         avg32 = 1e-3 * f["st"]["chi0_bulk_ms"] / nbf

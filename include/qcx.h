@@ -596,8 +596,8 @@ int qcx_set_autotune(qcx_ctx* ctx, int mode);
 /* Configuration of the last bulk launch: cfg = {K split, pipeline (2 or 3 LDS stages;
  * 4: three stages with the transition slab one step ahead of the weights),
  * 0: through energy panels), row fragments per wave} (zeros if there was no
- * bulk), and the time spent
- * tuning in that call (ms, 0 when the shape was cached).  Errors:
+ * bulk: in FP64, by either route, and at n_G = 1 with FP64 head/wings), and the
+ * time spent tuning in that call (ms, 0 when the shape was cached).  Errors:
  * QCX_ESTATE before qcx_chi0. */
 int qcx_bulk_config(qcx_ctx* ctx, int cfg[3], double* tune_ms);
 /* Force the LDS pipeline of the chi0 bulk kernel (2, 3 or 4 as reported by

@@ -171,7 +171,7 @@ inline void panel_ranges(int n, int tile, long most, bool diag, std::vector<Pane
 // columns; their dozen small launches cost as much as a whole small problem.
 // The rates are least squares fits to both routes timed on MI355X at 70 random
 // sizes (3^3 to 8^3 k points, 20 to 181 G, 8 to 450 frequencies; nine in ten
-// within 12%, direct 18%, of the time).  Where the rule took the panels they
+// within 12% of the time, the direct sum's within 30%).  Where the rule took the panels they
 // never lost by more than 19%; where it did not they would have won by 47% at
 // most.
 struct PanelWork {

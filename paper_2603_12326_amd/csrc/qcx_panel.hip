@@ -47,6 +47,7 @@ bool pan_job_plan(PanelJob& j, const PanelSet& set, bool force) {
   s.P0 = P0;
   s.P = 2 * P0;
   pan_sort_geom(s);
+  if (s.max_act > 65535) return false;  // the coefficients' grid has a row per entry
   j.tasks.clear();
   j.ranges.clear();
   j.ranges64.clear();

@@ -118,8 +118,9 @@ extern "C" {
 
 const char* qcx_build_info(void) {
   return "libqcx gfx950: rho FP64 (Hermite FT, 27-cell Bloch sum on FP64 MFMA fused with the "
-         "band contraction), chi0 bulk FP32-MFMA "
-         "32x32x2 / split-BF16-MFMA 32x32x16 (hi*hi+hi*lo+lo*hi), FP64 head/wings, FP64 "
+         "band contraction), chi0 through energy panels (moments on FP32-MFMA 16x16x4, response in "
+         "three bf16 planes on BF16-MFMA 32x32x16; or FP64-MFMA) or summed directly on FP32-MFMA "
+         "32x32x2 / split-BF16-MFMA 32x32x16 (hi*hi+hi*lo+lo*hi) / FP64-MFMA, FP64 head/wings, FP64 "
          "Gauss-Jordan diag(eps^-1)";
 }
 

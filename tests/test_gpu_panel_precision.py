@@ -81,3 +81,37 @@ def test_absorptive_part(spread, g_lo, g_hi, eta, w_max, precision):
     err = np.max(np.abs(got - ref) / (d[:, None] * d))
     print(f"{precision}: {err:.2e}")
     assert err <= _BAR[precision]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("name", ["all_electron", "long_entries"])
+def test_against_fp64(name, precision):
+    """The all-electron basis (52 AOs, core levels to -1800 eV), and 170,368
+    transitions, whose entries are longer than their usual 1,024: both modes
+    within 1e-6 of the largest |chi0|, 16 units of their 24-bit operands."""
+    import torch
+
+    from paper_2603_12326_amd import Context
+    from synth import make_all_electron, make_si_ng113
+    from tests.gpu_helpers import set_inputs
+
+    if name == "all_electron":
+        wl, n_g, w = make_all_electron(n_w=200, kgrid=4), 97, np.linspace(0.0, 100.0, 200)
+    else:
+        wl, n_g, w = make_si_ng113(n_q=1, kgrid=11), 61, np.linspace(0.0, 60.0, 300)
+    chi = []
+    for direct in (True, False):
+        c = Context(0)
+        if direct:
+            c.set_memory_limit(1 << 42)
+        set_inputs(c, wl)
+        c.pair_density(wl.G_int[:n_g])
+        x = torch.empty((len(w), n_g, n_g), dtype=torch.complex128, device="cuda")
+        c.chi0(w, 0.1, "fp64" if direct else precision, True, x)
+        c.sync()
+        assert direct or c.bulk_config()["stages"] == 0
+        c.close()
+        chi.append(x)
+    err = float((chi[1] - chi[0]).abs().max() / chi[0].abs().max())
+    print(f"{name} {precision}: {err:.2e}")
+    assert err <= 1e-6

@@ -342,7 +342,9 @@ typedef struct qcx_item {
  * current pair densities (qcx_pair_density) and all must be on one device; the
  * work is enqueued on the stream of ctxs[0].  The chi0 bulk of all items runs
  * in one persistent launch over a shared tile list; the FP64 head/wings,
- * assembly, inversion and loss of every item follow.  The sequence is captured
+ * assembly, inversion and loss of every item follow.  A batch always sums the
+ * transitions directly (qcx_chi0 may take energy panels: where those pay, items
+ * run one by one can be the faster way).  The sequence is captured
  * once per batch signature (items, frequencies, buffers) into a hipGraph owned
  * by ctxs[0] and replayed on later calls with the same signature; new states
  * or pair densities of the same shapes are picked up by the replay.
